@@ -2054,7 +2054,7 @@ kvop_status kvop_debug_gemm(int32_t dtype, int32_t out_dtype, int32_t epi, int32
   int odt = out_dtype == KVOP_F32 ? DT_F32 : DT_BF16;
   if (dt == DT_F32 && odt != DT_F32) return fail(KVOP_EINVAL, "f32 operands produce f32 results");
   GemmShape s{M, N, K, lda, ldb, ldc};
-  if (tile < 0) tile = gemm_pick_tile(dt, epi, s);
+  if (tile < 0) tile = gemm_pick_tile(dt, epi, s, (((uintptr_t)A | (uintptr_t)B) & 15) == 0);
   if (!gemm_tile_ok(dt, tile, s, epi)) return fail(KVOP_EINVAL, "tile cannot run this shape");
   HIPTRY(gemm(dt, odt, epi, tile, A, B, Cm, s, (hipStream_t)stream));
   return KVOP_OK;
@@ -2069,7 +2069,7 @@ kvop_status kvop_debug_gemm_rope(int32_t tile, const void* A, const void* B, voi
   hipStream_t st = (hipStream_t)stream;
   GemmShape s{M, N, K, K, K, N};
   const int epi = fused ? EPI_ROPE : EPI_STORE;
-  if (tile < 0) tile = gemm_pick_tile(DT_BF16, epi, s);
+  if (tile < 0) tile = gemm_pick_tile(DT_BF16, epi, s, (((uintptr_t)A | (uintptr_t)B) & 15) == 0);
   if (!gemm_tile_ok(DT_BF16, tile, s, epi)) return fail(KVOP_EINVAL, "tile cannot run this shape");
   if (fused) {
     const RopeEpi re{pos_dev, cos_dev, sin_dev, head_dim, rot_cols, 0, nullptr, nullptr, 1};

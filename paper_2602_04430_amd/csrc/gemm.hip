@@ -22,10 +22,22 @@
 
 namespace kvop {
 
+// Few rows (a single document, a map's decoding steps): the projection is bound by how fast the
+// weights reach the CUs.  One CU streams about 45 GB/s from HBM whatever it keeps in flight
+// (64 CUs 2.7 TB/s, 128 CUs 4.8 TB/s), so the tile must be narrow enough that the columns
+// spread over many CUs.  The narrow direct-load tiles stage 128- or 256-deep slabs (96-160 KiB
+// of LDS in flight) and add wavefronts that only load, since one wavefront issuing all loads of
+// a slab between its MFMAs is slower (16x32, one wavefront: down 24 us; four: 18).  K is never
+// split: an output's products are added in the same order by every tile, so the choice keeps
+// the bits.  Weights from HBM, M = 32: QKV 34 -> 9.1, O 33 -> 8.3, gate/up 36 -> 13.2, down
+// 88 -> 13.9 us (64x128 register-staged tile before); M = 192: 39 -> 14, 40 -> 10.5, 41 -> 22,
+// 98 -> 22.6 us; M = 2048: 45 -> 36, 42 -> 26, 124 -> 93, 97 -> 57 us (128x128 before).
+//
 // SWZ selects the LDS layout of a K-slab row (CPR 16-byte chunks):
 //   0: padded rows (BK + one chunk) — chunk c of row r at r*LDK + c*VEC
 //   1: unpadded, chunk c of row r stored at slot c ^ ((r >> 1) & (CPR-1))
-//   2: unpadded, chunk c of row r stored at slot c ^ (r & (CPR-1))
+//   2: unpadded, chunk c of row r stored at slot c ^ (r & (CPR-1) & 15) (16 rows of one chunk
+//      column then sit in 16 distinct chunks: every bank once)
 // NS = 0: slabs staged through registers (two LDS buffers); NS >= 2: slabs fetched by
 // direct global -> LDS loads into NS buffers, completion tracked with explicit vmcnt waits
 // (every thread issues the same number of loads per slab), K a multiple of BK.
@@ -54,12 +66,13 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B,
   constexpr int KSUB = 4 * VEC;             // K consumed per MFMA step group
   auto slot = [](int r, int c) {            // LDS chunk slot of logical chunk c in row r
     if constexpr (SWZ == 1) return c ^ ((r >> 1) & (CPR - 1));
-    else if constexpr (SWZ == 2) return c ^ (r & (CPR - 1));
+    else if constexpr (SWZ == 2) return c ^ (r & (CPR - 1) & 15);
     else if constexpr (SWZ == 3) return c ^ ((r >> 2) & (CPR - 1));
     else return c;
   };
   static_assert(NS == 0 || SWZ != 0, "direct loads write unpadded rows");
-  static_assert((BM / WM) * (BN / WN) == NW, "one wavefront per sub-tile");
+  constexpr int NWC = (BM / WM) * (BN / WN);   // wavefronts that own a sub-tile; the rest only load
+  static_assert(NWC == NW || (NWC < NW && NS >= 2 && SCH == 0), "one wavefront per sub-tile");
   static_assert(ACH * NT == BM * CPR && BCH * NT == BN * CPR, "tile/thread mismatch");
   static_assert(EPI != EPI_SWIGLU || (NI % 2 == 0), "swiglu needs gate/up block pairs");
 
@@ -152,16 +165,32 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B,
   // direct loads of slab k0 into buffer buf: chunk f = i NT + 64 wave + lane lands at LDS
   // chunk f (row f / CPR, slot f % CPR) and holds logical chunk slot(row, f % CPR) (the
   // XOR swizzle is its own inverse); rows past M / N read the last row (never stored)
+  // slabs deeper than 64 may end past K (a multiple of 64): the chunks past it read the last one
+  // of the row and the MFMA steps past it are not run
+  auto k_of = [&](int k0, int c) {
+    if constexpr (BK > 64) return min(k0 + c * VEC, K - VEC);
+    else return k0 + c * VEC;
+  };
   auto dma_a = [&](int k0, int bf) {
     T* As = a_base(bf);
 #pragma unroll
     for (int i = 0; i < ACH; i++) {
       const int f = tid + i * NT, r = f / CPR, c = slot(r, f % CPR);
       const uint8_t* g = reinterpret_cast<const uint8_t*>(
-          A + (int64_t)min(m0 + r, M - 1) * lda + k0 + c * VEC);
+          A + (int64_t)min(m0 + r, M - 1) * lda + k_of(k0, c));
       uint8_t* l = reinterpret_cast<uint8_t*>(As + (i * NT + 64 * wave) * VEC);
       __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)l, 16, 0, 0);
     }
+  };
+  // Rotary epilogue on a tile narrower than a head: the tile holds the BN/2 columns from cb of
+  // the head's first half and the matching BN/2 columns of its second half, so that both
+  // members of every rotated pair are in one tile
+  const bool pair_cols = EPI == EPI_ROPE && BN < 128 && rp.D > BN;
+  const int cb = pair_cols ? n0 / rp.D * rp.D + n0 % rp.D / 2 : n0;
+  auto b_row = [&](int r) {
+    if constexpr (EPI == EPI_ROPE && BN < 128)
+      return cb + r + (pair_cols && r >= BN / 2 ? (rp.D - BN) / 2 : 0);
+    else return n0 + r;
   };
   auto dma_b = [&](int k0, int bf) {
     T* Bs = b_base(bf);
@@ -169,7 +198,7 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B,
     for (int i = 0; i < BCH; i++) {
       const int f = tid + i * NT, r = f / CPR, c = slot(r, f % CPR);
       const uint8_t* g = reinterpret_cast<const uint8_t*>(
-          B + (int64_t)min(n0 + r, N - 1) * ldb + k0 + c * VEC);
+          B + (int64_t)min(b_row(r), N - 1) * ldb + k_of(k0, c));
       uint8_t* l = reinterpret_cast<uint8_t*>(Bs + (i * NT + 64 * wave) * VEC);
       __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)l, 16, 0, 0);
     }
@@ -307,8 +336,7 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B,
     }
     const T* As = smem + buf * STAGE + (wm * WM) * LDK;
     const T* Bs = smem + buf * STAGE + BM * LDK + (wn * WN) * LDK;
-#pragma unroll
-    for (int ks = 0; ks < BK; ks += KSUB) {
+    auto mfma_step = [&](int ks) __attribute__((always_inline)) {
       u32x4 af[MI], bfr[NI];
 #pragma unroll
       for (int i = 0; i < MI; i++)
@@ -331,6 +359,14 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B,
           for (int j = 0; j < NI; j++)
             acc[i][j] = mfma_bf16(__builtin_bit_cast(u16x8, af[i]), __builtin_bit_cast(u16x8, bfr[j]), acc[i][j]);
       }
+    };
+    if (NWC < NW && wave >= NWC) continue;
+    if (NS == 0 || BK <= 64 || (kt + 1) * BK <= K) {
+#pragma unroll
+      for (int ks = 0; ks < BK; ks += KSUB) mfma_step(ks);
+    } else {
+#pragma unroll 1
+      for (int ks = 0; kt * BK + ks < K; ks += KSUB) mfma_step(ks);
     }
     if constexpr (NS == 0) {
       if (kt + 1 < nk) sstore(buf ^ 1);
@@ -356,6 +392,7 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B,
     // rows 2-3 of the pair as packed BF16 pairs, one 4-byte store each.
     const bool odd = lane & 1;
     const int prow = 4 * (lane >> 4) + (odd ? 2 : 0), pcol = (lane & 15) & ~1;
+    if (NWC == NW || wave < NWC)
 #pragma unroll
     for (int i = 0; i < MI; i++)
 #pragma unroll
@@ -373,14 +410,16 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B,
         *reinterpret_cast<uint32_t*>(t + TP) = w1;
       }
     __syncthreads();
-    const int D = rp.D, half = D >> 1, gph = half >> 3;     // 8-pair groups per head
-    const int upr = (BN / D) * gph;                           // groups per tile row
+    const int D = rp.D, half = D >> 1;                       // pair distance in C
+    const int hw = pair_cols ? BN : D, pd = hw >> 1;         // pair distance in the tile
+    const int gph = pd >> 3;                                  // 8-pair groups per head (part)
+    const int upr = (BN / hw) * gph;                          // groups per tile row
     bf16_t* C = reinterpret_cast<bf16_t*>(Cv);
     bf16_t* Qa = reinterpret_cast<bf16_t*>(rp.q_alt);
     // BM * BN / 16 groups whatever D is: a fixed count per thread, fully unrolled so that the
     // position and table loads of all of them can be in flight together
-    constexpr int NU = BM * BN / 16 / NT;
-    static_assert(NU * 16 * NT == BM * BN, "rotary groups per thread");
+    constexpr int NG = BM * BN / 16, NU = (NG + NT - 1) / NT;
+    static_assert(NU * NT == NG || NU == 1, "rotary groups per thread");
     // phase 1: which group (row, head, 8 dimensions) each of this thread's NU groups is, and
     // its row's position; phase 2: the table rows at those positions; phase 3: rotate and
     // store.  No load sits behind a branch, so the loads of every group are in flight at once.
@@ -388,12 +427,12 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B,
     int gm_[NU], col_[NU], off_[NU], p_[NU];
 #pragma unroll
     for (int k = 0; k < NU; k++) {
-      const int u = tid + NT * k;
+      const int u = NG < NT ? min(tid, NG - 1) : tid + NT * k;
       const int row = u / upr, w = u - row * upr;
       const int hh = w / gph, i = (w - hh * gph) * 8;
       gm_[k] = m0 + row;
-      col_[k] = n0 + hh * D + i;
-      off_[k] = row * TP + hh * D + i;
+      col_[k] = cb + hh * hw + i;
+      off_[k] = row * TP + hh * hw + i;
       p_[k] = rp.pos[(int64_t)min(gm_[k], M - 1) * ps];
     }
     f32x4 ct_[NU][2], st_[NU][2];
@@ -411,8 +450,9 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B,
     for (int k = 0; k < NU; k++) {
       const int gm = gm_[k], col = col_[k];
       if (gm >= M || col >= N) continue;                    // N is a multiple of D
+      if (NG < NT && tid >= NG) continue;
       const u32x4 r1 = *reinterpret_cast<const u32x4*>(Tt + off_[k]);
-      const u32x4 r2 = *reinterpret_cast<const u32x4*>(Tt + off_[k] + half);
+      const u32x4 r2 = *reinterpret_cast<const u32x4*>(Tt + off_[k] + pd);
       bf16_t* c1 = C + (int64_t)gm * ldc + col;
       if (col >= rp.rot_cols) {
         *reinterpret_cast<u32x4*>(c1) = r1;
@@ -467,10 +507,11 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B,
   constexpr bool OUT_BF16 = sizeof(TO) == 2;
   constexpr int VW = OUT_BF16 ? 8 : 4;                      // output elements per 16-byte access
   constexpr int LPR = OW / VW;                              // lanes per row
-  constexpr int RPP = 64 / LPR;                             // rows per pass
+  constexpr int RPP = 64 / LPR < 16 ? 64 / LPR : 16;        // rows per pass (narrow outputs: lanes left over)
   static_assert(64 % LPR == 0 && 16 % RPP == 0, "epilogue lane split");
-  static_assert(NW * 16 * EP * 4 <= (NS == 0 ? 2 : NS) * (BM + BN) * LDK * (int)sizeof(T),
+  static_assert(NWC * 16 * EP * 4 <= (NS == 0 ? 2 : NS) * (BM + BN) * LDK * (int)sizeof(T),
                 "epilogue staging fits the slab buffers");
+  if (NWC < NW && wave >= NWC) return;
   const int n_out = EPI == EPI_SWIGLU ? N / 2 : N;
   const int col0 = (EPI == EPI_SWIGLU ? (n0 + wn * WN) / 2 : n0 + wn * WN);
   float* E = reinterpret_cast<float*>(smem_raw) + wave * 16 * EP;
@@ -494,7 +535,7 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B,
       const int rr = pass * RPP + lane / LPR, cc = (lane % LPR) * VW;
       const int row = row_base + rr, col = col0 + cc;
       const float* e = E + rr * EP + cc;
-      if (row < M) {
+      if (row < M && rr < 16) {
         if (vec_ok && col + VW <= n_out) {
           if constexpr (OUT_BF16) {
             u32x4 pk;
@@ -558,9 +599,22 @@ static const TileCfg kBf16Tiles[] = {
     {256, 256, 64, 128, 64, 1, 8, 2, "bf16_256x256x64_8w_w128x64_swz1_lds2_pipe_g4"},
     {256, 256, 64, 128, 64, 1, 8, 2, "bf16_256x256x64_8w_w128x64_swz1_lds2b3_pipe_g4"},
     {256, 256, 64, 128, 64, 1, 8, 2, "bf16_256x256x64_8w_w128x64_swz1_lds2a3_pipe_g4"},
+    // few rows: 16x16 per computing wavefront, the other wavefronts only load.  SwiGLU (16 gate + 16
+    // up columns per wavefront) and the rotary epilogue (pairs) take 32 columns in both.
+    {32, 16, 256, 16, 32, 2, 8, 4, "bf16_32x16x256_8w_swz2_lds4"},
+    {32, 32, 256, 16, 32, 2, 8, 4, "bf16_32x32x256_8w_swz2_lds4"},
+    {32, 64, 256, 16, 32, 2, 4, 3, "bf16_32x64x256_w16x32_swz2_lds3"},
+    {64, 32, 256, 16, 32, 2, 4, 3, "bf16_64x32x256_w16x32_swz2_lds3"},
+    {64, 64, 128, 32, 32, 2, 4, 5, "bf16_64x64x128_w32x32_swz2_lds5"},
+    {64, 128, 64, 32, 64, 2, 4, 3, "bf16_64x128x64_w32x64_swz2_lds3"},
+    {64, 128, 128, 32, 64, 2, 4, 3, "bf16_64x128x128_w32x64_swz2_lds3"},
+    {128, 128, 64, 64, 64, 2, 4, 2, "bf16_128x128x64_w64x64_swz2_lds2"},
+    {128, 128, 64, 64, 64, 2, 4, 4, "bf16_128x128x64_w64x64_swz2_lds4_pipe"},
+    {256, 128, 64, 64, 64, 2, 8, 3, "bf16_256x128x64_8w_w64x64_swz2_lds3_pipe"},
+    {128, 256, 64, 64, 64, 2, 8, 3, "bf16_128x256x64_8w_w64x64_swz2_lds3_pipe"},
 };
 
-int gemm_num_tiles(int dt) { return dt == DT_F32 ? 4 : 27; }
+int gemm_num_tiles(int dt) { return dt == DT_F32 ? 4 : (int)(sizeof(kBf16Tiles) / sizeof(kBf16Tiles[0])); }
 const char* gemm_tile_name(int dt, int t) { return dt == DT_F32 ? kF32Tiles[t].name : kBf16Tiles[t].name; }
 
 static const TileCfg& tile_cfg(int dt, int t) { return dt == DT_F32 ? kF32Tiles[t] : kBf16Tiles[t]; }
@@ -571,8 +625,9 @@ bool gemm_tile_ok(int dt, int t, const GemmShape& s, int epi) {
   int vec = dt == DT_F32 ? 4 : 8;
   if (s.K % vec || s.lda % vec || s.ldb % vec) return false;
   if (epi == EPI_SWIGLU && (s.N % 32 || (c.WN % 32))) return false;
-  if (epi == EPI_ROPE && (dt != DT_BF16 || c.BN % 128)) return false;   // whole heads of D <= 128 per tile
-  if (c.NS && s.K % c.BK) return false;   // direct-load tiles read whole slabs only
+  // whole heads per tile, or both halves of a part of one (direct-load tiles narrower than 128)
+  if (epi == EPI_ROPE && (dt != DT_BF16 || (c.BN % 128 && c.NS == 0))) return false;
+  if (c.NS && s.K % std::min(c.BK, 64)) return false;   // direct-load tiles read whole slabs (or 64-deep parts)
   return true;
 }
 
@@ -635,7 +690,20 @@ static hipError_t launch_cfg(int tile, const void* A, const void* B, void* C, co
       case 23: return launch_t<T, TO, EPI, 256, 128, 32, 128, 64, 3, 4, 2, 1>(A, B, C, s, st, rp);
       case 24: return launch_t<T, TO, EPI, 256, 256, 64, 128, 64, 1, 8, 2, 1>(A, B, C, s, st, rp, 4);
       case 25: return launch_t<T, TO, EPI, 256, 256, 64, 128, 64, 1, 8, 2, 1, 3>(A, B, C, s, st, rp, 4);
-      default: return launch_t<T, TO, EPI, 256, 256, 64, 128, 64, 1, 8, 2, 1, 0, 3>(A, B, C, s, st, rp, 4);
+      case 26: return launch_t<T, TO, EPI, 256, 256, 64, 128, 64, 1, 8, 2, 1, 0, 3>(A, B, C, s, st, rp, 4);
+      case 27: return launch_t<T, TO, EPI, 32, EPI == EPI_SWIGLU || EPI == EPI_ROPE ? 32 : 16, 256, 16,
+                               EPI == EPI_SWIGLU ? 32 : 16, 2, 8, 4>(A, B, C, s, st, rp);
+      case 28: return launch_t<T, TO, EPI, 32, 32, 256, 16, EPI == EPI_SWIGLU ? 32 : 16, 2, 8, 4>(A, B, C, s, st, rp);
+      case 29: return launch_t<T, TO, EPI, 32, 64, 256, 16, 32, 2, 4, 3>(A, B, C, s, st, rp);
+      case 30: return launch_t<T, TO, EPI, 64, 32, 256, 16, 32, 2, 4, 3>(A, B, C, s, st, rp);
+      case 31: return launch_t<T, TO, EPI, 64, 64, 128, 32, 32, 2, 4, 5>(A, B, C, s, st, rp);
+      case 32: return launch_t<T, TO, EPI, 64, 128, 64, 32, 64, 2, 4, 3>(A, B, C, s, st, rp);
+      case 33: return launch_t<T, TO, EPI, 64, 128, 128, 32, 64, 2, 4, 3>(A, B, C, s, st, rp);
+      case 34: return launch_t<T, TO, EPI, 128, 128, 64, 64, 64, 2, 4, 2>(A, B, C, s, st, rp);
+      case 35: return launch_t<T, TO, EPI, 128, 128, 64, 64, 64, 2, 4, 4, 1>(A, B, C, s, st, rp);
+      case 36: return launch_t<T, TO, EPI, 256, 128, 64, 64, 64, 2, 8, 3, 1>(A, B, C, s, st, rp);
+      case 37: return launch_t<T, TO, EPI, 128, 256, 64, 64, 64, 2, 8, 3, 1>(A, B, C, s, st, rp);
+      default: return hipErrorInvalidValue;
     }
   }
 }
@@ -701,16 +769,38 @@ bool gemm_tuned_import_line(int dt, int epi, int N, int K, int mb, const std::st
   return false;
 }
 
-int gemm_pick_tile(int dt, int epi, const GemmShape& s) {
-  if (epi == EPI_ROPE) epi = EPI_STORE;   // same main loop; the store epilogue's tuning applies
-  auto it = tuned().find({dt, epi, s.N, s.K, mbucket(s.M)});
-  if (it != tuned().end() && gemm_tile_ok(dt, it->second, s, epi)) return it->second;
+int gemm_pick_tile(int dt, int epi, const GemmShape& s, bool aligned) {
+  // same main loop: the store epilogue's tuning applies to the rotary one
+  auto it = tuned().find({dt, epi == EPI_ROPE ? EPI_STORE : epi, s.N, s.K, mbucket(s.M)});
+  if (it != tuned().end() && gemm_tile_ok(dt, it->second, s, epi) &&
+      (aligned || tile_cfg(dt, it->second).NS == 0))
+    return it->second;
   if (dt == DT_F32) return s.M <= 64 ? 1 : 0;
-  if (s.M <= 128) return 3;        // 64x128
-  if (s.M < 8192) return 7;        // 128x128, 4 wavefronts
-  if (gemm_tile_ok(dt, 26, s, epi)) return 26;  // 256x256, 8 wavefronts of 128x64, direct loads, pipelined,
-                                                // groups of 4 M-tiles, a third A-slab stage
-  return 11;                       // 256x256, 8 wavefronts of 64x128
+  // The tile with the least estimated time: rounds of resident workgroups over the 256 CUs,
+  // each taking a + b K / 1024 microseconds.  a and b are fits to the O (K = 2048) and down
+  // (K = 5632) projections timed with weights not in any cache, at row counts where one round
+  // is nearly full; every tile gives the same bits, so the choice is a matter of time only.
+  // Few rows: the time is a CU's share of the weights, so narrow tiles spread them over more
+  // CUs (M = 32, down: 88 us with the 16 workgroups of 64x128, 16 us with 64 of 32x32).
+  // Many rows: the larger the tile the fewer bytes per MFMA, until a round is not filled.
+  struct Cand { int tile, per_cu; float a, b; };
+  static const Cand cands[] = {
+      {27, 1, 4.7f, 1.6f}, {28, 1, 3.9f, 2.2f}, {29, 1, 3.5f, 3.3f}, {30, 1, 3.6f, 3.1f}, {31, 1, 4.7f, 4.3f},
+      {33, 1, 5.4f, 6.3f}, {32, 2, 5.7f, 12.2f}, {35, 1, 5.6f, 9.2f}, {34, 2, 9.0f, 17.6f}, {36, 1, 7.8f, 12.1f},
+      {37, 1, 8.3f, 12.4f}, {26, 1, 12.7f, 20.4f}};
+  int best = -1;
+  double best_t = 0.0;
+  for (const Cand& c : cands) {
+    if (!aligned) break;   // direct global -> LDS loads move aligned 16-byte chunks
+    if (!gemm_tile_ok(dt, c.tile, s, epi) || (c.tile == 27 && (epi == EPI_SWIGLU || epi == EPI_ROPE))) continue;
+    const TileCfg& t = kBf16Tiles[c.tile];
+    const int64_t tiles = (int64_t)((s.M + t.BM - 1) / t.BM) * ((s.N + t.BN - 1) / t.BN);
+    const double us = (double)((tiles + 256 * c.per_cu - 1) / (256 * c.per_cu)) * (c.a + c.b * s.K / 1024.0);
+    if (best < 0 || us < best_t) { best = c.tile; best_t = us; }
+  }
+  if (best >= 0) return best;
+  // K not a multiple of 64, or operands off 16-byte boundaries: register-staged tiles
+  return s.M <= 128 ? 3 : (s.M < 8192 ? 7 : 11);
 }
 
 }  // namespace kvop

@@ -43,8 +43,9 @@ hipError_t gemm(int dt, int out_dt, int epi, int tile, const void* A, const void
                 hipStream_t st, const RopeEpi* rope = nullptr);
 // head dims the rotary epilogue serves (whole heads in every BF16 tile, 8-pair groups)
 bool gemm_rope_supported(int D);
-// default tile for a shape (from the tuned table when present)
-int gemm_pick_tile(int dt, int epi, const GemmShape& s);
+// tile for a shape: the tuned table's, else the one of least estimated time; aligned: A and B
+// start on 16-byte boundaries (otherwise only register-staged tiles are taken)
+int gemm_pick_tile(int dt, int epi, const GemmShape& s, bool aligned = true);
 void gemm_set_tuned(int dt, int epi, int N, int K, int mbucket, int tile);
 int gemm_mbucket(int M);
 // tuning table as text lines "dtype epilogue N K mbucket tile_name"
