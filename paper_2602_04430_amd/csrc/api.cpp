@@ -303,6 +303,17 @@ struct LayerPlan {
   void select_one(int n, int stride, int off) { n_groups = 1; sel[0] = SelGroup{n, stride, off}; }
 };
 
+// what the attention launcher goes by: the longest work item's keys and the sum over all
+void count_keys(const std::vector<AttnWork>& work, AttnArgs* a) {
+  a->longest_keys = 0;
+  a->total_keys = 0;
+  for (const AttnWork& w : work) {
+    const int k = std::max(w.n_a, w.pad_a) + w.n_b + w.n_own;
+    a->longest_keys = std::max(a->longest_keys, k);
+    a->total_keys += k;
+  }
+}
+
 // skip_tail: stop once this layer's keys/values exist (prefill's last layer when the final
 // hidden states are not needed)
 kvop_status run_layer(kvop_model* m, int l, const LayerBufs& b, LayerPlan& lp, uint8_t* pool, int kvdt,
@@ -834,6 +845,7 @@ static kvop_status kv_build_impl(kvop_pool* p, const int32_t* tokens, const int6
     lp.alt_shift = nullptr;
     lp.attn.work = (const AttnWork*)(md + o_work);
     lp.attn.n_work = (int)work.size();
+    count_keys(work, &lp.attn);
     lp.attn.idx = nullptr;
     lp.attn.Pmax = Pmax;
     lp.own_from_qkv = false;
@@ -1203,6 +1215,7 @@ static kvop_status op_eval_impl(kvop_pool* p, const kvop_op* op, float r, const 
     lp.alt_shift = join ? (const int32_t*)(md + o_shift) : nullptr;
     lp.attn.work = (const AttnWork*)(md + o_work);
     lp.attn.n_work = (int)work.size();
+    count_keys(work, &lp.attn);
     lp.attn.idx = idx;
     lp.attn.Pmax = Pmax_s;
     lp.own_from_qkv = true;
@@ -1667,6 +1680,7 @@ kvop_status kvop_mixed_eval(kvop_pool* p, const kvop_mixed_op* ops, int32_t n_op
       lp.alt_shift = any_join ? (const int32_t*)(md + o_shift) : nullptr;
       lp.attn.work = (const AttnWork*)(md + o_work);
       lp.attn.n_work = (int)work.size();
+      count_keys(work, &lp.attn);
       lp.attn.idx = idx;
       lp.attn.Pmax = Pmax;
       lp.attn.counter = persistent ? counter : nullptr;

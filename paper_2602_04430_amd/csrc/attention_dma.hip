@@ -10,6 +10,15 @@
 // workgroup.  Completion is tracked with explicit vmcnt waits: every wavefront issues the
 // same number of vector-memory operations per tile.
 //
+// What bounds it: many long units, HBM (4.4 TB/s with a BF16 cache, 1024 documents of the scale
+// workload's lengths; 763 us a launch); a single unit, the chain of one tile's step (wait,
+// scores, maximum, exponentials, value product).  The loop is written for that chain: the three
+// cursors below step through a source with a few scalar operations (forming every tile's
+// addresses from the descriptors of all three sources took half of the loop's instructions), the
+// maximum crosses lanes without LDS, and no register load can make the compiler wait for the
+// tiles in flight (a conditional query load did, at every tile).  One unit of 4096 keys: 189 ->
+// 113 us (1.47 -> 0.88 us a tile); FP8 cache, 1024 documents: 712 -> 550 us.
+//
 // LDS layout of a tile part (K or V): rows in the source dtype (FP8 cache rows, BF16
 // cache or own rows), chunk c of row r at slot c ^ swz(r).  The K swizzle spreads the 16
 // rows read at one chunk by an S^T operand over distinct banks; the V swizzle does the
@@ -19,6 +28,7 @@
 // value is a BF16 value) and their per-16-row block scales multiply scores and
 // probabilities as in the register-staged kernel.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "kernels.h"
@@ -43,23 +53,23 @@ struct DmaCfg {
   static constexpr int NJ = 2 * REGION / 16 / 256;   // chunk loads per thread per tile
   static constexpr int NR = NJ / 2;                  // rows per thread per tile (K and V chunks share them)
   static_assert(NJ >= 2 && NJ % 2 == 0, "tile split");
-  static constexpr int META = 3 * 64 * 4;            // ksc | vsc | unused (64 slots each)
+  static constexpr int META = FP8 ? 3 * 64 * 4 : 0;  // ksc | vsc | unused (64 slots each)
   static constexpr int STAGE = 2 * REGION + META;
-  static constexpr int RING = NS * STAGE;            // row-number ring: NS + 1 slots of 64
-  static constexpr int LDS = RING + (NS + 1) * 64 * 4;
+  static constexpr int LEAD = NS - 1;                // row numbers are loaded LEAD tiles before their chunks
+  static constexpr int NRING = NS + LEAD;            // row-number ring: tiles ti .. ti + NS - 1 + LEAD
+  static constexpr int RING = NS * STAGE;
+  static constexpr int LDS = RING + NRING * 64 * 4;
   static constexpr int LDS_TOTAL = LDS;
-  // vmcnt that leaves only the newest tile's chunk + metadata loads outstanding
-  static constexpr int WAIT = NS >= 3 ? NJ + 1 : 0;
-  static_assert(NJ + 1 <= 15, "vmcnt immediates");
-  static_assert(NS == 2 || NS == 3, "stages");
+  static constexpr int OPS = NJ + (FP8 ? 1 : 0);     // vector-memory operations of one tile (chunks, FP8 scales)
+  static_assert((NS - 2) * (OPS + 1) <= 63 && NS >= 2, "vmcnt immediates");
 };
 
 // log2(16 / CH): consecutive rows that share one 256-byte bank line
 template <int CH> struct RowShift {
   static constexpr int v = CH >= 16 ? 0 : (CH == 8 ? 1 : (CH == 4 ? 2 : 3));
 };
-template <int CH> __device__ inline int swz_k(int r) { return (r >> RowShift<CH>::v) & (CH - 1); }
-template <int CH> __device__ inline int swz_v(int r) { return CH >= 4 ? 2 * ((r >> RowShift<CH>::v) & (CH / 2 - 1)) : 0; }
+template <int CH> __host__ __device__ constexpr int swz_k(int r) { return (r >> RowShift<CH>::v) & (CH - 1); }
+template <int CH> __host__ __device__ constexpr int swz_v(int r) { return CH >= 4 ? 2 * ((r >> RowShift<CH>::v) & (CH / 2 - 1)) : 0; }
 // V swizzle of FP8 rows (read by ds_read_b64_tr_b8: rows r, r + 1, r + 2, r + 3 and the
 // same + 16 at one chunk, for two lane groups): distinct (slot, bank line half) pairs
 template <int CH> __device__ inline int swz_v8(int r) {
@@ -73,40 +83,59 @@ template <int N> __device__ inline void vm_wait() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
-// ds_read_b64_tr_b16 as inline assembly.  The builtin form makes the compiler wait for every
-// direct-to-LDS load in flight (vmcnt(0)) before it, since it cannot tell which LDS bytes
-// the read touches.  The assembly form is followed by an explicit lgkmcnt(0) wait; the
-// caller reads V only from stages whose loads have completed (checked by the tile wait).
-// The result may only be used after lgkm_wait_all() has taken it as an operand.
-__device__ inline u32x2 ds_read_tr16(const uint8_t* p) {
-  const uint32_t addr = (uint32_t)reinterpret_cast<uintptr_t>(p);
-  u32x2 v;
-  asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(v) : "v"(addr) : "memory");
-  return v;
+// waits until only `behind` (0 .. MAXB, uniform) tiles of OPS operations and ROWS row-number loads
+// are outstanding
+template <int MAXB, int OPS, int ROWS> __device__ inline void vm_wait_behind(int behind) {
+  if constexpr (MAXB < 0) {
+    vm_wait<0>();
+  } else {
+    if (behind >= MAXB) vm_wait<MAXB * OPS + ROWS>();
+    else vm_wait_behind<MAXB - 1, OPS, ROWS>(behind);
+  }
 }
-__device__ inline u32x2 ds_read_tr8(const uint8_t* p) {
-  const uint32_t addr = (uint32_t)reinterpret_cast<uintptr_t>(p);
-  u32x2 v;
-  asm volatile("ds_read_b64_tr_b8 %0, %1" : "=v"(v) : "v"(addr) : "memory");
-  return v;
+
+// Transposed LDS reads as inline assembly, each block with its own wait.  (The builtin form makes
+// the compiler wait for every direct-to-LDS load in flight (vmcnt(0)) before it, since it
+// cannot tell which LDS bytes the read touches.)  The caller reads V only from stages whose
+// loads have completed (checked by the tile wait).
+__device__ inline uint32_t lds_addr(const uint8_t* p) { return (uint32_t)reinterpret_cast<uintptr_t>(p); }
+// y[2 i] from address ad[i], y[2 i + 1] from ad[i] + STEP
+template <int STEP> __device__ inline void ds_read_tr16_x8(const uint32_t (&ad)[4], u32x2 (&y)[8]) {
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %8\n\tds_read_b64_tr_b16 %1, %8 offset:%c12\n\t"
+      "ds_read_b64_tr_b16 %2, %9\n\tds_read_b64_tr_b16 %3, %9 offset:%c12\n\t"
+      "ds_read_b64_tr_b16 %4, %10\n\tds_read_b64_tr_b16 %5, %10 offset:%c12\n\t"
+      "ds_read_b64_tr_b16 %6, %11\n\tds_read_b64_tr_b16 %7, %11 offset:%c12\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(y[0]), "=&v"(y[1]), "=&v"(y[2]), "=&v"(y[3]), "=&v"(y[4]), "=&v"(y[5]), "=&v"(y[6]), "=&v"(y[7])
+      : "v"(ad[0]), "v"(ad[1]), "v"(ad[2]), "v"(ad[3]), "i"(STEP)
+      : "memory");
 }
-// lgkmcnt(0), tied to the values it guards so that no use is scheduled above it
-template <int N> __device__ inline void lgkm_wait_all(u32x2 (&v)[N]);
-template <> __device__ inline void lgkm_wait_all<4>(u32x2 (&v)[4]) {
-  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]) : : "memory");
+__device__ inline void ds_read_tr8_x4(const uint32_t (&ad)[4], u32x2 (&y)[4]) {
+  asm volatile(
+      "ds_read_b64_tr_b8 %0, %4\n\tds_read_b64_tr_b8 %1, %5\n\t"
+      "ds_read_b64_tr_b8 %2, %6\n\tds_read_b64_tr_b8 %3, %7\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(y[0]), "=&v"(y[1]), "=&v"(y[2]), "=&v"(y[3])
+      : "v"(ad[0]), "v"(ad[1]), "v"(ad[2]), "v"(ad[3])
+      : "memory");
 }
-template <> __device__ inline void lgkm_wait_all<8>(u32x2 (&v)[8]) {
-  asm volatile("s_waitcnt lgkmcnt(0)"
-               : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7])
-               :
-               : "memory");
+
+// m c - mc with the product rounded first
+__device__ inline float scaled_minus(float m, float c, float mc) {
+#pragma clang fp contract(off)
+  return m * c - mc;
 }
-template <> __device__ inline void lgkm_wait_all<16>(u32x2 (&v)[16]) {
-  asm volatile("s_waitcnt lgkmcnt(0)"
-               : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]),
-                 "+v"(v[8]), "+v"(v[9]), "+v"(v[10]), "+v"(v[11]), "+v"(v[12]), "+v"(v[13]), "+v"(v[14]), "+v"(v[15])
-               :
-               : "memory");
+
+// maximum over the four lanes l % 16 + {0, 16, 32, 48}: two register-to-register lane swaps (a
+// shuffle through LDS would add its latency twice to every softmax step)
+__device__ inline float max_over_groups(float x) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, x);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const float m = fmaxf(__builtin_bit_cast(float, (uint32_t)a[0]), __builtin_bit_cast(float, (uint32_t)a[1]));
+  const uint32_t v = __builtin_bit_cast(uint32_t, m);
+  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return fmaxf(__builtin_bit_cast(float, (uint32_t)b[0]), __builtin_bit_cast(float, (uint32_t)b[1]));
 }
 
 // plain global load (global_load, not flat: a flat load also counts in lgkmcnt)
@@ -114,46 +143,37 @@ template <typename T> __device__ inline T gload(const T* p) {
   return *reinterpret_cast<const __attribute__((address_space(1))) T*>(reinterpret_cast<uintptr_t>(p));
 }
 
-struct __attribute__((aligned(8))) DmaSrc {
-  const uint8_t* k;     // row 0 of the keys (bytes)
-  const uint8_t* v;
-  int64_t pitch;        // bytes between rows
-  const int32_t* idx;   // retained list or null (rows 0..n-1)
-  const float* ksc;     // FP8 block scales (per 16 rows) or null
-  const float* vsc;
-  int n, clampL, pos_add;
-  int npad;             // keys iterated (>= n when padded, else n); keys past n are masked
-};
-
-template <typename TKV, int D, int KT, int NS, int KC>
+template <typename TKV, int D, int KT, int NS, int KC, bool LISTS>
 __device__ void attn_dma_unit(const AttnArgs& a, int unit, uint8_t* smem) {
   using C = DmaCfg<TKV, D, KT, NS>;
   constexpr int NQ = D / 32;                 // 32-deep K steps of S^T
   constexpr int ND = D / 16;                 // 16-wide d blocks of the output
-  constexpr int NBC = KC / 16;               // 16-key blocks of one compute step
-  constexpr int NSTEP = KT / KC;             // compute steps per cache tile
   static_assert(KT % KC == 0 && KC % 32 == 0, "compute steps of whole 32-key pairs");
   constexpr bool FP8 = C::FP8;
 
   const int Hkv = a.Hkv;
   const int h = unit % Hkv;
-  const AttnWork w = a.work[unit / Hkv];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // the work item's fields one by one: a struct that is read through selected members would live
+  // in scratch memory, and a scratch load waits behind every tile load in flight
+  const AttnWork* wp = a.work + unit / Hkv;
+  const int64_t w_off_a = wp->off_a, w_off_b = wp->off_b, w_idx_a = wp->idx_a, w_idx_b = wp->idx_b;
+  const int w_L_a = wp->L_a, w_L_b = wp->L_b, w_n_a = wp->n_a, w_n_b = wp->n_b, w_q_row0 = wp->q_row0;
+  const int w_q_pos0 = wp->q_pos0, w_n_q = wp->n_q, w_own_row0 = wp->own_row0, w_n_own = wp->n_own;
+  const int w_own_pos0 = wp->own_pos0, w_pad_a = wp->pad_a;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qi = lane & 15, g4 = lane >> 4;
   const int r = wave * 16 + qi;
   const int gq = r / a.Pmax, p = r % a.Pmax;
-  const bool qvalid = gq < a.G && p < w.n_q;
+  const bool qvalid = gq < a.G && p < w_n_q;
   const bool wave_active = __any(qvalid);
   const int hq = h * a.G + (gq < a.G ? gq : 0);
-  const int qpos = w.q_pos0 + p;
-  const int64_t qrow = (int64_t)w.q_row0 + (qvalid ? p : 0);
+  const int qpos = w_q_pos0 + p;
+  const int64_t qrow = (int64_t)w_q_row0 + (qvalid ? p : 0);
 
-  // ---- query fragments (B operand of S^T); qa: rotated for document B (joins)
-  // (joins: the fragments of the queries rotated at position - L_A are loaded when the
-  // tiles of document B begin, and the plain ones again after them; holding both sets
-  // would cost the registers of a third resident workgroup)
+  // ---- query fragments (B operand of S^T).  Joins: the fragments of the queries rotated at
+  // position - L_A are loaded when the tiles of document B begin, and the plain ones again
+  // after them (both sets would cost the registers of a resident workgroup).
   u32x4 qf[NQ];
-  const bool has_b = w.n_b > 0;
   const bf16_t* q_plain = reinterpret_cast<const bf16_t*>(a.q) + qrow * a.q_stride + hq * D;
   const bf16_t* q_rot = reinterpret_cast<const bf16_t*>(a.q_alt ? a.q_alt : a.q) + qrow * a.q_stride + hq * D;
   auto load_q = [&](const bf16_t* q) {
@@ -163,123 +183,146 @@ __device__ void attn_dma_unit(const AttnArgs& a, int unit, uint8_t* smem) {
   };
   load_q(q_plain);
 
-  // ---- key sources: 0 = document A, 1 = document B, 2 = own rows.  Three separate
-  // variables selected field by field (a dynamically indexed local array would live in
-  // scratch memory, and a scratch load waits behind every tile load in flight).
-  auto init_doc = [&](DmaSrc& s, int64_t off, int L, int64_t il, int n, int pos_add, int pad) {
-    s.n = n;
-    s.npad = n > 0 ? max(n, pad) : 0;
-    s.clampL = max(L, 1);
-    s.pos_add = pos_add;
-    s.idx = il >= 0 ? a.idx + il : nullptr;
-    s.pitch = C::RBC;
-    s.ksc = s.vsc = nullptr;
-    s.k = s.v = a.pool;
-    if (n > 0) {
-      const uint8_t* base = a.pool + off;
-      const int64_t kv_elems = (int64_t)L * D;
-      const int64_t head_off = ((int64_t)(a.layer * Hkv + h) * 2) * kv_elems;
-      s.k = base + head_off * (int64_t)sizeof(TKV);
-      s.v = s.k + kv_elems * (int64_t)sizeof(TKV);
-      if constexpr (FP8) {
-        const int nblk = (L + 15) >> 4;
-        const float* sb = reinterpret_cast<const float*>(base + (int64_t)2 * a.n_layers * Hkv * kv_elems);
-        s.ksc = sb + ((int64_t)(a.layer * Hkv + h) * 2) * nblk;
-        s.vsc = s.ksc + nblk;
-      }
-    }
+  // ---- key sources: 0 = document A, 1 = document B, 2 = own rows.  Three cursors walk the same
+  // sequence of tiles: the row numbers being fetched, the chunks being fetched, the tile being
+  // computed.  Each keeps what it needs of its current source and steps through it with a few
+  // scalar operations; a source's addresses are formed only when a cursor enters it.
+  auto keys_of = [&](int s) { return s == 0 ? w_n_a : (s == 1 ? w_n_b : w_n_own); };
+  auto iterated = [&](int s) { return s == 0 && w_n_a > 0 ? max(w_n_a, w_pad_a) : keys_of(s); };
+  auto step_of = [&](int s) { return FP8 && s == 2 ? C::KTO : KT; };
+  auto next_source = [&](int s) {     // the next source with keys (2 when there is none)
+    do s++;
+    while (s < 2 && keys_of(s) == 0);
+    return s;
   };
-  DmaSrc src0, src1, src2;
-  init_doc(src0, w.off_a, w.L_a, w.idx_a, w.n_a, 0, w.pad_a);
-  init_doc(src1, w.off_b, w.L_b, w.idx_b, w.n_b, w.L_a, 0);
-  {
-    DmaSrc& s = src2;
-    s.n = w.n_own;
-    s.npad = w.n_own;
-    s.clampL = max(w.n_own, 1);
-    s.pos_add = w.own_pos0;
-    s.idx = nullptr;
-    s.ksc = s.vsc = nullptr;
-    s.pitch = a.own_stride * 2;
-    const uint8_t* ob = reinterpret_cast<const uint8_t*>(a.own) + (int64_t)w.own_row0 * s.pitch;
-    s.k = ob + (int64_t)(a.own_kcol + h * D) * 2;
-    s.v = ob + (int64_t)(a.own_vcol + h * D) * 2;
-  }
-  const int TA = (src0.npad + KT - 1) / KT, TB = (src1.npad + KT - 1) / KT;
-  const int TO = (src2.n + C::KTO - 1) / C::KTO;
-  vm_wait<0>();  // the query fragments have arrived (the loop's waits count tile loads only)
-  __syncthreads();
-  const int T = TA + TB + TO;
+  auto list_of = [&](int s) -> const int32_t* {
+    const int64_t il = s == 0 ? w_idx_a : w_idx_b;
+    return LISTS && s < 2 && il >= 0 ? a.idx + il : nullptr;
+  };
+  const int first = keys_of(0) > 0 ? 0 : (keys_of(1) > 0 ? 1 : 2);
+  const int TA = w_n_a > 0 ? (iterated(0) + KT - 1) / KT : 0, TB = (w_n_b + KT - 1) / KT;
+  const int T = TA + TB + (w_n_own + C::KTO - 1) / C::KTO;
   // a valid address for loads whose value is not used (keeps the per-tile load count fixed)
   const int32_t* dummy = reinterpret_cast<const int32_t*>(a.work + unit / Hkv);
 
-  auto tile_src = [&](int ti, int& sidx, int& t0) {
-    if (ti < TA) { sidx = 0; t0 = ti * KT; }
-    else if (ti < TA + TB) { sidx = 1; t0 = (ti - TA) * KT; }
-    else { sidx = 2; t0 = (ti - TA - TB) * C::KTO; }
+  // Row numbers of retained lists reach LDS by direct loads too (one 4-byte load per key, lane =
+  // key), LEAD tiles before the chunks that need them, into a ring of NRING slots: the loop
+  // holds no register-destination memory load, so the only waits on memory are explicit.
+  int* ring = reinterpret_cast<int*>(smem + C::RING);
+  struct { int s, t, n, np, slot; const int32_t* idx; } rc;
+  auto enter_rows = [&](int s) {
+    rc.s = s;
+    rc.t = 0;
+    rc.n = keys_of(s);
+    rc.np = iterated(s);
+    rc.idx = list_of(s);
+  };
+  auto issue_rows = [&]() {
+    if constexpr (LISTS) {
+      // a padded tile (past the source's keys) loads the source's rows again from the start of
+      // the list, cyclically: real rows, so the padded keys cost loads and multiplies.  Past the
+      // last tile the load goes on with row numbers that nobody reads.
+      const int tl = rc.t < rc.n ? rc.t : rc.t % max(rc.n, 1);
+      const int32_t* g = rc.idx ? rc.idx + min(tl + lane, rc.n - 1) : dummy;
+      __builtin_amdgcn_global_load_lds(g, (lds_void_t*)(ring + rc.slot * 64), 4, 0, 0);
+      rc.slot = rc.slot + 1 == C::NRING ? 0 : rc.slot + 1;
+      rc.t += step_of(rc.s);
+      if (rc.t >= rc.np && rc.s < 2) enter_rows(next_source(rc.s));
+    }
   };
 
-  // Row numbers of retained lists reach LDS by direct loads too (one 4-byte load per key,
-  // lane = key), one step before the tile's chunks are issued, into a ring of NS + 1
-  // slots: the loop then holds no register-destination memory load, so the only waits on
-  // memory are the explicit ones below.  Ring slot of tile X: X % (NS + 1).
-  int* ring = reinterpret_cast<int*>(smem + C::RING);
-  // The current source is selected field by field from the three descriptors, which are
-  // uniform across the workgroup and stay in scalar registers (an indexed local array
-  // would live in scratch memory, and a scratch load waits behind every tile load in
-  // flight).
-  auto pick = [&](int sidx) {
-    DmaSrc r;
-#define KVOP_PICK(f) r.f = sidx == 0 ? src0.f : (sidx == 1 ? src1.f : src2.f)
-    KVOP_PICK(k); KVOP_PICK(v); KVOP_PICK(pitch); KVOP_PICK(idx); KVOP_PICK(ksc); KVOP_PICK(vsc);
-    KVOP_PICK(n); KVOP_PICK(clampL); KVOP_PICK(pos_add); KVOP_PICK(npad);
-#undef KVOP_PICK
-    return r;
-  };
-  auto issue_rows = [&](int ti) {
-    int sidx, t0;
-    tile_src(ti, sidx, t0);
-    const DmaSrc s = pick(sidx);
-    // a padded tile (past the source's keys) loads the source's rows again from the start
-    // of the list, cyclically: real rows, so the padded keys cost loads and multiplies
-    const int tl = t0 < s.n ? t0 : t0 % s.n;
-    const int32_t* g = s.idx ? s.idx + min(tl + lane, s.n - 1) : dummy;
-    __builtin_amdgcn_global_load_lds(g, (lds_void_t*)(ring + (ti % (NS + 1)) * 64), 4, 0, 0);
-  };
-  // chunk loads of tile ti into stage st, then one metadata load per wavefront (key =
-  // lane): wave 0 the K block scales, wave 1 the V block scales, waves 2-3 none (a load of
-  // an unused word keeps the count per wavefront the same)
-  auto issue_tile = [&](int ti, int st) {
-    int sidx, t0;
-    tile_src(ti, sidx, t0);
-    const DmaSrc s = pick(sidx);
-    const int tl = t0 < s.n ? t0 : t0 % s.n;   // as in issue_rows
-    const int* rws = ring + (ti % (NS + 1)) * 64;
-    uint8_t* sb = smem + st * C::STAGE;
-    const bool own = sidx == 2;
-    const int ch = own ? C::CHO : C::CHC;
-#pragma unroll
-    for (int j = 0; j < C::NJ; j++) {
-      const int jr = j % C::NR;
-      const bool is_v = j >= C::NR;
-      const int f = 256 * jr + tid;              // chunk index inside the part
-      const int rr = f / ch, slot = f % ch;
-      const int t = min(tl + rr, s.n - 1);
-      const int row = min(max(s.idx ? rws[rr] : t, 0), s.clampL - 1);
-      int sw;
-      if (own) sw = is_v ? swz_v<C::CHO>(rr) : swz_k<C::CHO>(rr);
-      else if (FP8) sw = is_v ? swz_v8<C::CHC>(rr) : swz_k<C::CHC>(rr);
-      else sw = is_v ? swz_v<C::CHC>(rr) : swz_k<C::CHC>(rr);
-      const uint8_t* g = (is_v ? s.v : s.k) + (int64_t)row * s.pitch + (slot ^ sw) * 16;
-      uint8_t* l = sb + (is_v ? C::REGION : 0) + (256 * jr + 64 * wave) * 16;
-      __builtin_amdgcn_global_load_lds(g, (lds_void_t*)l, 16, 0, 0);
+  // chunk loads of the next tile, then (FP8) one metadata load per wavefront (key = lane):
+  // wave 0 the K block scales, wave 1 the V block scales, waves 2-3 none (a load of an unused
+  // word keeps the count per wavefront the same)
+  struct { int s, t, n, np, clampL, pitch, slot, stage; bool list; const uint8_t *k, *v; const float *ksc, *vsc; } ic;
+  auto enter_tiles = [&](int s) {
+    ic.s = s;
+    ic.t = 0;
+    ic.n = keys_of(s);
+    ic.np = iterated(s);
+    ic.list = list_of(s) != nullptr;
+    ic.ksc = ic.vsc = nullptr;
+    ic.k = ic.v = a.pool;
+    if (s == 2) {
+      ic.clampL = max(ic.n, 1);
+      ic.pitch = (int)a.own_stride * 2;
+      const uint8_t* ob = reinterpret_cast<const uint8_t*>(a.own) + (int64_t)w_own_row0 * a.own_stride * 2;
+      ic.k = ob + (int64_t)(a.own_kcol + h * D) * 2;
+      ic.v = ob + (int64_t)(a.own_vcol + h * D) * 2;
+    } else if (ic.n > 0) {
+      const int L = s == 0 ? w_L_a : w_L_b;
+      ic.clampL = max(L, 1);
+      ic.pitch = C::RBC;
+      const uint8_t* base = a.pool + (s == 0 ? w_off_a : w_off_b);
+      const int64_t kv_elems = (int64_t)L * D;
+      const int64_t hk = (int64_t)(a.layer * Hkv + h) * 2;
+      ic.k = base + hk * kv_elems * (int64_t)sizeof(TKV);
+      ic.v = ic.k + kv_elems * (int64_t)sizeof(TKV);
+      if constexpr (FP8) {
+        const int nblk = (L + 15) >> 4;
+        ic.ksc = reinterpret_cast<const float*>(base + (int64_t)2 * a.n_layers * Hkv * kv_elems) + hk * nblk;
+        ic.vsc = ic.ksc + nblk;
+      }
     }
-    float* meta = reinterpret_cast<float*>(sb + 2 * C::REGION);
-    const int row = min(max(s.idx ? rws[lane] : min(tl + lane, s.n - 1), 0), s.clampL - 1);
-    const void* g = dummy;
-    if (wave == 0 && s.ksc) g = s.ksc + (row >> 4);
-    if (wave == 1 && s.vsc) g = s.vsc + (row >> 4);
-    __builtin_amdgcn_global_load_lds(g, (lds_void_t*)(meta + min(wave, 2) * 64), 4, 0, 0);
+  };
+  auto issue_chunks = [&](auto own_c) __attribute__((always_inline)) {
+    constexpr bool OWN = decltype(own_c)::value;
+    constexpr int CH = OWN ? C::CHO : C::CHC;
+    const int tl = ic.t < ic.n ? ic.t : ic.t % max(ic.n, 1);   // as in issue_rows
+    const int* rws = ring + ic.slot * 64;
+    uint8_t* sb = smem + ic.stage * C::STAGE;
+    uint32_t off[C::NR];
+#pragma unroll
+    for (int j = 0; j < C::NR; j++) {
+      const int rr = (256 * j + tid) / CH;         // key of the tile
+      const int t = min(tl + rr, ic.n - 1);
+      const int row = min(max(!OWN && ic.list ? rws[rr] : t, 0), ic.clampL - 1);
+      off[j] = (uint32_t)row * (uint32_t)ic.pitch;
+    }
+#pragma unroll
+    for (int v = 0; v < 2; v++)
+#pragma unroll
+      for (int j = 0; j < C::NR; j++) {
+        const int rr = (256 * j + tid) / CH, slot = (256 * j + tid) % CH;
+        const int sw = v ? (FP8 && !OWN ? swz_v8<CH>(rr) : swz_v<CH>(rr)) : swz_k<CH>(rr);
+        const uint8_t* g = (v ? ic.v : ic.k) + (off[j] + (uint32_t)((slot ^ sw) * 16));
+        uint8_t* l = sb + (v ? C::REGION : 0) + (256 * j + 64 * wave) * 16;
+        __builtin_amdgcn_global_load_lds(g, (lds_void_t*)l, 16, 0, 0);
+      }
+    if constexpr (FP8) {
+      float* meta = reinterpret_cast<float*>(sb + 2 * C::REGION);
+      const void* g = dummy;
+      if (!OWN && wave < 2) {
+        const int row = min(max(ic.list ? rws[lane] : min(tl + lane, ic.n - 1), 0), ic.clampL - 1);
+        g = (wave == 0 ? ic.ksc : ic.vsc) + (row >> 4);
+      }
+      __builtin_amdgcn_global_load_lds(g, (lds_void_t*)(meta + min(wave, 2) * 64), 4, 0, 0);
+    }
+  };
+  auto issue_tile = [&]() __attribute__((always_inline)) {
+    if constexpr (FP8) {
+      if (ic.s == 2) issue_chunks(std::true_type{});
+      else issue_chunks(std::false_type{});
+    } else {
+      issue_chunks(std::false_type{});             // own rows have the cache's layout
+    }
+    ic.slot = ic.slot + 1 == C::NRING ? 0 : ic.slot + 1;
+    ic.stage = ic.stage + 1 == NS ? 0 : ic.stage + 1;
+    ic.t += step_of(ic.s);
+    if (ic.t >= ic.np && ic.s < 2) enter_tiles(next_source(ic.s));
+  };
+
+  // the tile being computed
+  struct { int s, t, n, np, pos_add, top, slot, stage; bool list; } cc;
+  auto enter_compute = [&](int s) {
+    cc.s = s;
+    cc.t = 0;
+    cc.n = keys_of(s);
+    cc.np = iterated(s);
+    cc.list = list_of(s) != nullptr;
+    cc.pos_add = s == 0 ? 0 : (s == 1 ? w_L_a : w_own_pos0);
+    // no list row of a document lies past its length: whether a tile can hold an invisible key
+    cc.top = (s == 0 ? w_L_a : w_L_b) - 1;
   };
 
   float m_run = -INFINITY, l_run = 0.f;
@@ -287,199 +330,221 @@ __device__ void attn_dma_unit(const AttnArgs& a, int unit, uint8_t* smem) {
 #pragma unroll
   for (int i = 0; i < ND; i++) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // Prologue: rows of tile 0; then for q = 0 .. NS-2: rows of tile q + 1, chunks of tile q.
-  // Waiting until only the newest chunk loads (NJ + 1) are outstanding guarantees the rows
-  // issued just before them.
+  vm_wait<0>();  // the query fragments have arrived (the loop's waits count tile loads only)
+  __syncthreads();
+  // Step j issues the row numbers of tile j + NS - 1 + LEAD, then the chunks of tile j + NS - 1;
+  // the prologue runs steps -(NS - 1) .. -1.  The row numbers of a tile are older than the
+  // chunks of the tile LEAD before it, so once tile ti has landed the row numbers that step ti
+  // needs have too, while NS - 2 later tiles stay in flight.
   if (T > 0) {
-    issue_rows(0);
-    vm_wait<0>();
-    __builtin_amdgcn_s_barrier();
-  }
+    rc.slot = ic.slot = cc.slot = ic.stage = cc.stage = 0;
+    enter_rows(first);
+    enter_tiles(first);
+    enter_compute(first);
+    if constexpr (LISTS) {
 #pragma unroll
-  for (int q = 0; q < NS - 1; q++) {
-    if (q < T) {
-      if (q + 1 < T) issue_rows(q + 1);
-      issue_tile(q, q);
-      vm_wait<C::NJ + 1>();
+      for (int q = 0; q < C::LEAD; q++) issue_rows();
+      vm_wait<0>();
       __builtin_amdgcn_s_barrier();
     }
+#pragma unroll
+    for (int q = 0; q < NS - 1; q++) {
+      issue_rows();
+      if (q < T) issue_tile();
+    }
   }
+  constexpr int ROWS = LISTS ? NS - 2 : 0;         // row-number loads behind a tile
 
-  for (int ti = 0; ti < T; ti++) {
-    // Tile ti and the rows of tile ti + NS - 1 have landed once only the previous step's
-    // chunk loads may be outstanding (NS = 3; NS = 2 waits for everything); if that step
-    // issued no chunks, wait for everything.  Then a bare s_barrier makes every
-    // wavefront's loads visible and marks tile ti - 1 consumed (a fence would wait for
-    // the loads still in flight).
-    if (ti + NS - 2 < T) vm_wait<C::WAIT>();
-    else vm_wait<0>();
-    __builtin_amdgcn_s_barrier();
-    if (ti + NS < T) issue_rows(ti + NS);
-    if (ti + NS - 1 < T) issue_tile(ti + NS - 1, (ti + NS - 1) % NS);
-
-    int sidx, t0;
-    tile_src(ti, sidx, t0);
-    const DmaSrc s = pick(sidx);
-    const bool own = sidx == 2;
-    const bool tile_fp8 = FP8 && !own;
-    const int nbt = (own ? C::KTO : KT) / 16;  // 16-key blocks present in this tile
-    const uint8_t* sb = smem + (ti % NS) * C::STAGE;
+  // One online-softmax step over NB 16-key blocks from block kb0 of the tile at sb.
+  auto compute = [&](const uint8_t* sb, auto own_c, auto nb_c, int kb0, bool need_mask) __attribute__((always_inline)) {
+    constexpr bool T8 = FP8 && !decltype(own_c)::value;   // FP8 rows
+    constexpr int NB = decltype(nb_c)::value;
+    constexpr int RB = T8 ? C::RBC : C::RBO;
     const uint8_t* Kp = sb;
     const uint8_t* Vp = sb + C::REGION;
     const float* ksc_s = reinterpret_cast<const float*>(sb + 2 * C::REGION);
     const float* vsc_s = ksc_s + 64;
-    const int* rows_s = ring + (ti % (NS + 1)) * 64;
-
-    // document B is scored with the queries rotated at (position - L_A)
-    if (has_b && (ti == TA || ti == TA + TB)) load_q(ti == TA ? q_rot : q_plain);
-    if (!wave_active) continue;
-
-    // The tile is computed in steps of KC keys (blocks kb0 .. kb0 + NBC - 1), each with its own
-    // online-softmax update: a tile may carry more keys than one step holds in registers.
+    // ---- scores S^T[key][query]: lane holds keys 16 (kb0 + b) + 4 g4 + t of query column qi
+    f32x4 sc[NB];
 #pragma unroll
-    for (int hc = 0; hc < NSTEP; hc++) {
-      const int kb0 = hc * NBC;
-      if (kb0 >= nbt) break;
-      // ---- scores S^T[key][query]: lane holds keys 16 (kb0 + b) + 4 g4 + t of query column qi
-      f32x4 sc[NBC];
+    for (int b = 0; b < NB; b++) sc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int b = 0; b < NBC; b++) {
-        sc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (kb0 + b >= nbt) continue;
-        const int kr = 16 * (kb0 + b) + qi;
+    for (int b = 0; b < NB; b++) {
+      const int kr = 16 * (kb0 + b) + qi;
 #pragma unroll
-        for (int k = 0; k < NQ; k++) {
-          u32x4 kf;
-          if (tile_fp8) {
-            const int pc = 4 * k + g4;  // 8-byte piece of the FP8 row
-            const u32x2 raw = *reinterpret_cast<const u32x2*>(Kp + kr * C::RBC + ((pc >> 1) ^ swz_k<C::CHC>(kr)) * 16 +
-                                                             (pc & 1) * 8);
-            kf = fp8x8_to_bf16x8(raw[0], raw[1]);
-          } else if (own) {
-            kf = *reinterpret_cast<const u32x4*>(Kp + kr * C::RBO + ((4 * k + g4) ^ swz_k<C::CHO>(kr)) * 16);
-          } else {
-            kf = *reinterpret_cast<const u32x4*>(Kp + kr * C::RBC + ((4 * k + g4) ^ swz_k<C::CHC>(kr)) * 16);
-          }
-          sc[b] = mfma_bf16(__builtin_bit_cast(u16x8, kf), __builtin_bit_cast(u16x8, qf[k]), sc[b]);
+      for (int k = 0; k < NQ; k++) {
+        u32x4 kf;
+        if constexpr (T8) {
+          const int pc = 4 * k + g4;  // 8-byte piece of the FP8 row
+          const u32x2 raw = *reinterpret_cast<const u32x2*>(Kp + kr * RB + ((pc >> 1) ^ swz_k<C::CHC>(kr)) * 16 +
+                                                           (pc & 1) * 8);
+          kf = fp8x8_to_bf16x8(raw[0], raw[1]);
+        } else {
+          kf = *reinterpret_cast<const u32x4*>(Kp + kr * RB + ((4 * k + g4) ^ swz_k<C::CHO>(kr)) * 16);
         }
+        sc[b] = mfma_bf16(__builtin_bit_cast(u16x8, kf), __builtin_bit_cast(u16x8, qf[k]), sc[b]);
       }
-      // ---- online softmax (FP32).  Keys past the source's end and keys after the query's
-      // position are masked; only tiles that can hold such keys test positions.
-      const int n_here = s.n - t0;
-      const bool need_mask = own || n_here < nbt * 16 || (!s.idx && t0 + nbt * 16 - 1 + s.pos_add > w.q_pos0) ||
-                             (s.idx && rows_s[nbt * 16 - 1] + s.pos_add > w.q_pos0);
-      float mx = -INFINITY;
+    }
+    // ---- online softmax (FP32).  Keys past the source's end and keys after the query's position
+    // are masked; only tiles that can hold such keys test positions.
+    if constexpr (T8) {
 #pragma unroll
-      for (int b = 0; b < NBC; b++)
+      for (int b = 0; b < NB; b++) sc[b] *= *reinterpret_cast<const f32x4*>(ksc_s + 16 * (kb0 + b) + 4 * g4);
+    }
+    if (need_mask) {
+      const int n_here = cc.n - cc.t;
+      const int* rows_s = ring + cc.slot * 64;
 #pragma unroll
-        for (int t = 0; t < 4; t++) {
-          const int key = 16 * (kb0 + b) + 4 * g4 + t;
-          float v = sc[b][t];
-          if (tile_fp8) v *= ksc_s[key];
-          if (kb0 + b >= nbt) {
-            v = -INFINITY;
-          } else if (need_mask) {
-            const int kpos = key < n_here ? (s.idx ? rows_s[key] : t0 + key) + s.pos_add : 0x7fffffff;
-            if (!(kpos <= qpos)) v = -INFINITY;
-          }
-          sc[b][t] = v;
-          mx = fmaxf(mx, v);
+      for (int b = 0; b < NB; b++) {
+        const int key = 16 * (kb0 + b) + 4 * g4;
+        int kp[4] = {cc.t + key, cc.t + key + 1, cc.t + key + 2, cc.t + key + 3};
+        if (LISTS && cc.list) {
+          const u32x4 rw = *reinterpret_cast<const u32x4*>(rows_s + key);
+#pragma unroll
+          for (int t = 0; t < 4; t++) kp[t] = (int)rw[t];
         }
-      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float c = a.scale_log2;
-      const float m_new = fmaxf(m_run, mx);
-      const float mc = m_new == -INFINITY ? 0.f : m_new * c;
-      // rescale of the running sums: exactly 1 when the maximum did not move (the contracted
-      // m_run * c - mc is then the rounding error of mc, not 0), 0 when m_run = -inf
-      const float alpha = m_new > m_run ? __builtin_amdgcn_exp2f(m_run * c - mc) : 1.f;
-      float psum = 0.f;
 #pragma unroll
-      for (int b = 0; b < NBC; b++)
+        for (int t = 0; t < 4; t++)
+          if (!(key + t < n_here && kp[t] + cc.pos_add <= qpos)) sc[b][t] = -INFINITY;
+      }
+    }
+    float mx = -INFINITY;
 #pragma unroll
-        for (int t = 0; t < 4; t++) {
-          const float pv = __builtin_amdgcn_exp2f(fmaf(sc[b][t], c, -mc));  // exp2(-inf) = 0
-          sc[b][t] = pv;
-          psum += pv;
-        }
-      l_run = l_run * alpha + psum;
-      m_run = m_new;
+    for (int b = 0; b < NB; b++)
+#pragma unroll
+      for (int t = 0; t < 4; t++) mx = fmaxf(mx, sc[b][t]);
+    mx = max_over_groups(mx);
+    const float c = a.scale_log2;
+    const float m_new = fmaxf(m_run, mx);
+    const float mc = m_new == -INFINITY ? 0.f : m_new * c;
+    // rescale of the running sums: exactly 1 when the maximum did not move (the fused
+    // m_run * c - mc is then the rounding error of mc, not 0), 0 when m_run = -inf.  The roundings
+    // are spelled out: a tile's later steps subtract the rounded products.
+    const bool moved = m_new > m_run;
+    const float up = kb0 == 0 ? __builtin_fmaf(m_run, c, -mc) : scaled_minus(m_run, c, mc);
+    const float alpha = moved ? __builtin_amdgcn_exp2f(up) : 1.f;
+    float psum = 0.f;
+#pragma unroll
+    for (int b = 0; b < NB; b++)
+#pragma unroll
+      for (int t = 0; t < 4; t++) {
+        const float pv = __builtin_amdgcn_exp2f(fmaf(sc[b][t], c, -mc));  // exp2(-inf) = 0
+        sc[b][t] = pv;
+        psum += pv;
+      }
+    l_run = l_run * alpha + psum;
+    m_run = m_new;
+    // (a product with exactly 1 changes nothing: skipped when no query's maximum moved, which
+    // after the first tiles of a long document is the usual case)
+    if (__any(moved)) {
 #pragma unroll
       for (int i = 0; i < ND; i++) o[i] *= alpha;
+    }
 
-      // ---- O^T[d][query] += V^T[d][key] P^T[key][query].  K slots 0..3 of lane group g4 are
-      // keys 32 b2 + 4 g4 + t, slots 4..7 keys 32 b2 + 16 + 4 g4 + t (b2: pair of the tile;
-      // bl: the same pair's first block within this step).
+    // ---- O^T[d][query] += V^T[d][key] P^T[key][query].  K slots 0..3 of lane group g4 are
+    // keys 32 b2 + 4 g4 + t, slots 4..7 keys 32 b2 + 16 + 4 g4 + t (b2: pair of the tile).
 #pragma unroll
-      for (int bp = 0; bp < NBC / 2; bp++) {
-        const int bl = 2 * bp, b2 = kb0 / 2 + bp;
-        if (2 * b2 >= nbt) continue;
-        u32x4 pb;
+    for (int bp = 0; bp < NB / 2; bp++) {
+      const int bl = 2 * bp, b2 = kb0 / 2 + bp;
+      if constexpr (T8) {
+        sc[bl] *= *reinterpret_cast<const f32x4*>(vsc_s + 32 * b2 + 4 * g4);
+        sc[bl + 1] *= *reinterpret_cast<const f32x4*>(vsc_s + 32 * b2 + 16 + 4 * g4);
+      }
+      u32x4 pb;
 #pragma unroll
-        for (int t = 0; t < 4; t += 2) {
-          float p0 = sc[bl][t], p0n = sc[bl][t + 1];
-          float p1 = sc[bl + 1][t], p1n = sc[bl + 1][t + 1];
-          if (tile_fp8) {
-            p0 *= vsc_s[32 * b2 + 4 * g4 + t];
-            p0n *= vsc_s[32 * b2 + 4 * g4 + t + 1];
-            p1 *= vsc_s[32 * b2 + 16 + 4 * g4 + t];
-            p1n *= vsc_s[32 * b2 + 16 + 4 * g4 + t + 1];
-          }
-          pb[t / 2] = pack_bf16x2(p0, p0n);
-          pb[2 + t / 2] = pack_bf16x2(p1, p1n);
-        }
-        // lane (qi, g4) reads V[keys 32 b2 + 4 g4 + 0..3 (+16)][d = 16 i + qi].  A tile with a
-        // single 16-key block in this pair (a 16-key own tile) has no rows +16: those keys
-        // carry p = 0, so any finite row will do (the tile's own rows, not bytes past it)
-        const int vr0 = 32 * b2 + 4 * g4 + (qi >> 2), vr1 = 2 * b2 + 1 < nbt ? vr0 + 16 : vr0;
-        if (tile_fp8) {
-          // 8-bit transposed reads: within a lane group, lane qi addresses key slot qi / 2
-          // (row 32 b2 + 4 g4 + (qi/2 < 4 ? qi/2 : 16 + qi/2 - 4)) at byte columns
-          // 16 i + 8 (qi % 2) .. +7; lane qi receives byte column 16 i + qi of the 8 rows
-          const int ks = qi >> 1;
-          const int vr = 32 * b2 + 4 * g4 + (ks < 4 ? ks : 12 + ks);
-          const int sv = swz_v8<C::CHC>(vr);
-          u32x2 y[ND];
+      for (int t = 0; t < 4; t += 2) {
+        pb[t / 2] = pack_bf16x2(sc[bl][t], sc[bl][t + 1]);
+        pb[2 + t / 2] = pack_bf16x2(sc[bl + 1][t], sc[bl + 1][t + 1]);
+      }
+      if constexpr (T8) {
+        // 8-bit transposed reads: within a lane group, lane qi addresses key slot qi / 2
+        // (row 32 b2 + 4 g4 + (qi/2 < 4 ? qi/2 : 16 + qi/2 - 4)) at byte columns
+        // 16 i + 8 (qi % 2) .. +7; lane qi receives byte column 16 i + qi of the 8 rows
+        const int ks = qi >> 1;
+        const int vr = 32 * b2 + 4 * g4 + (ks < 4 ? ks : 12 + ks);
+        const int sv = swz_v8<C::CHC>(vr);
 #pragma unroll
-          for (int i = 0; i < ND; i++) y[i] = ds_read_tr8(Vp + vr * C::RBC + ((i ^ sv) * 16) + (qi & 1) * 8);
-          lgkm_wait_all<ND>(y);
+        for (int i0 = 0; i0 < ND; i0 += 4) {
+          uint32_t ad[4];
+          u32x2 y[4];
 #pragma unroll
-          for (int i = 0; i < ND; i++) {
+          for (int i = 0; i < 4; i++) ad[i] = lds_addr(Vp + vr * RB + (((i0 + i) ^ sv) * 16) + (qi & 1) * 8);
+          ds_read_tr8_x4(ad, y);
+#pragma unroll
+          for (int i = 0; i < 4; i++) {
             const u32x4 va = fp8x8_to_bf16x8(y[i][0], y[i][1]);
-            o[i] = mfma_bf16(__builtin_bit_cast(u16x8, va), __builtin_bit_cast(u16x8, pb), o[i]);
+            o[i0 + i] = mfma_bf16(__builtin_bit_cast(u16x8, va), __builtin_bit_cast(u16x8, pb), o[i0 + i]);
           }
-        } else {
-          // 16-bit transposed reads: lane (qi, g4) addresses row vr (qi / 4 selects the key),
-          // columns 16 i + 4 (qi % 4) .. +3; lane qi receives column 16 i + qi of 4 rows
-          const int rb = own ? C::RBO : C::RBC;
-          const int s0 = own ? swz_v<C::CHO>(vr0) : swz_v<C::CHC>(vr0);
-          const int s1 = own ? swz_v<C::CHO>(vr1) : swz_v<C::CHC>(vr1);
-          // 32-key tiles: in two halves of the d blocks (fewer live registers, for the
-          // register budget of three resident workgroups)
-          constexpr int NHALF = KC == 32 ? 2 : 1;
+        }
+      } else {
+        // 16-bit transposed reads: lane (qi, g4) addresses row 32 b2 + 4 g4 + qi / 4 and the row 16
+        // after it (same swizzle), columns 16 i + 4 (qi % 4) .. +3; lane qi receives column
+        // 16 i + qi of the 4 rows of its group
+        const int vr = 32 * b2 + 4 * g4 + (qi >> 2);
+        static_assert(swz_v<C::CHO>(16) == 0, "rows 16 apart share a swizzle");
 #pragma unroll
-          for (int h2 = 0; h2 < NHALF; h2++) {
-            constexpr int NH = ND / NHALF;
-            u32x2 y[2 * NH];
+        for (int i0 = 0; i0 < ND; i0 += 4) {
+          uint32_t ad[4];
+          u32x2 y[8];
 #pragma unroll
-            for (int ii = 0; ii < NH; ii++) {
-              const int i = h2 * NH + ii;
-              const int cch = (16 * i + 4 * (qi & 3)) >> 3, half = qi & 1;
-              y[2 * ii] = ds_read_tr16(Vp + vr0 * rb + (cch ^ s0) * 16 + half * 8);
-              y[2 * ii + 1] = ds_read_tr16(Vp + vr1 * rb + (cch ^ s1) * 16 + half * 8);
-            }
-            lgkm_wait_all<2 * NH>(y);
+          for (int i = 0; i < 4; i++) {
+            const int cch = (16 * (i0 + i) + 4 * (qi & 3)) >> 3;
+            ad[i] = lds_addr(Vp + vr * RB + (cch ^ swz_v<C::CHO>(vr)) * 16 + (qi & 1) * 8);
+          }
+          ds_read_tr16_x8<16 * RB>(ad, y);
 #pragma unroll
-            for (int ii = 0; ii < NH; ii++) {
-              const int i = h2 * NH + ii;
-              const u32x4 va = u32x4{y[2 * ii][0], y[2 * ii][1], y[2 * ii + 1][0], y[2 * ii + 1][1]};
-              o[i] = mfma_bf16(__builtin_bit_cast(u16x8, va), __builtin_bit_cast(u16x8, pb), o[i]);
-            }
+          for (int i = 0; i < 4; i++) {
+            const u32x4 va = u32x4{y[2 * i][0], y[2 * i][1], y[2 * i + 1][0], y[2 * i + 1][1]};
+            o[i0 + i] = mfma_bf16(__builtin_bit_cast(u16x8, va), __builtin_bit_cast(u16x8, pb), o[i0 + i]);
           }
         }
       }
-    }  // steps
+    }
+  };
+
+  for (int ti = 0; ti < T; ti++) {
+    // Wait for tile ti: ROWS row-number loads and the tiles after ti (at most NS - 2) may be in
+    // flight behind it.  Then a bare s_barrier makes every wavefront's loads visible and marks
+    // tile ti - 1 consumed (a fence would wait for the loads still in flight).
+    const int behind = T - 1 - ti;
+    if (behind >= NS - 2) vm_wait<(NS - 2) * C::OPS + ROWS>();
+    else vm_wait_behind<NS - 3, C::OPS, ROWS>(behind);
+    __builtin_amdgcn_s_barrier();
+    issue_rows();
+    if (ti + NS - 1 < T) issue_tile();
+
+    // document B is scored with the queries rotated at (position - L_A).  The wait belongs to
+    // these loads alone: left to the compiler it would stand before the score products of every
+    // tile, and wait there for the tiles in flight.
+    if (TB > 0 && (ti == TA || ti == TA + TB)) {
+      load_q(ti == TA ? q_rot : q_plain);
+      vm_wait<0>();
+    }
+    if (wave_active) {
+      const uint8_t* sb = smem + cc.stage * C::STAGE;
+      const bool own = cc.s == 2;
+      const int n_here = cc.n - cc.t;
+      const int last = cc.list ? cc.top : min(cc.t + (own ? C::KTO : KT) - 1, own ? 0x7fffffff : cc.top);
+      const bool need_mask = own || n_here < KT || last + cc.pos_add > w_q_pos0;
+      if (FP8 && own) {
+        constexpr int NB = C::KTO / 16 < KC / 16 ? C::KTO / 16 : KC / 16;
+#pragma unroll
+        for (int kb0 = 0; kb0 < C::KTO / 16; kb0 += NB)
+          compute(sb, std::true_type{}, std::integral_constant<int, NB>{}, kb0, true);
+      } else {
+        // a tile may carry more keys than one step holds in registers
+#pragma unroll 1
+        for (int kb0 = 0; kb0 < KT / 16; kb0 += KC / 16)
+          compute(sb, std::false_type{}, std::integral_constant<int, KC / 16>{}, kb0, need_mask);
+      }
+    }
+    cc.slot = cc.slot + 1 == C::NRING ? 0 : cc.slot + 1;
+    cc.stage = cc.stage + 1 == NS ? 0 : cc.stage + 1;
+    cc.t += step_of(cc.s);
+    if (cc.t >= cc.np && cc.s < 2) enter_compute(next_source(cc.s));
   }
+
+  vm_wait<0>();  // row numbers fetched past the last tile have landed: nothing writes this LDS later
 
   // ---- normalise and store: lane holds O[query qi][d = 16 i + 4 g4 + t]
   float l_tot = l_run + __shfl_xor(l_run, 16, 64);
@@ -498,22 +563,21 @@ __device__ void attn_dma_unit(const AttnArgs& a, int unit, uint8_t* smem) {
   }
 }
 
-// One workgroup per unit.
-// 32-key compute steps keep three workgroups' registers per CU (and their tiles fit LDS), or
-// four with two stages (128 VGPRs: four wavefronts per SIMD; 34 KB of LDS per workgroup);
-// the register budget is capped to match
-template <typename TKV, int D, int KT, int NS, int KC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KC == 32 ? (NS == 2 ? 4 : 3) : 1)))
+// One workgroup per unit.  32-key compute steps of a BF16 cache fit 128 VGPRs (four wavefronts per
+// SIMD), which two stages use (34 KB of LDS: four workgroups per CU); an FP8 cache's widening
+// takes 168 (three).  The register budget is capped to match.
+template <typename TKV, int D, int KT, int NS, int KC, bool LISTS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KC == 32 ? (NS == 2 ? 4 : NS == 3 ? 3 : 2) : 1)))
 void attn_dma_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint8_t dma_smem[];
-  attn_dma_unit<TKV, D, KT, NS, KC>(a, blockIdx.x, dma_smem);
+  attn_dma_unit<TKV, D, KT, NS, KC, LISTS>(a, blockIdx.x, dma_smem);
 }
 
 // Persistent form: a fixed grid takes units from a device counter (zeroed by the caller
 // before the launch) until every unit is taken; every workgroup exits once the counter
 // passes the unit count, so the grid always drains.
-template <typename TKV, int D, int KT, int NS, int KC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KC == 32 ? 3 : 1)))
+template <typename TKV, int D, int KT, int NS, int KC, bool LISTS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KC == 32 ? (NS <= 3 ? 3 : 2) : 1)))
 void attn_dma_persistent_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint8_t dma_smem[];
   __shared__ int next;
@@ -524,20 +588,20 @@ void attn_dma_persistent_kernel(AttnArgs a) {
     const int unit = next;
     __syncthreads();
     if (unit >= total) break;
-    attn_dma_unit<TKV, D, KT, NS, KC>(a, unit, dma_smem);
+    attn_dma_unit<TKV, D, KT, NS, KC, LISTS>(a, unit, dma_smem);
   }
 }
 
-template <typename TKV, int D, int KT, int NS, int KC = KT>
-static hipError_t launch_dma(const AttnArgs& a, hipStream_t st) {
+template <typename TKV, int D, int KT, int NS, int KC, bool LISTS>
+static hipError_t launch_dma_t(const AttnArgs& a, hipStream_t st) {
   using C = DmaCfg<TKV, D, KT, NS>;
   const int64_t units = (int64_t)a.n_work * a.Hkv;
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void*)attn_dma_kernel<TKV, D, KT, NS, KC>,
+    hipError_t e = hipFuncSetAttribute((const void*)attn_dma_kernel<TKV, D, KT, NS, KC, LISTS>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_TOTAL);
     if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)attn_dma_persistent_kernel<TKV, D, KT, NS, KC>,
+      e = hipFuncSetAttribute((const void*)attn_dma_persistent_kernel<TKV, D, KT, NS, KC, LISTS>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_TOTAL);
     if (e != hipSuccess) return e;
     attr_set = true;
@@ -548,16 +612,22 @@ static hipError_t launch_dma(const AttnArgs& a, hipStream_t st) {
     static int per_cu = 0;
     if (per_cu == 0) {
       hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &per_cu, (const void*)attn_dma_persistent_kernel<TKV, D, KT, NS, KC>, 256, C::LDS_TOTAL);
+          &per_cu, (const void*)attn_dma_persistent_kernel<TKV, D, KT, NS, KC, LISTS>, 256, C::LDS_TOTAL);
       if (e != hipSuccess || per_cu < 1) per_cu = 2;
     }
     const int64_t wgs = (int64_t)per_cu * std::max(a.n_cu, 1);
-    hipLaunchKernelGGL((attn_dma_persistent_kernel<TKV, D, KT, NS, KC>),
+    hipLaunchKernelGGL((attn_dma_persistent_kernel<TKV, D, KT, NS, KC, LISTS>),
                        dim3((unsigned)std::min<int64_t>(units, wgs)), dim3(256), C::LDS_TOTAL, st, a);
   } else {
-    hipLaunchKernelGGL((attn_dma_kernel<TKV, D, KT, NS, KC>), dim3((unsigned)units), dim3(256), C::LDS_TOTAL, st, a);
+    hipLaunchKernelGGL((attn_dma_kernel<TKV, D, KT, NS, KC, LISTS>), dim3((unsigned)units), dim3(256), C::LDS_TOTAL, st, a);
   }
   return hipGetLastError();
+}
+
+// prefill reads whole documents (no retained lists): its form has no row numbers to fetch
+template <typename TKV, int D, int KT, int NS, int KC = KT>
+static hipError_t launch_dma(const AttnArgs& a, hipStream_t st) {
+  return a.idx ? launch_dma_t<TKV, D, KT, NS, KC, true>(a, st) : launch_dma_t<TKV, D, KT, NS, KC, false>(a, st);
 }
 
 // variant: 0 = KT 64 / 2 stages, 1 = KT 64 / 3 stages, 2 = 32-key compute steps over tiles of
@@ -571,6 +641,17 @@ static hipError_t launch_dma(const AttnArgs& a, hipStream_t st) {
 // three stages.  The stage count changes no arithmetic: all forms of a variant agree bit
 // for bit.  (D = 64 has no 32-key variant: its FP8 tile would be under one chunk load per
 // thread.)
+// Few documents of very different lengths: the launch ends with its longest unit, whose tiles are
+// one chain (0.9 us each while its CU is quiet; one unit of 4096 keys 113 us), so two workgroups
+// per CU with three tiles in flight serve it better than four with one.  192 documents of 16 to
+// 3072 rows: 133 us against 156; 1024 of 16 to 4096 rows, bound by HBM: 772 against 765.  The line
+// is where the chain takes half the time that the bytes take at 4.4 TB/s.
+static bool longest_unit_bound(const AttnArgs& a, int D) {
+  const double chain_us = a.longest_keys / 32.0 * 0.9;
+  const double bytes_us = (double)a.total_keys * a.Hkv * D * 4.0 / 4.4e6;
+  return 2.0 * chain_us > bytes_us;
+}
+
 template <typename TKV, int D>
 static hipError_t launch_dma_variant(int variant, const AttnArgs& a, hipStream_t st) {
   if (variant == 0) return launch_dma<TKV, D, 64, 2>(a, st);
@@ -579,6 +660,7 @@ static hipError_t launch_dma_variant(int variant, const AttnArgs& a, hipStream_t
     if (variant == 1) return launch_dma<TKV, D, 64, 3>(a, st);
     if constexpr (sizeof(TKV) == 1) return launch_dma<TKV, D, 64, 3, 32>(a, st);
     else if (a.counter) return launch_dma<TKV, D, 32, 3>(a, st);
+    else if (longest_unit_bound(a, D)) return launch_dma<TKV, D, 32, 4>(a, st);
     else return launch_dma<TKV, D, 32, 2>(a, st);
   }
 }

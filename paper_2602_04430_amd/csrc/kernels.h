@@ -90,6 +90,8 @@ struct AttnArgs {
   int persistent_wgs;  // persistent launch: number of workgroups (register-staged kernel)
   int n_cu;            // persistent launch: compute units; the direct-load kernels launch as
                        // many workgroups as fit on them at once
+  int longest_keys;    // keys of the unit that iterates most of them, and of all work items
+  int64_t total_keys;  // together: what the choice of stages goes by
   int decode;          // 1: a decoding step (one query position per item, no document B); the
                        // streaming decode kernel serves it where it supports the shape
 };
