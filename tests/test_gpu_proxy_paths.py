@@ -1,0 +1,48 @@
+"""The proxy's one-pass inference, standardiser and batch reductions at the edges of their splits."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_04430_amd import kvop as K
+from paper_2602_04430_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _proxy(d, h, seed):
+    rng = np.random.default_rng(seed)
+    p = synth.proxy_init(d, h, 2, seed)
+    p["b1"] = (rng.standard_normal(h) * 0.05).astype(np.float32)
+    p["w2"] = (rng.standard_normal((2, h)) * 0.4).astype(np.float32)
+    flat = np.concatenate([p["w1"].ravel(), p["b1"], p["w2"].ravel(), p["b2"]]).astype(np.float32)
+    return p, K.kvop_proxy_create(d, h, torch.from_numpy(flat).cuda())
+
+
+def _infer(px, f, tau=0.6):
+    n = f.shape[0]
+    out = [torch.full((n,), 7, dtype=torch.int8, device="cuda"), torch.full((n,), np.nan, device="cuda"),
+           torch.full((n,), 7, dtype=torch.int8, device="cuda")]
+    K.kvop_proxy_infer(px, f, tau, *out)
+    torch.cuda.synchronize()
+    return [x.cpu().numpy() for x in out]
+
+
+@pytest.mark.parametrize("n", [1, 2, 255, 256, 257, 1791, 1792, 1793, 2048, 2049])
+def test_standardiser_streams_the_same_sums(device, n):
+    """The streaming standardiser and the one-thread-per-column one (features off a 16-byte
+    boundary) add the same rows in the same order: bit-equal answers afterwards."""
+    d, h = 128, 64
+    rng = np.random.default_rng(n)
+    base = torch.from_numpy((rng.standard_normal(n * d + 1) * 2 + 0.5).astype(np.float32)).cuda()
+    off = base[1:].view(n, d)                       # 4 bytes past a 16-byte boundary
+    on = off.clone()
+    assert off.data_ptr() % 16 == 4 and on.data_ptr() % 16 == 0
+    outs = []
+    for f in (on, off):
+        _, px = _proxy(d, h, 9)
+        K.kvop_proxy_fit_standardizer(px, f)
+        outs.append(_infer(px, f))
+        K.kvop_proxy_destroy(px)
+    for a, b in zip(*outs):
+        np.testing.assert_array_equal(a, b)
+    assert np.all(np.isfinite(outs[0][1]))
