@@ -148,38 +148,50 @@ hipError_t proxy_stats(const float* F, int64_t n, int d, float* mean, float* ist
 }
 
 // ---------------------------------------------------------------- gather (+ transpose)
-// tile of 32 rows x 64 features per workgroup; xT (optional) receives the transpose
+// tile of 32 rows x 64 features per workgroup, four features per lane and load; xT (optional)
+// receives the transpose, eight rows per store (B a multiple of 8 then)
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // features may start anywhere
 __global__ __launch_bounds__(256) void proxy_gather_kernel(const float* __restrict__ F, int d,
                                                            const int32_t* __restrict__ rows, int B,
                                                            const float* __restrict__ mean,
                                                            const float* __restrict__ istd, bf16_t* __restrict__ x,
                                                            bf16_t* __restrict__ xT) {
   __shared__ bf16_t tile[32][64 + 2];
-  const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 64;
-  for (int e = threadIdx.x; e < 32 * 64; e += 256) {
-    int rr = e / 64, cc = e % 64;
-    int b = r0 + rr, c = c0 + cc;
-    bf16_t v = 0;
-    if (b < B && c < d) {
-      int64_t src = rows ? rows[b] : b;
-      v = f2bf((F[src * d + c] - mean[c]) * istd[c]);
-      x[(int64_t)b * d + c] = v;
-    }
-    tile[rr][cc] = v;
+  const int r0 = blockIdx.y * 32, cc = 4 * (threadIdx.x % 16), c = blockIdx.x * 64 + cc;
+  const f32x4 mu = *reinterpret_cast<const f32x4*>(mean + c), is = *reinterpret_cast<const f32x4*>(istd + c);
+  f32x4_any v[2];
+#pragma unroll
+  for (int i = 0; i < 2; i++) {
+    const int b = min(r0 + 16 * i + (int)threadIdx.x / 16, B - 1);
+    const int64_t src = rows ? rows[b] : b;
+    v[i] = *reinterpret_cast<const f32x4_any*>(F + src * d + c);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; i++) {
+    const int rr = 16 * i + threadIdx.x / 16, b = r0 + rr;
+    u32x2 pk;
+    pk[0] = pack_bf16x2((v[i][0] - mu[0]) * is[0], (v[i][1] - mu[1]) * is[1]);
+    pk[1] = pack_bf16x2((v[i][2] - mu[2]) * is[2], (v[i][3] - mu[3]) * is[3]);
+    if (b < B) *reinterpret_cast<u32x2*>(x + (int64_t)b * d + c) = pk;
+    *reinterpret_cast<uint32_t*>(&tile[rr][cc]) = pk[0];
+    *reinterpret_cast<uint32_t*>(&tile[rr][cc + 2]) = pk[1];
   }
   if (!xT) return;
   __syncthreads();
-  for (int e = threadIdx.x; e < 32 * 64; e += 256) {
-    int cc = e / 32, rr = e % 32;
-    int b = r0 + rr, c = c0 + cc;
-    if (b < B && c < d) xT[(int64_t)c * B + b] = tile[rr][cc];
+  const int tc = threadIdx.x / 4, b8 = 8 * (threadIdx.x % 4);
+  if (r0 + b8 < B) {
+    u32x4 o;
+#pragma unroll
+    for (int q = 0; q < 4; q++) o[q] = (uint32_t)tile[b8 + 2 * q][tc] | ((uint32_t)tile[b8 + 2 * q + 1][tc] << 16);
+    *reinterpret_cast<u32x4*>(xT + (int64_t)(blockIdx.x * 64 + tc) * B + r0 + b8) = o;
   }
 }
 
 hipError_t proxy_gather(const float* F, int d, const int32_t* rows, int B, const float* mean, const float* istd,
                         bf16_t* x, bf16_t* xT, hipStream_t st) {
   if (B <= 0) return hipSuccess;
-  dim3 grid((d + 63) / 64, (B + 31) / 32);
+  if (d % 64 || (xT && B % 8)) return hipErrorInvalidValue;
+  dim3 grid(d / 64, (B + 31) / 32);
   hipLaunchKernelGGL(proxy_gather_kernel, grid, dim3(256), 0, st, F, d, rows, B, mean, istd, x, xT);
   return hipGetLastError();
 }
@@ -271,40 +283,65 @@ hipError_t proxy_head_train(const float* h1, int B, int H, const float* b1, cons
 }
 
 // ---------------------------------------------------------------- reductions over the batch
-// thread j: db1[j], dW2[0][j], dW2[1][j]; thread 0 also db2 and the mean loss (fixed order)
-__global__ void proxy_reduce_kernel(const float* __restrict__ a, const float* __restrict__ dz,
-                                    const float* __restrict__ dh1, const float* __restrict__ loss_row, int B, int H,
-                                    float* __restrict__ g_b1, float* __restrict__ g_w2, float* __restrict__ g_b2,
-                                    float* __restrict__ loss) {
-  int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j < H) {
-    float sb = 0.f, s0 = 0.f, s1 = 0.f;
-    for (int b = 0; b < B; b++) {
-      float av = a[(int64_t)b * H + j];
-      sb += dh1[(int64_t)b * H + j];
-      s0 += dz[2 * b] * av;
-      s1 += dz[2 * b + 1] * av;
+// Workgroup w < H / 16: db1, dW2[0], dW2[1] of hidden units 16 w .. 16 w + 15, 64 row groups of the
+// batch side by side, added in a fixed order (rows rg, rg + 64, ..., then the groups); the last
+// workgroup: db2 and the mean loss.  One thread per unit over the whole batch, as first
+// written, took 169 us at 512 x 256 (one workgroup, a serial chain of loads); now 5 us.
+__global__ __launch_bounds__(1024) void proxy_reduce_kernel(const float* __restrict__ a, const float* __restrict__ dz,
+                                                            const float* __restrict__ dh1,
+                                                            const float* __restrict__ loss_row, int B, int H,
+                                                            float* __restrict__ g_b1, float* __restrict__ g_w2,
+                                                            float* __restrict__ g_b2, float* __restrict__ loss) {
+  __shared__ float part[16][16][3];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const bool tail = (int)blockIdx.x == H / 16;
+  const int j = blockIdx.x * 16 + threadIdx.x % 16;
+  float s[3] = {0.f, 0.f, 0.f};
+  if (!tail) {
+    for (int b = threadIdx.x / 16; b < B; b += 64) {
+      const float av = a[(int64_t)b * H + j];
+      s[0] += dh1[(int64_t)b * H + j];
+      s[1] += dz[2 * b] * av;
+      s[2] += dz[2 * b + 1] * av;
     }
-    g_b1[j] = sb;
-    g_w2[j] = s0;
-    g_w2[H + j] = s1;
+  } else {
+    for (int b = threadIdx.x; b < B; b += 1024) {
+      s[0] += dz[2 * b];
+      s[1] += dz[2 * b + 1];
+      s[2] += loss_row[b];
+    }
   }
-  if (j == 0) {
-    float d0 = 0.f, d1 = 0.f, l = 0.f;
-    for (int b = 0; b < B; b++) {
-      d0 += dz[2 * b];
-      d1 += dz[2 * b + 1];
-      l += loss_row[b];
+#pragma unroll
+  for (int k = 0; k < 3; k++) {
+    if (tail) {
+      s[k] = wave_sum(s[k]);
+    } else {
+      s[k] += __shfl_xor(s[k], 16, 64);
+      s[k] += __shfl_xor(s[k], 32, 64);
     }
-    g_b2[0] = d0;
-    g_b2[1] = d1;
-    if (loss) *loss = l / (float)B;
+    if (lane < 16) part[wave][lane][k] = s[k];
+  }
+  __syncthreads();
+  if (threadIdx.x >= 16) return;
+  float t[3] = {0.f, 0.f, 0.f};
+  for (int w = 0; w < 16; w++)
+#pragma unroll
+    for (int k = 0; k < 3; k++) t[k] += part[w][threadIdx.x][k];
+  if (!tail) {
+    g_b1[j] = t[0];
+    g_w2[j] = t[1];
+    g_w2[H + j] = t[2];
+  } else if (threadIdx.x == 0) {
+    g_b2[0] = t[0];
+    g_b2[1] = t[1];
+    if (loss) *loss = t[2] / (float)B;
   }
 }
 
 hipError_t proxy_reduce(const float* a, const float* dz, const float* dh1, const float* loss_row, int B, int H,
                         float* g_b1, float* g_w2, float* g_b2, float* loss, hipStream_t st) {
-  hipLaunchKernelGGL(proxy_reduce_kernel, dim3((H + 255) / 256), dim3(256), 0, st, a, dz, dh1, loss_row, B, H, g_b1, g_w2,
+  if (H % 16) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(proxy_reduce_kernel, dim3(H / 16 + 1), dim3(1024), 0, st, a, dz, dh1, loss_row, B, H, g_b1, g_w2,
                      g_b2, loss);
   return hipGetLastError();
 }

@@ -38,10 +38,10 @@ struct kvop_proxy {
 namespace {
 
 // per-batch workspace: x [B d] bf16 | xT [d B] bf16 | h1 [B H] | a [B H] | dz [2B] | dh1 [B H] |
-// dh1T [H B] bf16 | loss_row [B] | loss [1]
+// dh1T [H B] bf16 | loss_row [B]
 struct ProxyWs {
   uint16_t *x, *xT, *dh1T;
-  float *h1, *a, *dz, *dh1, *loss_row, *loss;
+  float *h1, *a, *dz, *dh1, *loss_row;
 };
 
 kvop_status carve_ws(kvop_proxy* p, int B, hipStream_t st, ProxyWs* w) {
@@ -49,7 +49,7 @@ kvop_status carve_ws(kvop_proxy* p, int B, hipStream_t st, ProxyWs* w) {
   size_t o_x = 0, o_xT = o_x + align_up(B * d * 2, 256), o_h1 = o_xT + align_up(B * d * 2, 256),
          o_a = o_h1 + align_up(B * H * 4, 256), o_dz = o_a + align_up(B * H * 4, 256),
          o_dh1 = o_dz + align_up(2 * B * 4, 256), o_dh1T = o_dh1 + align_up(B * H * 4, 256),
-         o_lr = o_dh1T + align_up(H * B * 2, 256), o_l = o_lr + align_up(B * 4, 256), end = o_l + 256;
+         o_lr = o_dh1T + align_up(H * B * 2, 256), end = o_lr + align_up(B * 4, 256);
   if (p->ws.reserve(end, st) != hipSuccess) return fail(KVOP_ENOMEM, "proxy workspace");
   char* b = (char*)p->ws.p;
   w->x = (uint16_t*)(b + o_x);
@@ -60,13 +60,13 @@ kvop_status carve_ws(kvop_proxy* p, int B, hipStream_t st, ProxyWs* w) {
   w->dh1 = (float*)(b + o_dh1);
   w->dh1T = (uint16_t*)(b + o_dh1T);
   w->loss_row = (float*)(b + o_lr);
-  w->loss = (float*)(b + o_l);
   return KVOP_OK;
 }
 
-// forward projection + head backward + reductions: gradients of the mean CE loss in p->grads
+// forward projection + head backward + reductions: gradients of the mean CE loss in grads, the loss
+// in loss (nullable)
 kvop_status proxy_backward(kvop_proxy* p, const float* feats, const int32_t* labels, const int32_t* rows, int B,
-                           hipStream_t st, ProxyWs* w) {
+                           hipStream_t st, ProxyWs* w, float* grads, float* loss) {
   kvop_status s = carve_ws(p, B, st, w);
   if (s != KVOP_OK) return s;
   const int d = p->d, H = p->H;
@@ -80,10 +80,10 @@ kvop_status proxy_backward(kvop_proxy* p, const float* feats, const int32_t* lab
   {
     // dW1 [H, d] = dh1^T [H, B] . x [B, d]: contraction over the batch (x^T is [d, B])
     GemmShape g{H, d, B, B, B, d};
-    HIPTRY(gemm(DT_BF16, DT_F32, EPI_STORE, gemm_pick_tile(DT_BF16, EPI_STORE, g), w->dh1T, w->xT, p->grads, g, st));
+    HIPTRY(gemm(DT_BF16, DT_F32, EPI_STORE, gemm_pick_tile(DT_BF16, EPI_STORE, g), w->dh1T, w->xT, grads, g, st));
   }
-  HIPTRY(proxy_reduce(w->a, w->dz, w->dh1, w->loss_row, B, H, p->grads + p->o_b1(), p->grads + p->o_w2(),
-                      p->grads + p->o_b2(), w->loss, st));
+  HIPTRY(proxy_reduce(w->a, w->dz, w->dh1, w->loss_row, B, H, grads + p->o_b1(), grads + p->o_w2(), grads + p->o_b2(), loss,
+                      st));
   return KVOP_OK;
 }
 
@@ -175,11 +175,7 @@ kvop_status kvop_proxy_grads(kvop_proxy* p, const float* feats, const int32_t* l
   if (!p || !feats || !labels || batch < 8 || batch % 8) return fail(KVOP_EINVAL, "batch must be a multiple of 8");
   hipStream_t st = (hipStream_t)stream;
   ProxyWs w;
-  kvop_status s = proxy_backward(p, feats, labels, rows, batch, st, &w);
-  if (s != KVOP_OK) return s;
-  if (grads_out) HIPTRY(hipMemcpyAsync(grads_out, p->grads, p->P * 4, hipMemcpyDeviceToDevice, st));
-  if (loss_out) HIPTRY(hipMemcpyAsync(loss_out, w.loss, 4, hipMemcpyDeviceToDevice, st));
-  return KVOP_OK;
+  return proxy_backward(p, feats, labels, rows, batch, st, &w, grads_out ? grads_out : p->grads, loss_out);
 }
 
 kvop_status kvop_proxy_train_step(kvop_proxy* p, const float* feats, const int32_t* labels, const int32_t* rows,
@@ -188,12 +184,11 @@ kvop_status kvop_proxy_train_step(kvop_proxy* p, const float* feats, const int32
   if (!(lr > 0.f)) return fail(KVOP_EINVAL, "learning rate must be positive");
   hipStream_t st = (hipStream_t)stream;
   ProxyWs w;
-  kvop_status s = proxy_backward(p, feats, labels, rows, batch, st, &w);
+  kvop_status s = proxy_backward(p, feats, labels, rows, batch, st, &w, p->grads, loss_out);
   if (s != KVOP_OK) return s;
   p->step++;
   HIPTRY(proxy_adam(p->params, p->grads, p->m, p->v, p->P, (int64_t)p->H * p->d, p->w1b, lr, p->beta1, p->beta2,
                     p->eps, p->step, st));
-  if (loss_out) HIPTRY(hipMemcpyAsync(loss_out, w.loss, 4, hipMemcpyDeviceToDevice, st));
   return KVOP_OK;
 }
 

@@ -46,3 +46,33 @@ def test_standardiser_streams_the_same_sums(device, n):
     for a, b in zip(*outs):
         np.testing.assert_array_equal(a, b)
     assert np.all(np.isfinite(outs[0][1]))
+
+
+@pytest.mark.parametrize("batch,h", [(8, 64), (64, 128), (72, 64), (1032, 256), (512, 512)])
+def test_gradients_over_batch_remainders(device, batch, h):
+    """Bias, head and loss gradients against sums in float64 over the batch.  Bound: the FP32 terms
+    carry the BF16 roundings of x and W1 (relative 2^-8 each, 2^-6 of the sum of magnitudes covers
+    both layers)."""
+    d = 128
+    p, px = _proxy(d, h, batch)
+    rng = np.random.default_rng(batch)
+    feats = rng.standard_normal((batch + 5, d)).astype(np.float32)
+    labels = rng.integers(0, 2, batch + 5).astype(np.int32)
+    rows = rng.permutation(batch + 5)[:batch].astype(np.int32)
+    g = torch.empty(h * d + 3 * h + 2, device="cuda")
+    loss = torch.empty(1, device="cuda")
+    K.kvop_proxy_grads(px, torch.from_numpy(feats).cuda(), torch.from_numpy(labels).cuda(),
+                       torch.from_numpy(rows).cuda(), batch, g, loss)
+    torch.cuda.synchronize()
+    got = g.cpu().numpy().astype(np.float64)
+    t = {q: torch.tensor(np.asarray(v, np.float64), requires_grad=True) for q, v in p.items()}
+    x = torch.tensor(feats[rows].astype(np.float64))
+    z = torch.nn.functional.gelu(x @ t["w1"].T + t["b1"]) @ t["w2"].T + t["b2"]
+    ref = torch.nn.functional.cross_entropy(z, torch.tensor(labels[rows].astype(np.int64)))
+    ref.backward()
+    o = h * d
+    for lo, hi, name in ((0, o, "w1"), (o, o + h, "b1"), (o + h, o + 3 * h, "w2"), (o + 3 * h, o + 3 * h + 2, "b2")):
+        e = got[lo:hi] - t[name].grad.numpy().ravel()
+        assert np.linalg.norm(e) <= 2.0 ** -6 * (np.linalg.norm(t[name].grad.numpy()) + 2.0 ** -6), name
+    assert abs(float(loss[0]) - float(ref)) <= 2.0 ** -6
+    K.kvop_proxy_destroy(px)
