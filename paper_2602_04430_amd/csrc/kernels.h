@@ -206,6 +206,11 @@ hipError_t read_cache(int kvdt, const uint8_t* region, int L, int D, int layer, 
 hipError_t proxy_stats(const float* F, int64_t n, int d, float* mean, float* istd, hipStream_t st);
 hipError_t proxy_gather(const float* F, int d, const int32_t* rows, int B, const float* mean, const float* istd,
                         uint16_t* x, uint16_t* xT, hipStream_t st);
+// inference over n rows in one pass (features, BF16 W1 [H][d], head): whether it is the faster form
+bool proxy_infer_fused(int n, int d, int H);
+hipError_t proxy_infer(const float* F, int n, int d, int H, const float* mean, const float* istd, const uint16_t* w1,
+                       const float* b1, const float* W2, const float* b2, float tau, int8_t* cls, float* conf,
+                       int8_t* answered, hipStream_t st);
 hipError_t proxy_head_infer(const float* h1, int n, int H, const float* b1, const float* W2, const float* b2,
                             float tau, int8_t* cls, float* conf, int8_t* answered, hipStream_t st);
 hipError_t proxy_head_train(const float* h1, int B, int H, const float* b1, const float* W2, const float* b2,

@@ -9,6 +9,8 @@
 //   dW1       : dh1^T x on the projection kernel (contraction over the batch)
 //   reduce    : dW2 = dz^T a, db2 = sum dz, db1 = sum dh1, loss = mean CE (fixed order)
 //   adam      : bias-corrected Adam on the FP32 masters; refresh the BF16 copy of W1
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -200,6 +202,184 @@ hipError_t proxy_gather(const float* F, int d, const int32_t* rows, int B, const
 __device__ inline float gelu_f(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
 __device__ inline float gelu_grad_f(float x) {
   return 0.5f * (1.0f + erff(x * 0.70710678118654752f)) + x * 0.39894228040143268f * expf(-0.5f * x * x);
+}
+
+// Inference over blocks of 16 MB rows in one pass over the features: each of the first MB
+// wavefronts standardises 16 rows in registers (its A fragments, loaded PA slabs ahead) and
+// multiplies them with slabs of W1 that two more wavefronts bring into LDS by direct loads; the
+// hidden pre-activations then go through LDS to the per-row head below, in its order of
+// additions.  The MFMA steps run over the depth in order, as the projection tiles do, so the
+// results equal the separate passes (gather, projection, head) bit for bit.
+//
+// Bound by reading the features once (164 MB for 20 000 x 2048).  The rows per workgroup are the
+// fewest that make one round of the 256 CUs (16 to 96): every workgroup streams all of W1 from
+// L2, and a second round would cost as much again.  20 000 rows: 133 us as three passes (72
+// gather, 48 projection, 13 head) when this was written, 56 us now.
+constexpr int kInferLoaders = 2, kInferStages = 4, kInferAhead = 3;
+
+__device__ inline float gelu_f(float x);
+
+template <int MB, int H>
+__global__ __launch_bounds__(64 * (MB + kInferLoaders)) void proxy_infer_kernel(
+    const float* __restrict__ F, int n, int d, const float* __restrict__ mean, const float* __restrict__ istd,
+    const bf16_t* __restrict__ W1, const float* __restrict__ b1, const float* __restrict__ W2,
+    const float* __restrict__ b2, float tau, int8_t* __restrict__ cls, float* __restrict__ conf,
+    int8_t* __restrict__ answered) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t infer_smem[];
+  constexpr int NB = H / 16, OPS = H * 8 / (64 * kInferLoaders), STAGE = H * 128, U = H / 64, EP = H + 4;
+  static_assert(OPS * 64 * kInferLoaders == H * 8, "chunks per loader thread");
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int r0 = blockIdx.x * 16 * MB, nt = d / 64;
+  // the standardiser in LDS: read from memory beside the features, every use of it would wait for
+  // the features in flight (loads return in order)
+  float* st_mean = reinterpret_cast<float*>(infer_smem + (size_t)kInferStages * STAGE);
+  float* st_istd = st_mean + d;
+  for (int c = threadIdx.x; c < d; c += blockDim.x) {
+    st_mean[c] = mean[c];
+    st_istd[c] = istd[c];
+  }
+  __syncthreads();
+  if (wave >= MB) {
+    // ---- W1 slabs: row j of the slab (64 deep) as eight 16-byte chunks, chunk c at slot c ^ (j / 2 & 7)
+    const int lt = threadIdx.x - 64 * MB;
+    auto issue = [&](int t) {
+      uint8_t* dst = infer_smem + (t % kInferStages) * STAGE;
+#pragma unroll
+      for (int i = 0; i < OPS; i++) {
+        const int f = i * 64 * kInferLoaders + lt, j = f / 8, c = (f % 8) ^ ((j >> 1) & 7);
+        __builtin_amdgcn_global_load_lds(
+            reinterpret_cast<const uint8_t*>(W1 + (int64_t)j * d + 64 * t + 8 * c),
+            (__attribute__((address_space(3))) void*)(dst + (i * 64 * kInferLoaders + 64 * (wave - MB)) * 16), 16, 0, 0);
+      }
+    };
+    for (int t = 0; t < kInferStages - 1 && t < nt; t++) issue(t);
+    for (int t = 0; t < nt; t++) {
+      loads_wait_behind<kInferStages - 2, OPS>(nt - 1 - t);
+      __builtin_amdgcn_s_barrier();                    // slab t visible, slab t - 1 consumed
+      if (t + kInferStages - 1 < nt) issue(t + kInferStages - 1);
+    }
+    __builtin_amdgcn_s_barrier();                      // the last slab is consumed
+  } else {
+    const int lrow = lane & 15, lg = lane >> 4;
+    const float* fr = F + (int64_t)min(r0 + 16 * wave + lrow, n - 1) * d + 8 * lg;
+    f32x4_any a[kInferAhead][4];
+    auto load_a = [&](int t, f32x4_any (&v)[4]) {
+#pragma unroll
+      for (int q = 0; q < 4; q++) v[q] = *reinterpret_cast<const f32x4_any*>(fr + 64 * t + 32 * (q >> 1) + 4 * (q & 1));
+    };
+    f32x4 acc[NB];
+#pragma unroll
+    for (int j = 0; j < NB; j++) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < kInferAhead; u++) load_a(min(u, nt - 1), a[u]);
+    for (int t0 = 0; t0 < nt; t0 += kInferAhead) {
+#pragma unroll
+      for (int u = 0; u < kInferAhead; u++) {
+        const int t = t0 + u;
+        if (t >= nt) break;
+        asm volatile("" ::: "memory");                 // one slab's reads at a time (registers)
+        u32x4 fa[2];
+#pragma unroll
+        for (int ks = 0; ks < 2; ks++)
+#pragma unroll
+          for (int hq = 0; hq < 2; hq++) {
+            const int c = 64 * t + 32 * ks + 8 * lg + 4 * hq;
+            const f32x4 mu = *reinterpret_cast<const f32x4*>(st_mean + c);
+            const f32x4 is = *reinterpret_cast<const f32x4*>(st_istd + c);
+            const f32x4_any v = a[u][2 * ks + hq];
+            fa[ks][2 * hq] = pack_bf16x2((v[0] - mu[0]) * is[0], (v[1] - mu[1]) * is[1]);
+            fa[ks][2 * hq + 1] = pack_bf16x2((v[2] - mu[2]) * is[2], (v[3] - mu[3]) * is[3]);
+          }
+        load_a(min(t + kInferAhead, nt - 1), a[u]);
+        __builtin_amdgcn_s_barrier();                  // slab t visible
+        asm volatile("" ::: "memory");
+        const uint8_t* Bs = infer_smem + (t % kInferStages) * STAGE;
+#pragma unroll
+        for (int ks = 0; ks < 2; ks++)
+#pragma unroll
+          for (int j = 0; j < NB; j++) {
+            const int row = 16 * j + lrow;
+            const u32x4 fb = *reinterpret_cast<const u32x4*>(Bs + row * 128 + ((4 * ks + lg) ^ ((row >> 1) & 7)) * 16);
+            acc[j] = mfma_bf16(__builtin_bit_cast(u16x8, fa[ks]), __builtin_bit_cast(u16x8, fb), acc[j]);
+          }
+      }
+    }
+    __builtin_amdgcn_s_barrier();                      // the last slab is consumed
+    asm volatile("" ::: "memory");
+    float* E = reinterpret_cast<float*>(infer_smem) + wave * 16 * EP;
+#pragma unroll
+    for (int j = 0; j < NB; j++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) E[(4 * lg + r) * EP + 16 * j + lrow] = acc[j][r];
+  }
+  __syncthreads();
+  // ---- head: one wavefront per row
+  for (int rr = wave; rr < 16 * MB && r0 + rr < n; rr += MB + kInferLoaders) {
+    const float* h1 = reinterpret_cast<const float*>(infer_smem) + rr * EP;
+    float z0 = 0.f, z1 = 0.f;
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const int j = lane + 64 * u;
+      const float act = gelu_f(h1[j] + b1[j]);
+      z0 = __builtin_fmaf(act, W2[j], z0);
+      z1 = __builtin_fmaf(act, W2[H + j], z1);
+    }
+    z0 = wave_sum(z0) + b2[0];
+    z1 = wave_sum(z1) + b2[1];
+    const float m = fmaxf(z0, z1);
+    const float e0 = expf(z0 - m), e1 = expf(z1 - m);
+    const float p0 = e0 / (e0 + e1), p1 = e1 / (e0 + e1);
+    if (lane == 0) {
+      const int c = p1 > p0 ? 1 : 0;
+      const float cf = c ? p1 : p0;
+      cls[r0 + rr] = (int8_t)c;
+      conf[r0 + rr] = cf;
+      answered[r0 + rr] = cf > tau ? 1 : 0;
+    }
+  }
+}
+
+template <int MB, int H>
+static hipError_t launch_infer(const float* F, int n, int d, const float* mean, const float* istd, const bf16_t* w1,
+                               const float* b1, const float* W2, const float* b2, float tau, int8_t* cls, float* conf,
+                               int8_t* answered, hipStream_t st) {
+  static_assert((size_t)kInferStages * H * 128 >= (size_t)16 * MB * (H + 4) * 4, "pre-activations fit the slabs");
+  const size_t lds = (size_t)kInferStages * H * 128 + 8 * (size_t)d;
+  auto kern = proxy_infer_kernel<MB, H>;
+  static const hipError_t attr =
+      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 << 10);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL(kern, dim3((n + 16 * MB - 1) / (16 * MB)), dim3(64 * (MB + kInferLoaders)), lds, st, F, n, d, mean,
+                     istd, w1, b1, W2, b2, tau, cls, conf, answered);
+  return hipGetLastError();
+}
+
+// Fewer rows than this run the separate passes: a workgroup's stream of W1 takes 28 us whatever its
+// rows (2048 -> 256: 4096 rows 29 us in three passes, 38 in one; 8192 rows 42 and 43; 20 000
+// rows 82 and 56).  The standardiser has 32 KiB of LDS beside the slabs.
+constexpr int kInferFusedRows = 8192;
+static bool infer_sizes_ok(int d, int H) { return d % 64 == 0 && d <= 4096 && (H == 64 || H == 128 || H == 256); }
+bool proxy_infer_fused(int n, int d, int H) { return n >= kInferFusedRows && infer_sizes_ok(d, H); }
+
+hipError_t proxy_infer(const float* F, int n, int d, int H, const float* mean, const float* istd, const bf16_t* w1,
+                       const float* b1, const float* W2, const float* b2, float tau, int8_t* cls, float* conf,
+                       int8_t* answered, hipStream_t st) {
+  if (n <= 0) return hipSuccess;
+  if (!infer_sizes_ok(d, H)) return hipErrorInvalidValue;
+  const int mb = std::min(6, std::max(1, (n + 256 * 16 - 1) / (256 * 16)));
+#define KVOP_INFER(MB)                                                                                                 \
+  (H == 256   ? launch_infer<MB, 256>(F, n, d, mean, istd, w1, b1, W2, b2, tau, cls, conf, answered, st)               \
+   : H == 128 ? launch_infer<MB, 128>(F, n, d, mean, istd, w1, b1, W2, b2, tau, cls, conf, answered, st)               \
+              : launch_infer<MB, 64>(F, n, d, mean, istd, w1, b1, W2, b2, tau, cls, conf, answered, st))
+  switch (mb) {
+    case 1: return KVOP_INFER(1);
+    case 2: return KVOP_INFER(2);
+    case 3: return KVOP_INFER(3);
+    case 4: return KVOP_INFER(4);
+    case 5: return KVOP_INFER(5);
+    default: return KVOP_INFER(6);
+  }
+#undef KVOP_INFER
 }
 
 // one wavefront per row; H <= 512 (H/64 hidden units per lane)

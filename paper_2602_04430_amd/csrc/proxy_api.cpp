@@ -199,6 +199,11 @@ kvop_status kvop_proxy_infer(kvop_proxy* p, const float* feats, int64_t n, float
   const int chunk = 65536;
   for (int64_t r0 = 0; r0 < n; r0 += chunk) {
     const int B = (int)std::min<int64_t>(chunk, n - r0);
+    if (proxy_infer_fused(B, p->d, p->H)) {
+      HIPTRY(proxy_infer(feats + r0 * p->d, B, p->d, p->H, p->mean, p->istd, p->w1b, p->params + p->o_b1(),
+                         p->params + p->o_w2(), p->params + p->o_b2(), tau, cls + r0, conf + r0, answered + r0, st));
+      continue;
+    }
     ProxyWs w;
     kvop_status s = carve_ws(p, B, st, &w);
     if (s != KVOP_OK) return s;
@@ -221,6 +226,11 @@ kvop_status kvop_proxy_infer_noalloc(kvop_proxy* p, const float* feats, int64_t 
                                  std::to_string(d) + ", d_hidden " + std::to_string(H) + " (" + std::to_string(n) +
                                  " given): split the call");
   if (n == 0) return KVOP_OK;
+  if (proxy_infer_fused((int)n, p->d, p->H)) {   // needs no scratch
+    HIPTRY(proxy_infer(feats, (int)n, p->d, p->H, p->mean, p->istd, p->w1b, p->params + p->o_b1(),
+                       p->params + p->o_w2(), p->params + p->o_b2(), tau, cls, conf, answered, (hipStream_t)stream));
+    return KVOP_OK;
+  }
   void* base = nullptr;
   kvop_status s = scratch_address(&base);
   if (s != KVOP_OK) return s;

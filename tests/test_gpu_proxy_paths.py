@@ -27,6 +27,39 @@ def _infer(px, f, tau=0.6):
     return [x.cpu().numpy() for x in out]
 
 
+@pytest.mark.parametrize("d,h", [(64, 64), (192, 128), (2048, 256), (320, 512)])
+def test_row_counts_and_widths(device, d, h):
+    """Every split of the rows gives a row the same answer, equal to the oracle's within the BF16
+    rounding of features and weights (h = 512 takes the separate passes).  The bound: z is a sum
+    of h products with relative input error 2^-8 twice, so |dz| <= 2^-6 sum |W2| |gelu| <=
+    2^-6 (sum W2^2)^1/2 (sum gelu^2)^1/2, and |dp| <= |dz| / 2 for two classes (two logits)."""
+    p, px = _proxy(d, h, d + h)
+    rng = np.random.default_rng(1)
+    n = 4096 * 5 + 7
+    feats = (rng.standard_normal((n, d)) * 0.7).astype(np.float32)
+    f = torch.from_numpy(feats).cuda()
+    cls, conf, ans = _infer(px, f)
+    for m in (1, 15, 17, 33, 4097, 8191, 8192, 8193, 12288, 12289, 16385):
+        if m > n:
+            break
+        c2, f2, a2 = _infer(px, f[:m])
+        np.testing.assert_array_equal(c2, cls[:m])
+        np.testing.assert_array_equal(f2, conf[:m])
+        np.testing.assert_array_equal(a2, ans[:m])
+    k = 200
+    w = {q: np.asarray(v, np.float64) for q, v in p.items()}
+    x = feats[-k:].astype(np.float64)
+    pre = x @ w["w1"].T + w["b1"]
+    act = 0.5 * pre * (1 + np.vectorize(__import__("math").erf)(pre / np.sqrt(2)))
+    z = act @ w["w2"].T + w["b2"]
+    pr = np.exp(z - z.max(1, keepdims=True))
+    ref = (pr / pr.sum(1, keepdims=True)).max(1)
+    spread = np.sqrt((w["w2"] ** 2).sum()) * np.sqrt((act ** 2).sum(1) + (x ** 2).sum(1) * (w["w1"] ** 2).sum(1).max())
+    assert np.all(np.abs(conf[-k:] - ref) <= 2.0 ** -6 * spread)
+    assert np.array_equal(ans, (conf > np.float32(0.6)).astype(np.int8))
+    K.kvop_proxy_destroy(px)
+
+
 @pytest.mark.parametrize("n", [1, 2, 255, 256, 257, 1791, 1792, 1793, 2048, 2049])
 def test_standardiser_streams_the_same_sums(device, n):
     """The streaming standardiser and the one-thread-per-column one (features off a 16-byte
