@@ -809,10 +809,28 @@ static kvop_status kv_build_impl(kvop_pool* p, const int32_t* tokens, const int6
         ea_items.push_back(std::min<int32_t>(1024, Ld - k0));
       }
     }
+    // pooled features: row chunks; documents of one chunk need no partial sums, so the others'
+    // slots are at most a 32nd of the rows (they fit the activations' normalised rows)
+    std::vector<PoolChunk> pchunks;
+    std::vector<PoolDoc> pdocs;
+    if (pooled) {
+      int32_t slots = 0;
+      for (int i = 0; i < nd; i++) {
+        const int32_t L = (int32_t)(row_off[i + 1] - row_off[i]), n = (L + kPoolRows - 1) / kPoolRows;
+        for (int32_t q = 0; q < n; q++)
+          pchunks.push_back(PoolChunk{i, (int32_t)row_off[i] + q * kPoolRows, std::min(kPoolRows, L - q * kPoolRows),
+                                      n > 1 ? slots + q : -1});
+        if (n > 1) {
+          pdocs.push_back(PoolDoc{i, slots, n, L});
+          slots += n;
+        }
+      }
+    }
     Mirror mir;
     size_t o_pos = mir.add(pos.size() * 4), o_blk = mir.add(blocks.size() * sizeof(KvBlock)),
            o_work = mir.add(work.size() * sizeof(AttnWork)), o_roff = mir.add(row_off.size() * 8),
-           o_ord = mir.add(nd * 4), o_items = mir.add(ea_items.size() * 4), o_inv = mir.add(rows * 4);
+           o_ord = mir.add(nd * 4), o_items = mir.add(ea_items.size() * 4),
+           o_pch = mir.add(pchunks.size() * sizeof(PoolChunk)), o_pdoc = mir.add(pdocs.size() * sizeof(PoolDoc));
     if (m->stage.reserve(mir.size) != hipSuccess || m->meta.reserve(mir.size, st) != hipSuccess) {
       rollback();
       return fail(KVOP_ENOMEM, "metadata staging");
@@ -823,8 +841,10 @@ static kvop_status kv_build_impl(kvop_pool* p, const int32_t* tokens, const int6
     memcpy(m->stage.p + o_roff, row_off.data(), row_off.size() * 8);
     memcpy(m->stage.p + o_ord, ea_ord.data(), nd * 4);
     memcpy(m->stage.p + o_items, ea_items.data(), ea_items.size() * 4);
+    if (!pchunks.empty()) memcpy(m->stage.p + o_pch, pchunks.data(), pchunks.size() * sizeof(PoolChunk));
+    if (!pdocs.empty()) memcpy(m->stage.p + o_pdoc, pdocs.data(), pdocs.size() * sizeof(PoolDoc));
     char* md = (char*)m->meta.p;
-    if (hipMemcpyAsync(md, m->stage.p, o_inv, hipMemcpyHostToDevice, st) != hipSuccess ||
+    if (hipMemcpyAsync(md, m->stage.p, mir.size, hipMemcpyHostToDevice, st) != hipSuccess ||
         hipEventRecord(m->stage.ev, st) != hipSuccess) {
       rollback();
       return fail(KVOP_EDEVICE, "metadata upload");
@@ -880,8 +900,9 @@ static kvop_status kv_build_impl(kvop_pool* p, const int32_t* tokens, const int6
       return fail(KVOP_EDEVICE, "expected-attention launch");
     }
     if (pooled) {
-      if (pooled_mean(b.x, d, (const int64_t*)(md + o_roff), nd, (int)rows, m->final_norm, c.rms_eps,
-                      (float*)(md + o_inv), pooled + (int64_t)i0 * d, st) != hipSuccess) {
+      if (pooled_mean(b.x, d, (const PoolChunk*)(md + o_pch), (int)pchunks.size(), (const PoolDoc*)(md + o_pdoc),
+                      (int)pdocs.size(), m->final_norm, c.rms_eps, (float*)b.h, pooled + (int64_t)i0 * d, st) !=
+          hipSuccess) {
         rollback();
         return fail(KVOP_EDEVICE, "pooled launch");
       }

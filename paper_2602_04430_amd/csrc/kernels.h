@@ -168,10 +168,14 @@ hipError_t rope_write_kv(int dt, int kvdt, void* qkv, int64_t ld, const KvBlock*
 // map decode bookkeeping: copy k, v of rows into a per-layer own-row buffer
 hipError_t copy_kv_rows(int dt, const void* qkv, int64_t ld, int kcol, int n_cols, const int32_t* src_rows,
                         const int32_t* dst_rows, int n, void* dst, int64_t ldd, hipStream_t st);
-// pooled[doc] = mean over the document's rows of rmsnorm(x)*g (FP32); row_off[n_docs+1]
-// are row offsets into x; inv_scratch holds n_rows floats
-hipError_t pooled_mean(const float* x, int d, const int64_t* row_off, int n_docs, int n_rows, const float* g,
-                       float eps, float* inv_scratch, float* pooled, hipStream_t st);
+// pooled[doc] = mean over the document's rows of rmsnorm(x)*g (FP32), from chunks of at most
+// kPoolRows rows of one document: slot < 0 finishes the document, else its partial sums go to
+// part[slot][d] and the document's entry in docs adds its slots up
+constexpr int kPoolRows = 64;
+struct PoolChunk { int32_t doc, row0, n, slot; };
+struct PoolDoc { int32_t doc, slot, n, L; };
+hipError_t pooled_mean(const float* x, int d, const PoolChunk* chunks, int n_chunks, const PoolDoc* docs, int n_docs,
+                       const float* g, float eps, float* part, float* pooled, hipStream_t st);
 // filter/join head: y = rmsnorm(x[row_of_item]) * g; logits (yes, no); log-odds decision
 // item i of the launch reads row in_rows[i] of x (or row i when in_rows is null) and writes
 // output row out_rows[i]
