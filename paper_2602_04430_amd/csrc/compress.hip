@@ -12,13 +12,14 @@
 // not depend on scheduling).  Selection: per document, the k highest scores (equal scores:
 // lower row first) listed in ascending row order, by a radix select over the score bits.
 //
-// Work layout of the log-weight kernel (256 threads = 4 wavefronts): the D x D covariance is
-// split so that wavefront w owns rows [w D/4, (w+1) D/4) and lane l an (D/32) x (D/8) block
-// (rows by l / 8, columns by l % 8): D = 128 gives 64 accumulators per lane.  Each document
-// row (query, then key) is staged in LDS as floats; a lane reads D/32 + D/8 of its values per
-// row and does (D/32)(D/8) FMAs.  The covariance then goes through LDS once to apply the
-// averaged rotation (each output element combines at most four inputs: the rotation mixes
-// dimension j only with j +- D/2).
+// Work layout of the log-weight kernel (256 threads = 4 wavefronts per document segment and query
+// head): the covariance of the document's queries is formed on MFMA from row tiles that arrive by
+// direct loads, goes through LDS once to apply the averaged rotation (each output element combines
+// at most four inputs: the rotation mixes dimension j only with j +- D/2), and the quadratic forms
+// run on FP32 MFMA, 32 keys per wavefront.  Bound by the FP32 matrix rate; both products use the
+// covariance's symmetry (36 of 64 blocks at D = 128).  On the vector ALU, a key per lane with
+// broadcast LDS reads of S_r, a layer of 63 000 rows x 16 heads took 1286 us (65 TFLOP/s of FP32
+// products, the queries' tiles transposed element by element); now 404 us.
 #include <algorithm>
 
 #include "common.h"
@@ -70,113 +71,212 @@ __device__ inline float block_max(float v, float* red) {
 }
 
 // ---------------------------------------------------------------- expected log-weights
+typedef __attribute__((address_space(3))) void lds_void_t;
+
+// two fragments of transposed LDS reads (rows at ad[i] and STEP bytes after), with their wait (see
+// the attention kernel: as builtins they would wait for the direct loads in flight)
+template <int STEP> __device__ inline void ds_read_tr16_x2(uint32_t a0, uint32_t a1, u32x4& f0, u32x4& f1) {
+  u32x2 y0, y1, y2, y3;
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %4\n\tds_read_b64_tr_b16 %1, %4 offset:%c6\n\t"
+      "ds_read_b64_tr_b16 %2, %5\n\tds_read_b64_tr_b16 %3, %5 offset:%c6\n\ts_waitcnt lgkmcnt(0)"
+      : "=&v"(y0), "=&v"(y1), "=&v"(y2), "=&v"(y3)
+      : "v"(a0), "v"(a1), "i"(STEP)
+      : "memory");
+  f0 = u32x4{y0[0], y0[1], y1[0], y1[1]};
+  f1 = u32x4{y2[0], y2[1], y3[0], y3[1]};
+}
+template <int STEP> __device__ inline void ds_read_tr16_x4(const uint32_t (&ad)[4], u32x4* f) {
+  u32x2 y[8];
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %8\n\tds_read_b64_tr_b16 %1, %8 offset:%c12\n\t"
+      "ds_read_b64_tr_b16 %2, %9\n\tds_read_b64_tr_b16 %3, %9 offset:%c12\n\t"
+      "ds_read_b64_tr_b16 %4, %10\n\tds_read_b64_tr_b16 %5, %10 offset:%c12\n\t"
+      "ds_read_b64_tr_b16 %6, %11\n\tds_read_b64_tr_b16 %7, %11 offset:%c12\n\ts_waitcnt lgkmcnt(0)"
+      : "=&v"(y[0]), "=&v"(y[1]), "=&v"(y[2]), "=&v"(y[3]), "=&v"(y[4]), "=&v"(y[5]), "=&v"(y[6]), "=&v"(y[7])
+      : "v"(ad[0]), "v"(ad[1]), "v"(ad[2]), "v"(ad[3]), "i"(STEP)
+      : "memory");
+#pragma unroll
+  for (int i = 0; i < 4; i++) f[i] = u32x4{y[2 * i][0], y[2 * i][1], y[2 * i + 1][0], y[2 * i + 1][1]};
+}
+template <int N> __device__ inline void loads_wait() {
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+
+// four consecutive elements as floats
+__device__ inline f32x4 ld4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+__device__ inline f32x4 ld4(const bf16_t* p) {
+  const u32x2 v = *reinterpret_cast<const u32x2*>(p);
+  f32x4 r;
+  r[0] = __builtin_bit_cast(float, v[0] << 16);
+  r[1] = __builtin_bit_cast(float, v[0] & 0xffff0000u);
+  r[2] = __builtin_bit_cast(float, v[1] << 16);
+  r[3] = __builtin_bit_cast(float, v[1] & 0xffff0000u);
+  return r;
+}
+
 template <typename T, int D>
-__global__ __launch_bounds__(kEaThreads) void ea_logw_kernel(const T* __restrict__ qkv, int64_t ld, int H, int Hkv,
+__global__ __launch_bounds__(kEaThreads) __attribute__((amdgpu_waves_per_eu(2))) void ea_logw_kernel(const T* __restrict__ qkv, int64_t ld, int H, int Hkv,
                                                              const int64_t* __restrict__ row_off,
                                                              const int32_t* __restrict__ items, int n_future,
                                                              const float* __restrict__ cos_tab,
                                                              const float* __restrict__ sin_tab,
                                                              float* __restrict__ e_out) {
-  constexpr int BR = D / 32, BC = D / 8, H2 = D / 2;
-  __shared__ __attribute__((aligned(16))) float region[D * D > kEaChunk * D ? D * D : kEaChunk * D];  // S, or rows
-  __shared__ float mu[D], mur[D], cb[H2], sb[H2];
+  constexpr int H2 = D / 2, NB = D / 16, SP = D + 4;   // 16-wide blocks; pitch of the covariance (floats)
+  // the covariance; before it the query rows: BF16 four stages of 64 rows, FP32 one of 64
+  __shared__ __attribute__((aligned(16))) float region[D * SP > kEaChunk * D * 2 ? D * SP : kEaChunk * D * 2];
+  __shared__ __attribute__((aligned(16))) float mu[D], mur[D];
+  __shared__ float cb[H2], sb[H2];
   // work item: (document, first key, key count); the statistics always cover all the
   // document's rows, the keys are this item's segment
   const int32_t* it = items + 3 * (blockIdx.x / H);
   const int doc = it[0], k_lo = it[1], k_hi = it[1] + it[2], h = blockIdx.x % H, g = (h * Hkv) / H;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, lr = lane & 15, lg = lane >> 4;
   const int64_t r0 = row_off[doc];
   const int L = (int)(row_off[doc + 1] - r0);
   const T* Q = qkv + r0 * ld + (int64_t)h * D;
   const T* Kp = qkv + r0 * ld + (int64_t)(H + g) * D;
-  const int a0 = w * (D / 4) + (lane >> 3) * BR, b0 = (lane & 7) * BC;
-
-  // mean of the pre-rotation queries (FP32 path: a pass of its own, each dimension's rows
-  // split over 256 / D threads; the BF16 path sums the rows it stages for the covariance)
-  if constexpr (sizeof(T) == 4) {
-    constexpr int SPLIT = kEaThreads / D;
-    const int j = tid % D, part = tid / D;
-    float s = 0.f;
-#pragma unroll 4
-    for (int i = part; i < L; i += SPLIT) s += ld_f(Q + (int64_t)i * ld + j);
-    region[tid] = s;
-    __syncthreads();
-    if (tid < D) {
-      float t = 0.f;
-      for (int q = 0; q < SPLIT; q++) t += region[q * D + tid];
-      mu[tid] = t / (float)L;
-    }
-    __syncthreads();
-  }
-  // covariance into region (float [D][D])
   const float invL = 1.0f / (float)L;
+  // averaged rotation over the future positions
+  if (tid < H2) {
+    float c = 0.f, s = 0.f;
+#pragma unroll 8
+    for (int p = L; p < L + n_future; p++) {
+      c += cos_tab[(int64_t)p * H2 + tid];
+      s += sin_tab[(int64_t)p * H2 + tid];
+    }
+    cb[tid] = c / (float)n_future;
+    sb[tid] = s / (float)n_future;
+  }
+  // ---- mean and covariance of the pre-rotation queries; covariance into region [D][SP]
   if constexpr (sizeof(T) == 2) {
-    // BF16 queries: S = sum over rows of q q^T on MFMA (exact products, FP32 sums) from a
-    // transposed LDS tile (tile[d][r] = q[c0 + r][d], pitch 40 so that the 16 rows one
-    // fragment read touches fall on distinct banks), then S / L - mu mu^T
-    constexpr int NB = D / 16, PK = 40, NBW = NB * NB / 4, DG = D / 8;
-    static_assert(NBW * 4 == NB * NB, "output blocks per wavefront");
-    bf16_t* tile = reinterpret_cast<bf16_t*>(region);
-    f32x4 cacc[NBW];
+    // BF16 queries: S = sum over rows of q q^T on MFMA (exact products, FP32 sums).  Row-major tiles
+    // of 64 rows by direct loads, three in flight; a transposed read gives a lane eight rows of one
+    // dimension, which serves as A and as B operand.  S is symmetric: wavefront w forms the
+    // blocks (j, i <= j) of block rows w and NB - 1 - w, and by a product with ones the sums of
+    // those dimensions.
+    constexpr int CH = D / 8, NS = 4, OPS = kEaChunk * CH / kEaThreads, TILE = kEaChunk * D;   // elements
+    constexpr int SH = CH >= 16 ? 0 : (CH == 8 ? 1 : 2);          // rows that share a 256-byte bank line
+    constexpr int NR = NB == 8 ? 2 : 1;                           // block rows per wavefront
+    static_assert(OPS * kEaThreads == kEaChunk * CH && NS * TILE * 2 <= (int)sizeof(region), "query tiles");
+    auto swz = [](int r) { return CH >= 4 ? 2 * ((r >> SH) & (CH / 2 - 1)) : 0; };
+    bf16_t* tiles = reinterpret_cast<bf16_t*>(region);
+    const int nt = (L + kEaChunk - 1) / kEaChunk;
+    auto issue = [&](int t) {
 #pragma unroll
-    for (int j = 0; j < NBW; j++) cacc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int sr = tid >> 3, sd = (tid & 7) * DG;   // staging: row, first dimension
-    float colsum[DG];
+      for (int i = 0; i < OPS; i++) {
+        const int f = i * kEaThreads + tid, r = f / CH, c = (f % CH) ^ swz(r);
+        __builtin_amdgcn_global_load_lds(
+            reinterpret_cast<const uint8_t*>(Q + (int64_t)min(t * kEaChunk + r, L - 1) * ld + 8 * c),
+            (lds_void_t*)(tiles + (t % NS) * TILE + (i * kEaThreads + 64 * w) * 8), 16, 0, 0);
+      }
+    };
+    f32x4 acc[NR][NB], ones[NR];
 #pragma unroll
-    for (int u = 0; u < DG; u++) colsum[u] = 0.f;
-    for (int c0 = 0; c0 < L; c0 += 32) {
-      bf16_t v[DG];
-      if (c0 + sr < L) {
-        const bf16_t* src = Q + (int64_t)(c0 + sr) * ld + sd;
+    for (int a = 0; a < NR; a++) {
+      ones[a] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int u = 0; u < DG; u += 4) {
-          const u32x2 x = *reinterpret_cast<const u32x2*>(src + u);
-          v[u] = (bf16_t)(x[0] & 0xffff);
-          v[u + 1] = (bf16_t)(x[0] >> 16);
-          v[u + 2] = (bf16_t)(x[1] & 0xffff);
-          v[u + 3] = (bf16_t)(x[1] >> 16);
+      for (int i = 0; i < NB; i++) acc[a][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const int wu = __builtin_amdgcn_readfirstlane(w);
+    int jr[NR];
+    jr[0] = wu < NB ? wu : -1;
+    if constexpr (NR == 2) jr[1] = NB - 1 - wu;
+    const u32x4 one = u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+    for (int t = 0; t < NS - 1 && t < nt; t++) issue(t);
+    for (int t = 0; t < nt; t++) {
+      const int behind = nt - 1 - t;
+      if (behind >= NS - 2) loads_wait<(NS - 2) * OPS>();
+      else if (behind == 1) loads_wait<OPS>();
+      else loads_wait<0>();
+      __builtin_amdgcn_s_barrier();                    // tile t visible, tile t - 1 consumed
+      if (t + NS - 1 < nt) issue(t + NS - 1);
+      const uint8_t* tb = reinterpret_cast<const uint8_t*>(tiles + (t % NS) * TILE);
+      const int left = L - t * kEaChunk;
+      if (jr[0] < 0) continue;
+#pragma unroll
+      for (int hs = 0; hs < kEaChunk / 32; hs++) {
+        // lane (lr, lg): rows 32 hs + 4 lg + 0..3 and + 16, dimension 16 i + lr
+        u32x4 fr[NB];
+        const int vr = 32 * hs + 4 * lg + (lr >> 2);
+        uint32_t ad[NB];
+#pragma unroll
+        for (int i = 0; i < NB; i++) {
+          const int c = (16 * i + 4 * (lr & 3)) >> 3;
+          ad[i] = (uint32_t)reinterpret_cast<uintptr_t>(tb + vr * D * 2 + (c ^ swz(vr)) * 16 + (lr & 1) * 8);
         }
-      } else {
+        if constexpr (NB == 2) {
+          ds_read_tr16_x2<16 * D * 2>(ad[0], ad[1], fr[0], fr[1]);
+        } else {
 #pragma unroll
-        for (int u = 0; u < DG; u++) v[u] = 0;
-      }
+          for (int i = 0; i < NB; i += 4) {
+            const uint32_t a4[4] = {ad[i], ad[i + 1], ad[i + 2], ad[i + 3]};
+            ds_read_tr16_x4<16 * D * 2>(a4, fr + i);
+          }
+        }
+        if (left < kEaChunk) {                         // rows past the document: zeros
+          const int ra = 32 * hs + 4 * lg;
+          u32x4 keep;
 #pragma unroll
-      for (int u = 0; u < DG; u++) {
-        tile[(sd + u) * PK + sr] = v[u];
-        colsum[u] += bf2f(v[u]);
-      }
-      __syncthreads();
+          for (int q = 0; q < 2; q++) {
+            keep[q] = (ra + 2 * q < left ? 0xffffu : 0u) | (ra + 2 * q + 1 < left ? 0xffff0000u : 0u);
+            keep[2 + q] = (ra + 16 + 2 * q < left ? 0xffffu : 0u) | (ra + 16 + 2 * q + 1 < left ? 0xffff0000u : 0u);
+          }
 #pragma unroll
-      for (int j = 0; j < NBW; j++) {
-        const int bi = w * NBW + j, br = bi / NB, bc = bi % NB;
-        const u32x4 fa = *reinterpret_cast<const u32x4*>(tile + (br * 16 + (lane & 15)) * PK + 8 * (lane >> 4));
-        const u32x4 fb = *reinterpret_cast<const u32x4*>(tile + (bc * 16 + (lane & 15)) * PK + 8 * (lane >> 4));
-        cacc[j] = mfma_bf16(__builtin_bit_cast(u16x8, fa), __builtin_bit_cast(u16x8, fb), cacc[j]);
+          for (int i = 0; i < NB; i++) fr[i] &= keep;
+        }
+#pragma unroll
+        for (int a = 0; a < NR; a++) {
+          u32x4 fj = fr[0];
+#pragma unroll
+          for (int i = 1; i < NB; i++)
+            if (jr[a] == i) fj = fr[i];                // uniform
+          ones[a] = mfma_bf16(__builtin_bit_cast(u16x8, fj), __builtin_bit_cast(u16x8, one), ones[a]);
+#pragma unroll
+          for (int i = 0; i < NB; i++)
+            if (i <= jr[a])
+              acc[a][i] = mfma_bf16(__builtin_bit_cast(u16x8, fj), __builtin_bit_cast(u16x8, fr[i]), acc[a][i]);
+        }
       }
-      __syncthreads();
     }
-    // mean: the 32 staging threads of each dimension group add their column sums
-    float* part = region + D * PK / 2;   // past the tile (floats)
+    __syncthreads();                                   // the tiles are consumed: region takes the covariance
 #pragma unroll
-    for (int u = 0; u < DG; u++) part[sr * D + sd + u] = colsum[u];
+    for (int a = 0; a < NR; a++)
+      if (jr[a] >= 0 && lr == 0)
+#pragma unroll
+        for (int r = 0; r < 4; r++) mu[16 * jr[a] + 4 * lg + r] = ones[a][r] * invL;
     __syncthreads();
-    if (tid < D) {
-      float t = 0.f;
-      for (int q = 0; q < 32; q++) t += part[q * D + tid];
-      mu[tid] = t * invL;
-    }
-    __syncthreads();
 #pragma unroll
-    for (int j = 0; j < NBW; j++) {
-      const int bi = w * NBW + j, br = bi / NB, bc = bi % NB;
+    for (int a = 0; a < NR; a++)
 #pragma unroll
-      for (int r = 0; r < 4; r++) {
-        const int ra = br * 16 + 4 * (lane >> 4) + r, rb = bc * 16 + (lane & 15);
-        region[ra * D + rb] = cacc[j][r] * invL - mu[ra] * mu[rb];
-      }
-    }
+      for (int i = 0; i < NB; i++)
+        if (i <= jr[a])
+#pragma unroll
+          for (int r = 0; r < 4; r++) {
+            const int ra = 16 * jr[a] + 4 * lg + r, rb = 16 * i + lr;
+            const float v = acc[a][i][r] * invL - mu[ra] * mu[rb];
+            region[ra * SP + rb] = v;
+            if (i < jr[a]) region[rb * SP + ra] = v;
+          }
   } else {
-    // FP32 queries: centred products on the vector ALU, accumulated in the lane's block
+    // FP32 queries: mean in a pass of its own (each dimension's rows split over 256 / D threads), then
+    // centred products on the vector ALU, accumulated in the lane's block of the covariance
+    constexpr int BR = D / 32, BC = D / 8, SPLIT = kEaThreads / D;
+    const int a0 = w * (D / 4) + (lane >> 3) * BR, b0 = (lane & 7) * BC;
+    {
+      const int j = tid % D, part = tid / D;
+      float s = 0.f;
+#pragma unroll 4
+      for (int i = part; i < L; i += SPLIT) s += ld_f(Q + (int64_t)i * ld + j);
+      region[tid] = s;
+      __syncthreads();
+      if (tid < D) {
+        float t = 0.f;
+        for (int q = 0; q < SPLIT; q++) t += region[q * D + tid];
+        mu[tid] = t / (float)L;
+      }
+      __syncthreads();
+    }
     float acc[BR][BC];
 #pragma unroll
     for (int a = 0; a < BR; a++)
@@ -207,29 +307,19 @@ __global__ __launch_bounds__(kEaThreads) void ea_logw_kernel(const T* __restrict
 #pragma unroll
     for (int a = 0; a < BR; a++)
 #pragma unroll
-      for (int b = 0; b < BC; b++) region[(a0 + a) * D + b0 + b] = acc[a][b] * invL;
-  }
-  // averaged rotation over the future positions, and the rotated mean
-  if (tid < H2) {
-    float c = 0.f, s = 0.f;
-    for (int p = L; p < L + n_future; p++) {
-      c += cos_tab[(int64_t)p * H2 + tid];
-      s += sin_tab[(int64_t)p * H2 + tid];
-    }
-    cb[tid] = c / (float)n_future;
-    sb[tid] = s / (float)n_future;
+      for (int b = 0; b < BC; b++) region[(a0 + a) * SP + b0 + b] = acc[a][b] * invL;
   }
   __syncthreads();
+  // ---- the rotated mean, and S_r = R S R^T in place, one 2x2 quad (a, a + D/2) x (b, b + D/2) at a
+  // time: the rotation mixes dimension j only with j + D/2, so a quad's outputs depend only on its inputs
   if (tid < D) {
     const int j = tid % H2;
     mur[tid] = tid < H2 ? cb[j] * mu[tid] - sb[j] * mu[tid + H2] : sb[j] * mu[j] + cb[j] * mu[tid];
   }
-  // S_r = R S R^T in place, one 2x2 quad (a, a + D/2) x (b, b + D/2) at a time: the rotation
-  // mixes dimension j only with j + D/2, so a quad's four outputs depend only on its inputs
   for (int qd = tid; qd < H2 * H2; qd += kEaThreads) {
     const int qa = qd / H2, qb = qd % H2;
-    float* r0p = region + qa * D;
-    float* r1p = region + (qa + H2) * D;
+    float* r0p = region + qa * SP;
+    float* r1p = region + (qa + H2) * SP;
     const float s00 = r0p[qb], s01 = r0p[qb + H2], s10 = r1p[qb], s11 = r1p[qb + H2];
     const float ca = cb[qa], sa = sb[qa], cc = cb[qb], sc = sb[qb];
     const float t00 = ca * s00 - sa * s10, t01 = ca * s01 - sa * s11;  // rows: R S
@@ -240,69 +330,60 @@ __global__ __launch_bounds__(kEaThreads) void ea_logw_kernel(const T* __restrict
     r1p[qb + H2] = sc * t10 + cc * t11;
   }
   __syncthreads();
-  __syncthreads();  // covariance reads done before the region holds keys
-  // expected log-weight of every rotated key: one key per lane (256 per pass), its rotated
-  // values in registers; S_r rows are read from LDS by all lanes at once (broadcast), so no
-  // cross-lane reduction is needed
+  // ---- expected log-weight of every rotated key: Y = S_r K^T on FP32 MFMA (products and sums in
+  // FP32), 32 keys per wavefront.  A lane holds dimensions 16 i + 4 lg + 0..3 of key lr (and of key
+  // 16 + lr): they are the B operand of block i (its depth runs over 4 lg + s), and Y comes out
+  // with the same dimensions in the same lane, so k . Y needs only a sum over the lane groups.
+  // S_r is symmetric: k^T S_r k = sum over block rows j of k_j . (2 sum_{i<j} S_ji k_i + S_jj k_j).
   const float inv_sqrt_d = rsqrtf((float)D), inv_2d = 0.5f / (float)D;
-  for (int c0 = k_lo; c0 < k_hi; c0 += kEaThreads) {
-    const int p = c0 + tid;
-    float k[D];
-    if (p < k_hi) {
-      const T* kr = Kp + (int64_t)p * ld;
-      const float* ct = cos_tab + (int64_t)p * H2;
-      const float* st = sin_tab + (int64_t)p * H2;
+  for (int c0 = k_lo + 32 * w; c0 < k_hi; c0 += 32 * (kEaThreads / 64)) {
+    f32x4 kv[2][NB];
 #pragma unroll
-      for (int j = 0; j < H2; j += 8) {
-        float x1[8], x2[8];
-        ld8(kr + j, x1);
-        ld8(kr + j + H2, x2);
+    for (int u = 0; u < 2; u++) {
+      const int p = min(c0 + 16 * u + lr, k_hi - 1);
+      const T* kr = Kp + (int64_t)p * ld + 4 * lg;
+      const float* ct = cos_tab + (int64_t)p * H2 + 4 * lg;
+      const float* st = sin_tab + (int64_t)p * H2 + 4 * lg;
 #pragma unroll
-        for (int u = 0; u < 8; u += 4) {
-          const f32x4 cs = *reinterpret_cast<const f32x4*>(ct + j + u);
-          const f32x4 sn = *reinterpret_cast<const f32x4*>(st + j + u);
-#pragma unroll
-          for (int v = 0; v < 4; v++) {
-            k[j + u + v] = x1[u + v] * cs[v] - x2[u + v] * sn[v];
-            k[j + u + v + H2] = x2[u + v] * cs[v] + x1[u + v] * sn[v];
-          }
-        }
+      for (int i = 0; i < NB / 2; i++) {
+        const f32x4 x1 = ld4(kr + 16 * i), x2 = ld4(kr + 16 * i + H2), cs = ld4(ct + 16 * i), sn = ld4(st + 16 * i);
+        kv[u][i] = x1 * cs - x2 * sn;
+        kv[u][i + NB / 2] = x2 * cs + x1 * sn;
       }
-    } else {
-#pragma unroll
-      for (int j = 0; j < D; j++) k[j] = 0.f;
     }
-    float e = 0.f;
-#pragma unroll 1
-    for (int blk = 0; blk < D / 8; blk++) {
-      float ka[8];
+    float e[2] = {0.f, 0.f};
 #pragma unroll
-      for (int c = 0; c < D / 8; c++)   // blk is uniform: one branch taken, no indexed registers
-        if (c == blk) {
+    for (int j = 0; j < NB; j++) {
+      asm volatile("" ::: "memory");                   // one block row's reads at a time (registers)
+      const float* srow = region + (16 * j + lr) * SP + 4 * lg;
+      f32x4 y[2];
 #pragma unroll
-          for (int u = 0; u < 8; u++) ka[u] = k[8 * c + u];
+      for (int u = 0; u < 2; u++) y[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i <= j; i++) {
+        if (i == j) {
+#pragma unroll
+          for (int u = 0; u < 2; u++) y[u] += y[u];
         }
-      // the block's eight rows of S_r k as eight independent FMA chains (S_r rows: broadcast
-      // LDS reads)
-      const float* sr = region + 8 * blk * D;
-      float y[8];
+        const f32x4 s4 = *reinterpret_cast<const f32x4*>(srow + 16 * i);
 #pragma unroll
-      for (int u = 0; u < 8; u++) y[u] = 0.f;
+        for (int s = 0; s < 4; s++)
 #pragma unroll
-      for (int b = 0; b < D; b += 4) {
-#pragma unroll
-        for (int u = 0; u < 8; u++) {
-          const f32x4 s4 = *reinterpret_cast<const f32x4*>(sr + u * D + b);
-          y[u] = fmaf(s4[0], k[b], y[u]);
-          y[u] = fmaf(s4[1], k[b + 1], y[u]);
-          y[u] = fmaf(s4[2], k[b + 2], y[u]);
-          y[u] = fmaf(s4[3], k[b + 3], y[u]);
-        }
+          for (int u = 0; u < 2; u++) y[u] = mfma_f32(s4[s], kv[u][i][s], y[u]);
       }
+      const f32x4 m4 = *reinterpret_cast<const f32x4*>(mur + 16 * j + 4 * lg);
 #pragma unroll
-      for (int u = 0; u < 8; u++) e = fmaf(ka[u], fmaf(y[u], inv_2d, mur[8 * blk + u] * inv_sqrt_d), e);
+      for (int u = 0; u < 2; u++)
+#pragma unroll
+        for (int s = 0; s < 4; s++) e[u] = fmaf(kv[u][j][s], fmaf(y[u][s], inv_2d, m4[s] * inv_sqrt_d), e[u]);
     }
-    if (p < k_hi) e_out[(r0 + p) * H + h] = e;
+#pragma unroll
+    for (int u = 0; u < 2; u++) {
+      e[u] += __shfl_xor(e[u], 16, 64);
+      e[u] += __shfl_xor(e[u], 32, 64);
+      const int p = c0 + 16 * u + lr;
+      if (lg == 0 && p < k_hi) e_out[(r0 + p) * H + h] = e[u];
+    }
   }
 }
 
@@ -313,7 +394,8 @@ __global__ __launch_bounds__(kEaThreads) void ea_contrib_kernel(const T* __restr
                                                                 const int32_t* __restrict__ order,
                                                                 const float* __restrict__ e_in,
                                                                 float* __restrict__ acc) {
-  __shared__ float red[4];
+  constexpr int kKeep = 8192;
+  __shared__ float red[4], keep[kKeep];
   __shared__ float mx[64], zs[64];
   const int doc = order[blockIdx.x / Hkv], g = blockIdx.x % Hkv, G = H / Hkv;
   const int tid = threadIdx.x;
@@ -323,9 +405,11 @@ __global__ __launch_bounds__(kEaThreads) void ea_contrib_kernel(const T* __restr
   for (int q = 0; q < G; q++) {
     const int h = g * G + q;
     float m = -INFINITY;
+#pragma unroll 4
     for (int i = tid; i < L; i += kEaThreads) m = fmaxf(m, e_in[(r0 + i) * H + h]);
     m = block_max(m, red);
     float z = 0.f;
+#pragma unroll 4
     for (int i = tid; i < L; i += kEaThreads) z += __expf(e_in[(r0 + i) * H + h] - m);
     z = block_sum(z, red);
     if (tid == 0) { mx[q] = m; zs[q] = z; }
@@ -333,19 +417,28 @@ __global__ __launch_bounds__(kEaThreads) void ea_contrib_kernel(const T* __restr
   __syncthreads();
   auto contrib = [&](int i) {
     float vn = 0.f;
-    for (int j = 0; j < D; j++) {
-      const float x = ld_f(V + (int64_t)i * ld + j);
-      vn = fmaf(x, x, vn);
+    const T* v = V + (int64_t)i * ld;
+#pragma unroll
+    for (int j = 0; j < D; j += 8) {
+      float x[8];
+      ld8(v + j, x);
+#pragma unroll
+      for (int u = 0; u < 8; u++) vn = fmaf(x[u], x[u], vn);
     }
     float wsum = 0.f;
     for (int q = 0; q < G; q++) wsum += __expf(e_in[(r0 + i) * H + g * G + q] - mx[q]) / zs[q];
     return wsum / (float)G * sqrtf(vn);
   };
+  // the first kKeep rows' contributions wait in LDS for the document's total
   float tot = 0.f;
-  for (int i = tid; i < L; i += kEaThreads) tot += contrib(i);
+  for (int i = tid; i < L; i += kEaThreads) {
+    const float c = contrib(i);
+    if (i < kKeep) keep[i] = c;
+    tot += c;
+  }
   tot = block_sum(tot, red);
   for (int i = tid; i < L; i += kEaThreads)
-    acc[(r0 + i) * Hkv + g] += tot > 0.f ? contrib(i) / tot : 1.0f / (float)L;
+    acc[(r0 + i) * Hkv + g] += tot > 0.f ? (i < kKeep ? keep[i] : contrib(i)) / tot : 1.0f / (float)L;
 }
 
 __global__ void ea_finish_kernel(const float* __restrict__ acc, int Hkv, int rows, float* __restrict__ out) {
