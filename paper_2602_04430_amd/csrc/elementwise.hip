@@ -54,14 +54,21 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ 
   const float* xr = x + (int64_t)row * ldx;
   TO* yr = y + (int64_t)row * ldy;
   constexpr int KEEP = 8;                     // 16-byte pieces per lane kept in registers
-  f32x4 keep[KEEP];
+  f32x4 keep[KEEP], gain[KEEP];               // (the gains come with the row: one latency, not two)
   float ss = 0.f;
 #pragma unroll
   for (int it = 0; it < KEEP; it++) {
     const int c = lane * 4 + 256 * it;
     if (c < d) {
-      const f32x4 v = *reinterpret_cast<const f32x4*>(xr + c);
-      keep[it] = v;
+      keep[it] = *reinterpret_cast<const f32x4*>(xr + c);
+      gain[it] = *reinterpret_cast<const f32x4*>(g + c);
+    }
+  }
+#pragma unroll
+  for (int it = 0; it < KEEP; it++) {
+    const int c = lane * 4 + 256 * it;
+    if (c < d) {
+      const f32x4 v = keep[it];
       ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
     }
   }
@@ -71,8 +78,7 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ 
   }
   ss = wave_sum(ss);
   float inv = 1.0f / sqrtf(ss / (float)d + eps);
-  auto put = [&](int c, const f32x4& v) {
-    const f32x4 gg = *reinterpret_cast<const f32x4*>(g + c);
+  auto put = [&](int c, const f32x4& v, const f32x4& gg) {
     if constexpr (sizeof(TO) == 2) {
       u32x2 pk;
       pk[0] = pack_bf16x2(v[0] * inv * gg[0], v[1] * inv * gg[1]);
@@ -86,9 +92,10 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ 
 #pragma unroll
   for (int it = 0; it < KEEP; it++) {
     const int c = lane * 4 + 256 * it;
-    if (c < d) put(c, keep[it]);
+    if (c < d) put(c, keep[it], gain[it]);
   }
-  for (int c = lane * 4 + 256 * KEEP; c < d; c += 256) put(c, *reinterpret_cast<const f32x4*>(xr + c));
+  for (int c = lane * 4 + 256 * KEEP; c < d; c += 256)
+    put(c, *reinterpret_cast<const f32x4*>(xr + c), *reinterpret_cast<const f32x4*>(g + c));
 }
 
 hipError_t rmsnorm_rows(int dt, const float* x, int64_t ldx, const float* g, int n_rows, int d, float eps, void* y,
