@@ -570,6 +570,13 @@ static const TileCfg kF32Tiles[] = {
     {64, 128, 32, 32, 64, 0, 4, 0, "f32_64x128x32_w32x64"},
     {128, 64, 32, 64, 32, 0, 4, 0, "f32_128x64x32_w64x32"},
     {128, 128, 32, 64, 64, 1, 4, 0, "f32_128x128x32_w64x64_swz1"},
+    {32, 16, 128, 16, 32, 2, 8, 4, "f32_32x16x128_8w_swz2_lds4"},
+    {32, 32, 128, 16, 32, 2, 8, 4, "f32_32x32x128_8w_swz2_lds4"},
+    {32, 64, 128, 16, 32, 2, 4, 3, "f32_32x64x128_w16x32_swz2_lds3"},
+    {64, 64, 64, 32, 32, 2, 4, 5, "f32_64x64x64_w32x32_swz2_lds5"},
+    {64, 64, 32, 32, 32, 1, 4, 4, "f32_64x64x32_w32x32_swz1_lds4"},
+    {64, 128, 32, 32, 64, 1, 4, 2, "f32_64x128x32_w32x64_swz1_lds2"},
+    {128, 128, 32, 64, 64, 1, 4, 2, "f32_128x128x32_w64x64_swz1_lds2"},
 };
 static const TileCfg kBf16Tiles[] = {
     {128, 128, 64, 64, 64, 0, 4, 0, "bf16_128x128x64_w64x64"},
@@ -614,7 +621,7 @@ static const TileCfg kBf16Tiles[] = {
     {128, 256, 64, 64, 64, 2, 8, 3, "bf16_128x256x64_8w_w64x64_swz2_lds3_pipe"},
 };
 
-int gemm_num_tiles(int dt) { return dt == DT_F32 ? 4 : (int)(sizeof(kBf16Tiles) / sizeof(kBf16Tiles[0])); }
+int gemm_num_tiles(int dt) { return (int)(dt == DT_F32 ? sizeof(kF32Tiles) : sizeof(kBf16Tiles)) / (int)sizeof(TileCfg); }
 const char* gemm_tile_name(int dt, int t) { return dt == DT_F32 ? kF32Tiles[t].name : kBf16Tiles[t].name; }
 
 static const TileCfg& tile_cfg(int dt, int t) { return dt == DT_F32 ? kF32Tiles[t] : kBf16Tiles[t]; }
@@ -660,7 +667,16 @@ static hipError_t launch_cfg(int tile, const void* A, const void* B, void* C, co
       case 0: return launch_t<T, TO, EPI, 128, 128, 32, 64, 64, 0>(A, B, C, s, st, rp);
       case 1: return launch_t<T, TO, EPI, 64, 128, 32, 32, 64, 0>(A, B, C, s, st, rp);
       case 2: return launch_t<T, TO, EPI, 128, 64, 32, 64, 32, 0>(A, B, C, s, st, rp);
-      default: return launch_t<T, TO, EPI, 128, 128, 32, 64, 64, 1>(A, B, C, s, st, rp);
+      case 3: return launch_t<T, TO, EPI, 128, 128, 32, 64, 64, 1>(A, B, C, s, st, rp);
+      case 4: return launch_t<T, TO, EPI, 32, EPI == EPI_SWIGLU ? 32 : 16, 128, 16, EPI == EPI_SWIGLU ? 32 : 16, 2, 8,
+                              4>(A, B, C, s, st, rp);
+      case 5: return launch_t<T, TO, EPI, 32, 32, 128, 16, EPI == EPI_SWIGLU ? 32 : 16, 2, 8, 4>(A, B, C, s, st, rp);
+      case 6: return launch_t<T, TO, EPI, 32, 64, 128, 16, 32, 2, 4, 3>(A, B, C, s, st, rp);
+      case 7: return launch_t<T, TO, EPI, 64, 64, 64, 32, 32, 2, 4, 5>(A, B, C, s, st, rp);
+      case 8: return launch_t<T, TO, EPI, 64, 64, 32, 32, 32, 1, 4, 4>(A, B, C, s, st, rp);
+      case 9: return launch_t<T, TO, EPI, 64, 128, 32, 32, 64, 1, 4, 2>(A, B, C, s, st, rp);
+      case 10: return launch_t<T, TO, EPI, 128, 128, 32, 64, 64, 1, 4, 2>(A, B, C, s, st, rp);
+      default: return hipErrorInvalidValue;
     }
   } else {
     switch (tile) {
@@ -775,31 +791,46 @@ int gemm_pick_tile(int dt, int epi, const GemmShape& s, bool aligned) {
   if (it != tuned().end() && gemm_tile_ok(dt, it->second, s, epi) &&
       (aligned || tile_cfg(dt, it->second).NS == 0))
     return it->second;
-  if (dt == DT_F32) return s.M <= 64 ? 1 : 0;
-  // The tile with the least estimated time: rounds of resident workgroups over the 256 CUs,
-  // each taking a + b K / 1024 microseconds.  a and b are fits to the O (K = 2048) and down
-  // (K = 5632) projections timed with weights not in any cache, at row counts where one round
-  // is nearly full; every tile gives the same bits, so the choice is a matter of time only.
-  // Few rows: the time is a CU's share of the weights, so narrow tiles spread them over more
-  // CUs (M = 32, down: 88 us with the 16 workgroups of 64x128, 16 us with 64 of 32x32).
-  // Many rows: the larger the tile the fewer bytes per MFMA, until a round is not filled.
-  struct Cand { int tile, per_cu; float a, b; };
-  static const Cand cands[] = {
-      {27, 1, 4.7f, 1.6f}, {28, 1, 3.9f, 2.2f}, {29, 1, 3.5f, 3.3f}, {30, 1, 3.6f, 3.1f}, {31, 1, 4.7f, 4.3f},
-      {33, 1, 5.4f, 6.3f}, {32, 2, 5.7f, 12.2f}, {35, 1, 5.6f, 9.2f}, {34, 2, 9.0f, 17.6f}, {36, 1, 7.8f, 12.1f},
-      {37, 1, 8.3f, 12.4f}, {26, 1, 12.7f, 20.4f}};
+  // The tile with the least estimated time; every tile gives the same bits, so the choice is a
+  // matter of time only.  A candidate's tiles go over the 256 CUs in rounds (of per_cu resident
+  // workgroups each); a round takes a + b K / 1024 microseconds, and fixed + tail K / 1024 more once,
+  // where workgroups of successive rounds share a CU and the last one runs alone.  The
+  // constants are fits to the O (K = 2048) and down (K = 5632) projections timed with weights
+  // not in any cache, at row counts where one round is nearly full.
+  // Few rows: the time is a CU's share of the weights (BF16) or of the MFMAs (FP32), so narrow
+  // tiles spread them over more CUs (M = 32, BF16 down: 88 us with the 16 workgroups of 64x128,
+  // 16 us with 64 of 32x32; M = 64, FP32 down: 235 us with 64x128, 44 us with 128 of 32x32).
+  // Many rows: the larger the tile the fewer bytes per MFMA, until a round is not filled
+  // (FP32, N = 2048, K = 5632: M = 512 415 us with the 64 register-staged 128x128 workgroups,
+  // 115 us with 256 of 64x64; M = 2048 424 us register-staged, 374 us direct-load, both 128x128).
+  struct Cand { int tile, per_cu; float a, b, fixed, tail; };
+  static const Cand bf16_cands[] = {
+      {27, 1, 4.7f, 1.6f, 0, 0}, {28, 1, 3.9f, 2.2f, 0, 0}, {29, 1, 3.5f, 3.3f, 0, 0},  {30, 1, 3.6f, 3.1f, 0, 0},
+      {31, 1, 4.7f, 4.3f, 0, 0}, {33, 1, 5.4f, 6.3f, 0, 0}, {32, 2, 5.7f, 12.2f, 0, 0}, {35, 1, 5.6f, 9.2f, 0, 0},
+      {34, 2, 9.0f, 17.6f, 0, 0}, {36, 1, 7.8f, 12.1f, 0, 0}, {37, 1, 8.3f, 12.4f, 0, 0}, {26, 1, 12.7f, 20.4f, 0, 0}};
+  static const Cand f32_cands[] = {
+      {4, 1, 2.8f, 7.5f, 0, 0},       {5, 1, 2.7f, 8.3f, 0, 0},       {6, 1, 4.8f, 12.7f, 0, 0},
+      {7, 1, 5.8f, 19.8f, 0, 0},      {8, 1, 0, 17.5f, 5.8f, 3.8f},   {9, 1, 0, 33.0f, 4.6f, 3.7f},
+      {10, 1, 0, 63.0f, 8.0f, 3.6f}};
+  const Cand* cands = dt == DT_F32 ? f32_cands : bf16_cands;
+  const int n_cands = (int)((dt == DT_F32 ? sizeof(f32_cands) : sizeof(bf16_cands)) / sizeof(Cand));
+  const int swiglu_narrow = dt == DT_F32 ? 4 : 27;   // 32 columns wide where columns go in pairs: no gain over the next
   int best = -1;
   double best_t = 0.0;
-  for (const Cand& c : cands) {
+  for (int i = 0; i < n_cands; i++) {
+    const Cand& c = cands[i];
     if (!aligned) break;   // direct global -> LDS loads move aligned 16-byte chunks
-    if (!gemm_tile_ok(dt, c.tile, s, epi) || (c.tile == 27 && (epi == EPI_SWIGLU || epi == EPI_ROPE))) continue;
-    const TileCfg& t = kBf16Tiles[c.tile];
+    if (!gemm_tile_ok(dt, c.tile, s, epi) || (c.tile == swiglu_narrow && (epi == EPI_SWIGLU || epi == EPI_ROPE)))
+      continue;
+    const TileCfg& t = tile_cfg(dt, c.tile);
     const int64_t tiles = (int64_t)((s.M + t.BM - 1) / t.BM) * ((s.N + t.BN - 1) / t.BN);
-    const double us = (double)((tiles + 256 * c.per_cu - 1) / (256 * c.per_cu)) * (c.a + c.b * s.K / 1024.0);
+    const double k = s.K / 1024.0, rounds = (double)((tiles + 256 * c.per_cu - 1) / (256 * c.per_cu));
+    const double us = rounds * (c.a + c.b * k) + c.fixed + c.tail * k;
     if (best < 0 || us < best_t) { best = c.tile; best_t = us; }
   }
   if (best >= 0) return best;
-  // K not a multiple of 64, or operands off 16-byte boundaries: register-staged tiles
+  // K not a multiple of 64 (BF16) or 32 (FP32), or operands off 16-byte boundaries: register-staged tiles
+  if (dt == DT_F32) return s.M <= 64 ? 1 : 0;
   return s.M <= 128 ? 3 : (s.M < 8192 ? 7 : 11);
 }
 

@@ -54,3 +54,25 @@ def test_operands_off_16_byte_boundaries(device):
     K.kvop_debug_gemm(K.KVOP_BF16, K.KVOP_BF16, 0, -1, A[:, 4:Kd + 4].contiguous(), B, ref, M, N, Kd, Kd, Kd, N)
     torch.cuda.synchronize()
     assert torch.equal(C, ref)
+
+
+@pytest.mark.parametrize("epi", [0, 1, 2])
+@pytest.mark.parametrize("N,Kd", [(2048, 2048), (384, 320), (2080, 192), (640, 5632), (256, 64), (96, 96), (64, 36)])
+def test_chosen_fp32_tile_gives_the_general_tiles_bits(device, epi, N, Kd):
+    """FP32: whole and partial slabs of 128 and 64, slabs of 32 only, and no direct-load tile."""
+    rng = np.random.default_rng(N + Kd + epi)
+    Nc = N // 2 if epi == 2 else N
+    seen = set()
+    for M in (1, 16, 17, 32, 33, 64, 65, 129, 257, 513, 1100, 2049):
+        A = torch.from_numpy(rng.standard_normal((M, Kd + 4)).astype(np.float32)).to(device)
+        B = torch.from_numpy(rng.standard_normal((N, Kd)).astype(np.float32) * 0.05).to(device)
+        C0 = torch.from_numpy(rng.standard_normal((M, Nc)).astype(np.float32)).to(device)
+        outs = []
+        for tile in (0, -1):
+            C = C0.clone()
+            K.kvop_debug_gemm(K.KVOP_F32, K.KVOP_F32, epi, tile, A, B, C, M, N, Kd, Kd + 4, Kd, Nc)
+            outs.append(C)
+        seen.add(K.kvop_gemm_pick_tile(K.KVOP_F32, epi, M, N, Kd))
+        torch.cuda.synchronize()
+        assert torch.equal(outs[0], outs[1]), (epi, M, N, Kd, sorted(seen))
+    assert Kd < 2048 or len(seen) >= 4, seen
