@@ -314,6 +314,37 @@ void count_keys(const std::vector<AttnWork>& work, AttnArgs* a) {
   }
 }
 
+// numbers the FP32 chunks of the items that have several; returns how many there are
+int number_chunks(std::vector<AttnWork>& work, int D) {
+  const int kt = attn_f32_tile(D), per_chunk = kAttnChunkKeys / kt;
+  auto tiles = [kt](int n) { return (n + kt - 1) / kt; };
+  int64_t n = 0;
+  for (AttnWork& w : work) {
+    const int c = (tiles(w.n_a) + tiles(w.n_b) + tiles(w.n_own) + per_chunk - 1) / per_chunk;
+    w.part0 = (int32_t)n;
+    if (c > 1) n += c;
+    if (n > INT32_MAX) return 0;
+  }
+  return (int)n;
+}
+
+// bytes of the chunks' states; a region of their own is not made larger than kMaxPart (4096-row
+// documents: some 120 of them with 64 query rows and 8 kv heads)
+constexpr size_t kMaxPart = (size_t)256 << 20;
+int64_t part_bytes(const kvop_model* m, int64_t chunks, int Pmax) {
+  const kvop_model_cfg& c = m->cfg;
+  return chunks * Pmax * c.n_heads * (c.head_dim + 2) * 4;
+}
+
+// Room for the chunks' states, where the attention takes them: the caller's, or the feed-forward
+// buffer, which is free until the attention is done; none if they do not fit (one workgroup then
+// takes all chunks of a unit, with the same result).
+void give_part(const kvop_model* m, const LayerBufs& b, int64_t rows, AttnArgs* a) {
+  const int64_t need = part_bytes(m, a->n_part, a->Pmax);
+  if (a->n_part <= 0 || m->dt != DT_F32 || !attention_f32_splits(m->cfg.head_dim, *a)) a->part = nullptr;
+  else if (!a->part && need <= rows * m->cfg.d_ffn * 4) a->part = (float*)b.act;
+}
+
 // skip_tail: stop once this layer's keys/values exist (prefill's last layer when the final
 // hidden states are not needed)
 kvop_status run_layer(kvop_model* m, int l, const LayerBufs& b, LayerPlan& lp, uint8_t* pool, int kvdt,
@@ -448,6 +479,7 @@ kvop_status run_layer(kvop_model* m, int l, const LayerBufs& b, LayerPlan& lp, u
   a.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)D));
   {
     ProfScope ps(PC_ATTENTION, st);
+    give_part(m, b, rows, &a);
     if (a.counter) HIPTRY(fill_i32(a.counter, 0, 1, st));
     HIPTRY(attention(dt, kvdt, D, a, st));
   }
@@ -1143,6 +1175,7 @@ static kvop_status op_eval_impl(kvop_pool* p, const kvop_op* op, float r, const 
       for (AttnWork& w : work) w.pad_a = kmax - w.n_b;
       for (AttnWork& w : work_last) w.pad_a = kmax - w.n_b;
     }
+    const int chunks = number_chunks(work, D), chunks_last = number_chunks(work_last, D);
     // map decode: work items with one query position against (retained rows + own rows)
     std::vector<AttnWork> dwork;
     std::vector<int32_t> own_src, own_dst;
@@ -1220,7 +1253,27 @@ static kvop_status op_eval_impl(kvop_pool* p, const kvop_op* op, float r, const 
     // workspace: activations (+ per-layer own rows for maps)
     size_t act = act_bytes(m, rows, join);
     size_t own_bytes = kind == KVOP_MAP ? (size_t)c.n_layers * B * rows_per_item * 2 * Hkv * D * e : 0;
-    if (m->ws.reserve(act + align_up(own_bytes, kAlign), st) != hipSuccess)
+    // FP32 chunks that do not fit the feed-forward buffer: a region of their own, if there is one to
+    // be had (not while the stream is captured: the workspace cannot grow there)
+    LayerPlan lp{};
+    count_keys(work, &lp.attn);
+    lp.attn.Hkv = Hkv;
+    lp.attn.G = G;
+    lp.attn.Pmax = Pmax_s;
+    size_t part = 0;
+    if (m->dt == DT_F32 && chunks > 0 && part_bytes(m, chunks, Pmax_s) > rows * F * 4 &&
+        attention_f32_splits(D, lp.attn)) {
+      hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+      if (hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone)
+        part = (size_t)part_bytes(m, chunks, Pmax_s);
+      if (part > kMaxPart) part = 0;
+    }
+    const size_t base_ws = align_up(act + align_up(own_bytes, kAlign), kAlign);
+    if (part && m->ws.reserve(base_ws + part, st) != hipSuccess) {
+      (void)hipGetLastError();
+      part = 0;
+    }
+    if (!part && m->ws.reserve(act + align_up(own_bytes, kAlign), st) != hipSuccess)
       return fail(KVOP_ENOMEM, "activation workspace");
     LayerBufs bufs = carve(m, (char*)m->ws.p, rows, join);
     char* ownbuf = (char*)m->ws.p + act;
@@ -1230,13 +1283,11 @@ static kvop_status op_eval_impl(kvop_pool* p, const kvop_op* op, float r, const 
       ProfScope ps(PC_EMBED, st);
       HIPTRY(embed_suffix(m->dt, m->embed, (const int32_t*)(md + o_suf), S, (int)rows, d, c.vocab, bufs.x, st));
     }
-    LayerPlan lp{};
     lp.rows = (int)rows;
     lp.pos = (const int32_t*)(md + o_pos);
     lp.alt_shift = join ? (const int32_t*)(md + o_shift) : nullptr;
     lp.attn.work = (const AttnWork*)(md + o_work);
     lp.attn.n_work = (int)work.size();
-    count_keys(work, &lp.attn);
     lp.attn.idx = idx;
     lp.attn.Pmax = Pmax_s;
     lp.own_from_qkv = true;
@@ -1252,6 +1303,8 @@ static kvop_status op_eval_impl(kvop_pool* p, const kvop_op* op, float r, const 
       lp.attn.work = (const AttnWork*)(md + (lp.q_last ? o_wlast : o_work));
       lp.attn.n_work = (int)(lp.q_last ? work_last.size() : work.size());
       lp.attn.Pmax = lp.q_last ? 1 : Pmax_s;
+      lp.attn.n_part = lp.q_last ? chunks_last : chunks;
+      lp.attn.part = part ? (float*)((char*)m->ws.p + base_ws) : nullptr;
       kvop_status s = run_layer(m, l, bufs, lp, p->base, p->kvdt, nullptr, 0, st);
       if (s != KVOP_OK) return s;
       if (kind == KVOP_MAP) {

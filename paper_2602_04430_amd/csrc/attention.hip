@@ -13,9 +13,8 @@
 // MFMA layout: scores are computed transposed, S^T = K Q^T, so every accumulator a lane
 // holds belongs to the same query (column lane % 16).  Softmax rescaling is then a
 // per-lane scalar and the probabilities are already in the B-operand layout of the
-// second product O^T = V^T P^T.  FP32 path: v_mfma_f32_16x16x4f32 with K and V row-major
-// in LDS.  BF16 path: v_mfma_f32_16x16x32_bf16 with V stored transposed in LDS; FP8
-// (E4M3) cache rows are widened to BF16 exactly while staging and their per-16-row FP32
+// second product O^T = V^T P^T, both on v_mfma_f32_16x16x32_bf16 with V stored transposed in
+// LDS (FP32 compute has a kernel of its own, attention_f32.hip); FP8 (E4M3) cache rows are widened to BF16 exactly while staging and their per-16-row FP32
 // block scales are applied to the scores (K) and to the probabilities (V).
 #include <algorithm>
 #include <type_traits>
@@ -27,13 +26,12 @@ namespace kvop {
 
 template <typename TC, int D>
 struct AttnCfg {
-  static constexpr bool F32 = std::is_same<TC, float>::value;
-  static constexpr int KT = F32 ? 32 : 64;       // keys per tile
-  static constexpr int KPAD = F32 ? 4 : 8;       // LDS row padding (elements)
-  static constexpr int KLD = D + KPAD;           // K row pitch (and V row pitch for f32)
-  static constexpr int VTLD = KT + 8;            // transposed V row pitch (bf16)
+  static constexpr int KT = 64;                  // keys per tile
+  static constexpr int KPAD = 8;                 // LDS row padding (elements)
+  static constexpr int KLD = D + KPAD;           // K row pitch
+  static constexpr int VTLD = KT + 8;            // transposed V row pitch
   static constexpr int KS_ELEMS = KT * KLD;
-  static constexpr int VS_ELEMS = F32 ? KT * KLD : D * VTLD;
+  static constexpr int VS_ELEMS = D * VTLD;
 };
 
 // One key source of a work item: rows of a cached document (through an optional retained
@@ -59,7 +57,7 @@ struct TileStage {
   static constexpr int NT = 256;
   static constexpr int CPR = D * (int)sizeof(TC) / 16;           // chunks per row in the compute dtype
   static constexpr int NK = (KT * CPR + NT - 1) / NT;             // K chunks per thread
-  static constexpr int NVU = C::F32 ? NK : ((KT / 2) * CPR + NT - 1) / NT;  // V units per thread
+  static constexpr int NVU = ((KT / 2) * CPR + NT - 1) / NT;  // V units per thread
   u32x4 kr[NK];
   u32x4 vr0[NVU], vr1[NVU];
   int kpos[NK];
@@ -93,23 +91,18 @@ struct TileStage {
           vs[i] = s.vsc[row >> 4];
         }
         if (cc < cpr_src) kr[i] = *reinterpret_cast<const u32x4*>(s.k + row * s.pitch + cc * 16);
-        if constexpr (C::F32) vr0[i] = *reinterpret_cast<const u32x4*>(s.v + row * s.pitch + cc * 16);
-      } else if constexpr (C::F32) {
-        vr0[i] = u32x4{0, 0, 0, 0};
       }
     }
-    if constexpr (!C::F32) {
 #pragma unroll
-      for (int i = 0; i < NVU; i++) {
-        int u = tid + i * NT;
-        int jp = u / CPR, cc = u % CPR;
-        int t = t0 + 2 * jp;
-        vr0[i] = u32x4{0, 0, 0, 0};
-        vr1[i] = u32x4{0, 0, 0, 0};
-        if (u < (KT / 2) * CPR && cc < cpr_src) {
-          if (t < s.n) vr0[i] = *reinterpret_cast<const u32x4*>(s.v + row_of(s, t) * s.pitch + cc * 16);
-          if (t + 1 < s.n) vr1[i] = *reinterpret_cast<const u32x4*>(s.v + row_of(s, t + 1) * s.pitch + cc * 16);
-        }
+    for (int i = 0; i < NVU; i++) {
+      int u = tid + i * NT;
+      int jp = u / CPR, cc = u % CPR;
+      int t = t0 + 2 * jp;
+      vr0[i] = u32x4{0, 0, 0, 0};
+      vr1[i] = u32x4{0, 0, 0, 0};
+      if (u < (KT / 2) * CPR && cc < cpr_src) {
+        if (t < s.n) vr0[i] = *reinterpret_cast<const u32x4*>(s.v + row_of(s, t) * s.pitch + cc * 16);
+        if (t + 1 < s.n) vr1[i] = *reinterpret_cast<const u32x4*>(s.v + row_of(s, t + 1) * s.pitch + cc * 16);
       }
     }
   }
@@ -126,50 +119,43 @@ struct TileStage {
         ksc_s[j] = ks[i];
         vsc_s[j] = vs[i];
       }
-      if constexpr (C::F32) {
-        *reinterpret_cast<u32x4*>(Ks + j * C::KLD + cc * 4) = kr[i];
-        *reinterpret_cast<u32x4*>(Vs + j * C::KLD + cc * 4) = vr0[i];
-      } else {
-        if (!fp8) {
-          *reinterpret_cast<u32x4*>(Ks + j * C::KLD + cc * 8) = kr[i];
-        } else if (cc < CPR / 2) {  // 16 codes -> 16 bf16 (elements 16 cc .. 16 cc + 15)
-          u32x4 lo, hi;
+      if (!fp8) {
+        *reinterpret_cast<u32x4*>(Ks + j * C::KLD + cc * 8) = kr[i];
+      } else if (cc < CPR / 2) {  // 16 codes -> 16 bf16 (elements 16 cc .. 16 cc + 15)
+        u32x4 lo, hi;
 #pragma unroll
-          for (int q = 0; q < 4; q++) {
-            uint32_t x = kr[i][q];
-            uint32_t b0 = e4m3_to_bf16(x & 0xff), b1 = e4m3_to_bf16((x >> 8) & 0xff);
-            uint32_t b2 = e4m3_to_bf16((x >> 16) & 0xff), b3 = e4m3_to_bf16(x >> 24);
-            if (q < 2) { lo[2 * q] = b0 | (b1 << 16); lo[2 * q + 1] = b2 | (b3 << 16); }
-            else { hi[2 * (q - 2)] = b0 | (b1 << 16); hi[2 * (q - 2) + 1] = b2 | (b3 << 16); }
-          }
-          *reinterpret_cast<u32x4*>(Ks + j * C::KLD + cc * 16) = lo;
-          *reinterpret_cast<u32x4*>(Ks + j * C::KLD + cc * 16 + 8) = hi;
+        for (int q = 0; q < 4; q++) {
+          uint32_t x = kr[i][q];
+          uint32_t b0 = e4m3_to_bf16(x & 0xff), b1 = e4m3_to_bf16((x >> 8) & 0xff);
+          uint32_t b2 = e4m3_to_bf16((x >> 16) & 0xff), b3 = e4m3_to_bf16(x >> 24);
+          if (q < 2) { lo[2 * q] = b0 | (b1 << 16); lo[2 * q + 1] = b2 | (b3 << 16); }
+          else { hi[2 * (q - 2)] = b0 | (b1 << 16); hi[2 * (q - 2) + 1] = b2 | (b3 << 16); }
         }
+        *reinterpret_cast<u32x4*>(Ks + j * C::KLD + cc * 16) = lo;
+        *reinterpret_cast<u32x4*>(Ks + j * C::KLD + cc * 16 + 8) = hi;
       }
     }
-    if constexpr (!C::F32) {
-      // transposed V: element (d, key) at dword d * VTLD/2 + (key/2 ^ swz(d)), swz(d) = 2*((d/16)&7),
-      // so the 16 lanes of one store (16 different d blocks) hit 16 different banks
-      uint32_t* vt = reinterpret_cast<uint32_t*>(Vs);
+    // transposed V: element (d, key) at dword d * VTLD/2 + (key/2 ^ swz(d)), swz(d) = 2*((d/16)&7),
+    // so the 16 lanes of one store (16 different d blocks) hit 16 different banks
+    uint32_t* vt = reinterpret_cast<uint32_t*>(Vs);
 #pragma unroll
-      for (int i = 0; i < NVU; i++) {
-        int u = tid + i * NT;
-        int jp = u / CPR, cc = u % CPR;
-        if (u >= (KT / 2) * CPR) continue;
-        if (!fp8) {
+    for (int i = 0; i < NVU; i++) {
+      int u = tid + i * NT;
+      int jp = u / CPR, cc = u % CPR;
+      if (u >= (KT / 2) * CPR) continue;
+      if (!fp8) {
 #pragma unroll
-          for (int e = 0; e < 8; e++) {
-            const int d = cc * 8 + e;
-            vt[d * (C::VTLD / 2) + (jp ^ (2 * ((d >> 4) & 7)))] = pair_halves(vr0[i][e >> 1], vr1[i][e >> 1], e & 1);
-          }
-        } else if (cc < CPR / 2) {
+        for (int e = 0; e < 8; e++) {
+          const int d = cc * 8 + e;
+          vt[d * (C::VTLD / 2) + (jp ^ (2 * ((d >> 4) & 7)))] = pair_halves(vr0[i][e >> 1], vr1[i][e >> 1], e & 1);
+        }
+      } else if (cc < CPR / 2) {
 #pragma unroll
-          for (int e = 0; e < 16; e++) {
-            const int d = cc * 16 + e;
-            uint32_t a = e4m3_to_bf16((vr0[i][e >> 2] >> ((e & 3) * 8)) & 0xff);
-            uint32_t b = e4m3_to_bf16((vr1[i][e >> 2] >> ((e & 3) * 8)) & 0xff);
-            vt[d * (C::VTLD / 2) + (jp ^ (2 * ((d >> 4) & 7)))] = a | (b << 16);
-          }
+        for (int e = 0; e < 16; e++) {
+          const int d = cc * 16 + e;
+          uint32_t a = e4m3_to_bf16((vr0[i][e >> 2] >> ((e & 3) * 8)) & 0xff);
+          uint32_t b = e4m3_to_bf16((vr1[i][e >> 2] >> ((e & 3) * 8)) & 0xff);
+          vt[d * (C::VTLD / 2) + (jp ^ (2 * ((d >> 4) & 7)))] = a | (b << 16);
         }
       }
     }
@@ -215,7 +201,7 @@ __device__ void attn_unit(const AttnArgs& a, int unit, AttnSmem<TC, D>& sm) {
   const int64_t qrow = (int64_t)w.q_row0 + (qvalid ? p : 0);
 
   // ---- query fragments (B operand of S^T = K Q^T); qa: rotated for document B (joins)
-  constexpr int NQ = C::F32 ? D / 16 : D / 32;
+  constexpr int NQ = D / 32;
   u32x4 qf[NQ], qa[NQ];
   const bool has_b = w.n_b > 0;
   {
@@ -223,7 +209,7 @@ __device__ void attn_unit(const AttnArgs& a, int unit, AttnSmem<TC, D>& sm) {
     const TC* q2 = reinterpret_cast<const TC*>(a.q_alt ? a.q_alt : a.q) + qrow * a.q_stride + hq * D;
 #pragma unroll
     for (int k = 0; k < NQ; k++) {
-      int d0 = C::F32 ? 16 * k + 4 * g4 : 32 * k + 8 * g4;
+      int d0 = 32 * k + 8 * g4;
       qf[k] = qvalid ? *reinterpret_cast<const u32x4*>(q + d0) : u32x4{0, 0, 0, 0};
       qa[k] = (qvalid && has_b) ? *reinterpret_cast<const u32x4*>(q2 + d0) : u32x4{0, 0, 0, 0};
     }
@@ -313,14 +299,8 @@ __device__ void attn_unit(const AttnArgs& a, int unit, AttnSmem<TC, D>& sm) {
       const TC* krow = Ks + (16 * b + qi) * C::KLD;
 #pragma unroll
       for (int k = 0; k < NQ; k++) {
-        if constexpr (C::F32) {
-          u32x4 kf = *reinterpret_cast<const u32x4*>(krow + 16 * k + 4 * g4);
-#pragma unroll
-          for (int t = 0; t < 4; t++) s[b] = mfma_f32(as_f32(kf[t]), as_f32(qf[k][t]), s[b]);
-        } else {
-          u32x4 kf = *reinterpret_cast<const u32x4*>(krow + 32 * k + 8 * g4);
-          s[b] = mfma_bf16(__builtin_bit_cast(u16x8, kf), __builtin_bit_cast(u16x8, qf[k]), s[b]);
-        }
+        u32x4 kf = *reinterpret_cast<const u32x4*>(krow + 32 * k + 8 * g4);
+        s[b] = mfma_bf16(__builtin_bit_cast(u16x8, kf), __builtin_bit_cast(u16x8, qf[k]), s[b]);
       }
     }
     // ---- online softmax in FP32.  Statistics are kept on raw scores (the scale is > 0) and
@@ -362,42 +342,31 @@ __device__ void attn_unit(const AttnArgs& a, int unit, AttnSmem<TC, D>& sm) {
     for (int i = 0; i < ND; i++) o[i] *= alpha;
 
     // ---- O^T[d][query] += V^T[d][key] P^T[key][query]
-    if constexpr (C::F32) {
 #pragma unroll
-      for (int b = 0; b < NB; b++)
+    for (int b2 = 0; b2 < NB / 2; b2++) {
+      u32x4 pb;
 #pragma unroll
-        for (int t = 0; t < 4; t++) {
-          const float* vrow = Vs + (16 * b + 4 * g4 + t) * C::KLD;
-#pragma unroll
-          for (int i = 0; i < ND; i++) o[i] = mfma_f32(vrow[16 * i + qi], s[b][t], o[i]);
+      for (int t = 0; t < 4; t += 2) {
+        float p0 = s[2 * b2][t], p0n = s[2 * b2][t + 1];
+        float p1 = s[2 * b2 + 1][t], p1n = s[2 * b2 + 1][t + 1];
+        if (FP8 && tile_fp8) {
+          p0 *= vsc_s[32 * b2 + 4 * g4 + t];
+          p0n *= vsc_s[32 * b2 + 4 * g4 + t + 1];
+          p1 *= vsc_s[32 * b2 + 16 + 4 * g4 + t];
+          p1n *= vsc_s[32 * b2 + 16 + 4 * g4 + t + 1];
         }
-    } else {
+        pb[t / 2] = pack_bf16x2(p0, p0n);
+        pb[2 + t / 2] = pack_bf16x2(p1, p1n);
+      }
+      const int jp_lo = 16 * b2 + 2 * g4;
 #pragma unroll
-      for (int b2 = 0; b2 < NB / 2; b2++) {
-        u32x4 pb;
-#pragma unroll
-        for (int t = 0; t < 4; t += 2) {
-          float p0 = s[2 * b2][t], p0n = s[2 * b2][t + 1];
-          float p1 = s[2 * b2 + 1][t], p1n = s[2 * b2 + 1][t + 1];
-          if (FP8 && tile_fp8) {
-            p0 *= vsc_s[32 * b2 + 4 * g4 + t];
-            p0n *= vsc_s[32 * b2 + 4 * g4 + t + 1];
-            p1 *= vsc_s[32 * b2 + 16 + 4 * g4 + t];
-            p1n *= vsc_s[32 * b2 + 16 + 4 * g4 + t + 1];
-          }
-          pb[t / 2] = pack_bf16x2(p0, p0n);
-          pb[2 + t / 2] = pack_bf16x2(p1, p1n);
-        }
-        const int jp_lo = 16 * b2 + 2 * g4;
-#pragma unroll
-        for (int i = 0; i < ND; i++) {
-          const bf16_t* vrow = Vs + (16 * i + qi) * C::VTLD;
-          const int sw = 2 * (i & 7);
-          u32x2 lo = *reinterpret_cast<const u32x2*>(vrow + 2 * (jp_lo ^ sw));
-          u32x2 hi = *reinterpret_cast<const u32x2*>(vrow + 2 * ((jp_lo + 8) ^ sw));
-          u32x4 va = {lo[0], lo[1], hi[0], hi[1]};
-          o[i] = mfma_bf16(__builtin_bit_cast(u16x8, va), __builtin_bit_cast(u16x8, pb), o[i]);
-        }
+      for (int i = 0; i < ND; i++) {
+        const bf16_t* vrow = Vs + (16 * i + qi) * C::VTLD;
+        const int sw = 2 * (i & 7);
+        u32x2 lo = *reinterpret_cast<const u32x2*>(vrow + 2 * (jp_lo ^ sw));
+        u32x2 hi = *reinterpret_cast<const u32x2*>(vrow + 2 * ((jp_lo + 8) ^ sw));
+        u32x4 va = {lo[0], lo[1], hi[0], hi[1]};
+        o[i] = mfma_bf16(__builtin_bit_cast(u16x8, va), __builtin_bit_cast(u16x8, pb), o[i]);
       }
     }
   }
@@ -412,14 +381,10 @@ __device__ void attn_unit(const AttnArgs& a, int unit, AttnSmem<TC, D>& sm) {
 #pragma unroll
   for (int i = 0; i < ND; i++) {
     int d0 = 16 * i + 4 * g4;
-    if constexpr (C::F32) {
-      *reinterpret_cast<f32x4*>(out + d0) = o[i] * inv;
-    } else {
-      u32x2 pk;
-      pk[0] = (uint32_t)f2bf(o[i][0] * inv) | ((uint32_t)f2bf(o[i][1] * inv) << 16);
-      pk[1] = (uint32_t)f2bf(o[i][2] * inv) | ((uint32_t)f2bf(o[i][3] * inv) << 16);
-      *reinterpret_cast<u32x2*>(out + d0) = pk;
-    }
+    u32x2 pk;
+    pk[0] = (uint32_t)f2bf(o[i][0] * inv) | ((uint32_t)f2bf(o[i][1] * inv) << 16);
+    pk[1] = (uint32_t)f2bf(o[i][2] * inv) | ((uint32_t)f2bf(o[i][3] * inv) << 16);
+    *reinterpret_cast<u32x2*>(out + d0) = pk;
   }
 }
 
@@ -486,10 +451,7 @@ hipError_t attention(int cdt, int kvdt, int D, const AttnArgs& a, hipStream_t st
   }
   if (a.counter && a.persistent_wgs < 1) return hipErrorInvalidValue;
   if (a.G * a.Pmax > 64 || a.G < 1 || a.Pmax < 1) return hipErrorInvalidValue;
-  if (cdt == DT_F32) {
-    if (kvdt != DT_F32) return hipErrorInvalidValue;
-    return launch_kv<float, float>(D, a, st);
-  }
+  if (cdt == DT_F32) return kvdt == DT_F32 ? attention_f32(D, a, st) : hipErrorInvalidValue;
   if (kvdt == DT_BF16) return launch_kv<bf16_t, bf16_t>(D, a, st);
   if (kvdt == DT_FP8) return launch_kv<bf16_t, fp8_t>(D, a, st);
   return hipErrorInvalidValue;

@@ -30,12 +30,12 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "attention_lds.h"
 #include "common.h"
 #include "kernels.h"
 
 namespace kvop {
 
-typedef __attribute__((address_space(3))) void lds_void_t;
 typedef short v4i16_t __attribute__((ext_vector_type(4)));
 typedef int v2i32_t __attribute__((ext_vector_type(2)));
 
@@ -77,23 +77,6 @@ template <int CH> __device__ inline int swz_v8(int r) {
   else return ((r >> 2) & 1) | (((r >> 4) & 1) << 1);
 }
 
-template <int N> __device__ inline void vm_wait() {
-  static_assert(N >= 0 && N <= 63, "vmcnt range");
-  // gfx9 s_waitcnt: vmcnt in bits 3:0 and 15:14, expcnt 6:4 (7: no wait), lgkmcnt 11:8 (15: no wait)
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
-
-// waits until only `behind` (0 .. MAXB, uniform) tiles of OPS operations and ROWS row-number loads
-// are outstanding
-template <int MAXB, int OPS, int ROWS> __device__ inline void vm_wait_behind(int behind) {
-  if constexpr (MAXB < 0) {
-    vm_wait<0>();
-  } else {
-    if (behind >= MAXB) vm_wait<MAXB * OPS + ROWS>();
-    else vm_wait_behind<MAXB - 1, OPS, ROWS>(behind);
-  }
-}
-
 // Transposed LDS reads as inline assembly, each block with its own wait.  (The builtin form makes
 // the compiler wait for every direct-to-LDS load in flight (vmcnt(0)) before it, since it
 // cannot tell which LDS bytes the read touches.)  The caller reads V only from stages whose
@@ -125,22 +108,6 @@ __device__ inline void ds_read_tr8_x4(const uint32_t (&ad)[4], u32x2 (&y)[4]) {
 __device__ inline float scaled_minus(float m, float c, float mc) {
 #pragma clang fp contract(off)
   return m * c - mc;
-}
-
-// maximum over the four lanes l % 16 + {0, 16, 32, 48}: two register-to-register lane swaps (a
-// shuffle through LDS would add its latency twice to every softmax step)
-__device__ inline float max_over_groups(float x) {
-  const uint32_t u = __builtin_bit_cast(uint32_t, x);
-  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const float m = fmaxf(__builtin_bit_cast(float, (uint32_t)a[0]), __builtin_bit_cast(float, (uint32_t)a[1]));
-  const uint32_t v = __builtin_bit_cast(uint32_t, m);
-  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  return fmaxf(__builtin_bit_cast(float, (uint32_t)b[0]), __builtin_bit_cast(float, (uint32_t)b[1]));
-}
-
-// plain global load (global_load, not flat: a flat load also counts in lgkmcnt)
-template <typename T> __device__ inline T gload(const T* p) {
-  return *reinterpret_cast<const __attribute__((address_space(1))) T*>(reinterpret_cast<uintptr_t>(p));
 }
 
 template <typename TKV, int D, int KT, int NS, int KC, bool LISTS>

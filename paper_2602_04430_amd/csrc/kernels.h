@@ -69,8 +69,13 @@ struct AttnWork {
   int32_t own_pos0;
   int32_t pad_a;      // padded batching: keys of A iterated (>= n_a; keys past n_a are loaded,
                       // multiplied and masked); 0 = n_a.  Direct-load kernels only.
+  int32_t part0;      // FP32, items of several chunks: the first one's number among all such
+                      // items' chunks
 };
 
+// FP32 attention: keys per tile, and per chunk (chunks have softmax states of their own)
+constexpr int attn_f32_tile(int D) { return D == 32 ? 32 : 16; }
+constexpr int kAttnChunkKeys = 512;
 struct AttnArgs {
   const AttnWork* work;
   int n_work;
@@ -92,6 +97,8 @@ struct AttnArgs {
                        // many workgroups as fit on them at once
   int longest_keys;    // keys of the unit that iterates most of them, and of all work items
   int64_t total_keys;  // together: what the choice of stages goes by
+  float* part;         // FP32: room for the states of the chunks that items of several chunks have
+  int n_part;          // (null: one workgroup per item and kv head), and how many those are
   int decode;          // 1: a decoding step (one query position per item, no document B); the
                        // streaming decode kernel serves it where it supports the shape
 };
@@ -103,6 +110,8 @@ bool attention_decode_ok(int kvdt, int D, int G);
 hipError_t attention_decode(int kvdt, int D, const AttnArgs& a, hipStream_t st);
 // BF16 compute with a BF16 or FP8 cache, D in {64, 128}: tiles fetched by direct global->LDS
 // loads.  variant: 0 = 64-key tiles / 2 stages, 1 = 64 / 3, 2 = 32 / 3.
+hipError_t attention_f32(int D, const AttnArgs& a, hipStream_t st);
+bool attention_f32_splits(int D, const AttnArgs& a);
 hipError_t attention_dma(int kvdt, int D, int variant, const AttnArgs& a, hipStream_t st);
 // FP8 (E4M3) codes -> BF16 bits with the conversion the direct-load kernels use (n % 8 == 0)
 hipError_t fp8_widen(const uint8_t* codes, uint16_t* out, int n, hipStream_t st);
