@@ -363,7 +363,9 @@ kvop_status run_layer(kvop_model* m, int l, const LayerBufs& b, LayerPlan& lp, u
   // output buffer, free until the attention runs), then copy them to every item rotated at its
   // positions; the result equals the per-row path bit for bit
   const int e = m->esz();
-  bool shared = fuse_rope && lp.n_shared > 0;
+  // (FP32 rows are rotated by a launch of their own, which serves the same two cases)
+  const bool suffix_rows = fuse_rope || (dt == DT_F32 && n_kvblocks == 0 && !lp.ea_row_off);
+  bool shared = suffix_rows && lp.n_shared > 0;
   {
     int64_t covered = 0, periods = 0;
     for (int i = 0; i < lp.n_shared; i++) {
@@ -374,7 +376,7 @@ kvop_status run_layer(kvop_model* m, int l, const LayerBufs& b, LayerPlan& lp, u
     }
     if (covered != rows || periods * qc > (int64_t)rows * H * D) shared = false;
   }
-  const int qlast = fuse_rope && !shared && lp.q_last > 0 && rows % lp.q_last == 0 ? lp.q_last : 0;
+  const int qlast = suffix_rows && !shared && lp.q_last > 0 && rows % lp.q_last == 0 ? lp.q_last : 0;
   {
     ProfScope ps(PC_RMSNORM, st);
     if (shared) {
@@ -405,17 +407,24 @@ kvop_status run_layer(kvop_model* m, int l, const LayerBufs& b, LayerPlan& lp, u
       const int nq = rows / qlast;
       // keys and values of every row (output columns H D .. qc; keys rotated)
       GemmShape kv{rows, 2 * Hkv * D, d, d, d, qc};
-      const RopeEpi rk{lp.pos, m->cos_tab, m->sin_tab, D, Hkv * D, 0, nullptr, nullptr, 1};
-      HIPTRY(gemm(dt, dt, EPI_ROPE, gemm_pick_tile(dt, EPI_ROPE, kv), b.h,
-                  (const char*)W.wqkv + (int64_t)H * D * d * e, (char*)b.qkv + (int64_t)H * D * e, kv, st, &rk));
       // queries of the last row of every item (rows q_last - 1, 2 q_last - 1, ...)
       GemmShape qs{nq, H * D, d, (int64_t)qlast * d, d, (int64_t)qlast * qc};
       const int64_t r0 = qlast - 1;
-      const RopeEpi rq{lp.pos + r0, m->cos_tab, m->sin_tab, D, H * D, H * D,
-                       lp.alt_shift ? (char*)b.qalt + r0 * qc * e : nullptr, lp.alt_shift ? lp.alt_shift + r0 : nullptr,
-                       qlast};
-      HIPTRY(gemm(dt, dt, EPI_ROPE, gemm_pick_tile(dt, EPI_ROPE, qs), (const char*)b.h + r0 * d * e, W.wqkv,
-                  (char*)b.qkv + r0 * qc * e, qs, st, &rq));
+      if (dt == DT_F32) {
+        HIPTRY(gemm(dt, dt, EPI_STORE, gemm_pick_tile(dt, EPI_STORE, kv), b.h,
+                    (const char*)W.wqkv + (int64_t)H * D * d * e, (char*)b.qkv + (int64_t)H * D * e, kv, st));
+        HIPTRY(gemm(dt, dt, EPI_STORE, gemm_pick_tile(dt, EPI_STORE, qs), (const char*)b.h + r0 * d * e, W.wqkv,
+                    (char*)b.qkv + r0 * qc * e, qs, st));
+      } else {
+        const RopeEpi rk{lp.pos, m->cos_tab, m->sin_tab, D, Hkv * D, 0, nullptr, nullptr, 1};
+        HIPTRY(gemm(dt, dt, EPI_ROPE, gemm_pick_tile(dt, EPI_ROPE, kv), b.h,
+                    (const char*)W.wqkv + (int64_t)H * D * d * e, (char*)b.qkv + (int64_t)H * D * e, kv, st, &rk));
+        const RopeEpi rq{lp.pos + r0, m->cos_tab, m->sin_tab, D, H * D, H * D,
+                         lp.alt_shift ? (char*)b.qalt + r0 * qc * e : nullptr, lp.alt_shift ? lp.alt_shift + r0 : nullptr,
+                         qlast};
+        HIPTRY(gemm(dt, dt, EPI_ROPE, gemm_pick_tile(dt, EPI_ROPE, qs), (const char*)b.h + r0 * d * e, W.wqkv,
+                    (char*)b.qkv + r0 * qc * e, qs, st, &rq));
+      }
     } else if (fuse_rope) {
       const RopeEpi re{lp.pos, m->cos_tab, m->sin_tab, D, (H + Hkv) * D, H * D, lp.alt_shift ? b.qalt : nullptr,
                        lp.alt_shift};
@@ -442,12 +451,20 @@ kvop_status run_layer(kvop_model* m, int l, const LayerBufs& b, LayerPlan& lp, u
       const LayerPlan::SharedBlock& sb = lp.shared[i];
       if (sb.rows == 0) continue;
       const int64_t r0 = sb.row0;
-      HIPTRY(rope_broadcast((char*)b.attn + off * qc * e, sb.period, (char*)b.qkv + r0 * qc * e, qc, sb.rows, qc,
+      HIPTRY(rope_broadcast(dt, (char*)b.attn + off * qc * e, sb.period, (char*)b.qkv + r0 * qc * e, qc, sb.rows, qc,
                             (H + Hkv) * D, H * D, D, lp.pos + r0, m->cos_tab, m->sin_tab,
                             lp.alt_shift ? (char*)b.qalt + r0 * qc * e : nullptr,
                             lp.alt_shift ? lp.alt_shift + r0 : nullptr, st));
       off += sb.period;
     }
+  } else if (!fuse_rope && qlast) {
+    ProfScope ps(PC_ROPE_KV, st);
+    const int64_t r0 = qlast - 1;
+    HIPTRY(rope_qk(dt, (char*)b.qkv + (int64_t)H * D * e, qc, rows, 0, Hkv, D, lp.pos, m->cos_tab, m->sin_tab, nullptr,
+                   nullptr, st));
+    HIPTRY(rope_qk(dt, (char*)b.qkv + r0 * qc * e, (int64_t)qlast * qc, rows / qlast, H, 0, D, lp.pos + r0, m->cos_tab,
+                   m->sin_tab, lp.alt_shift ? (char*)b.qalt + r0 * qc * e : nullptr,
+                   lp.alt_shift ? lp.alt_shift + r0 : nullptr, st, qlast));
   } else if (!fuse_rope) {
     ProfScope ps(PC_ROPE_KV, st);
     HIPTRY(rope_qk(dt, b.qkv, qc, rows, H, Hkv, D, lp.pos, m->cos_tab, m->sin_tab, lp.alt_shift ? b.qalt : nullptr,
@@ -2165,7 +2182,7 @@ kvop_status kvop_debug_gemm_rope(int32_t tile, const void* A, const void* B, voi
   } else {
     // the plain product, then the separate pass (each element read and written by one thread)
     HIPTRY(gemm(DT_BF16, DT_BF16, EPI_STORE, tile, A, B, Cm, s, st));
-    HIPTRY(rope_broadcast(Cm, std::max(M, 1), Cm, N, M, N, rot_cols, 0, head_dim, pos_dev, cos_dev, sin_dev, nullptr,
+    HIPTRY(rope_broadcast(DT_BF16, Cm, std::max(M, 1), Cm, N, M, N, rot_cols, 0, head_dim, pos_dev, cos_dev, sin_dev, nullptr,
                           nullptr, st));
   }
   return KVOP_OK;

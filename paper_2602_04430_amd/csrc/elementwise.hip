@@ -146,7 +146,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void rope_kernel(T* __restrict__ qkv, int64_t ld, int n_rows, int n_heads, int H,
                                                    int D, const int32_t* __restrict__ pos,
                                                    const float* __restrict__ cos_t, const float* __restrict__ sin_t,
-                                                   T* __restrict__ q_alt, const int32_t* __restrict__ shift) {
+                                                   T* __restrict__ q_alt, const int32_t* __restrict__ shift, int step) {
   const int half = D / 2, groups = half / 8;
   const int per_row = n_heads * groups;
   const int gid = blockIdx.x * blockDim.x + threadIdx.x;
@@ -157,11 +157,11 @@ __global__ __launch_bounds__(256) void rope_kernel(T* __restrict__ qkv, int64_t 
   float x1[8], x2[8], c[8], s[8], y1[8], y2[8];
   Vec8<T>::load(v + i, x1);
   Vec8<T>::load(v + i + half, x2);
-  const int p = pos[row];
+  const int p = pos[(int64_t)row * step];
   Vec8<float>::load(cos_t + (int64_t)p * half + i, c);
   Vec8<float>::load(sin_t + (int64_t)p * half + i, s);
-  if (q_alt && head < H && shift[row] >= 0) {
-    const int p2 = p - shift[row];
+  if (q_alt && head < H && shift[(int64_t)row * step] >= 0) {
+    const int p2 = p - shift[(int64_t)row * step];
     float c2[8], s2[8];
     Vec8<float>::load(cos_t + (int64_t)p2 * half + i, c2);
     Vec8<float>::load(sin_t + (int64_t)p2 * half + i, s2);
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(256) void rope_kernel(T* __restrict__ qkv, int64_t 
 
 hipError_t rope_qk(int dt, void* qkv, int64_t ld, int n_rows, int H, int Hkv, int D, const int32_t* pos,
                    const float* cos_tab, const float* sin_tab, void* q_alt, const int32_t* alt_shift,
-                   hipStream_t st) {
+                   hipStream_t st, int step) {
   if (n_rows <= 0) return hipSuccess;
   if ((D / 2) % 8 || ld % 8) return hipErrorInvalidValue;
   const int64_t total = (int64_t)n_rows * (H + Hkv) * (D / 16);
@@ -187,24 +187,25 @@ hipError_t rope_qk(int dt, void* qkv, int64_t ld, int n_rows, int H, int Hkv, in
   dim3 grid((unsigned)((total + 255) / 256));
   if (dt == DT_F32)
     hipLaunchKernelGGL(rope_kernel<float>, grid, dim3(256), 0, st, (float*)qkv, ld, n_rows, H + Hkv, H, D, pos, cos_tab,
-                       sin_tab, (float*)q_alt, alt_shift);
+                       sin_tab, (float*)q_alt, alt_shift, step);
   else
     hipLaunchKernelGGL(rope_kernel<bf16_t>, grid, dim3(256), 0, st, (bf16_t*)qkv, ld, n_rows, H + Hkv, H, D, pos,
-                       cos_tab, sin_tab, (bf16_t*)q_alt, alt_shift);
+                       cos_tab, sin_tab, (bf16_t*)q_alt, alt_shift, step);
   return hipGetLastError();
 }
 
 // Rows of a batch that repeat every src_rows rows before the rotation (every item's rows are
 // the same suffix at layer 0): each row is copied from its source row r mod src_rows, the
 // query and key heads (columns below rot_cols) rotated at the row's own position with the
-// arithmetic of the projection's rotary epilogue, so the rows equal what that epilogue writes
-// bit for bit; joins also get the queries rotated at position - shift into q_alt.
-__global__ __launch_bounds__(256) void rope_broadcast_kernel(const bf16_t* __restrict__ src, int src_rows,
-                                                             bf16_t* __restrict__ dst, int64_t ld, int n_rows,
+// arithmetic of the projection's rotary epilogue (BF16) or of rope_kernel (FP32), so the rows
+// equal what those write bit for bit; joins also get the queries rotated at position - shift into q_alt.
+template <typename T>
+__global__ __launch_bounds__(256) void rope_broadcast_kernel(const T* __restrict__ src, int src_rows,
+                                                             T* __restrict__ dst, int64_t ld, int n_rows,
                                                              int n_cols, int rot_cols, int q_cols, int D,
                                                              const int32_t* __restrict__ pos,
                                                              const float* __restrict__ cos_t,
-                                                             const float* __restrict__ sin_t, bf16_t* __restrict__ q_alt,
+                                                             const float* __restrict__ sin_t, T* __restrict__ q_alt,
                                                              const int32_t* __restrict__ shift) {
   const int half = D / 2, gph = half / 8;
   const int per_row = (n_cols / D) * gph;
@@ -212,45 +213,47 @@ __global__ __launch_bounds__(256) void rope_broadcast_kernel(const bf16_t* __res
   if (gid >= (int64_t)per_row * n_rows) return;
   const int row = (int)(gid / per_row), rem = (int)(gid - (int64_t)row * per_row);
   const int hh = rem / gph, i = (rem - hh * gph) * 8, col = hh * D + i;
-  const bf16_t* sp = src + (int64_t)(row % src_rows) * ld + col;
-  const u32x4 r1 = *reinterpret_cast<const u32x4*>(sp), r2 = *reinterpret_cast<const u32x4*>(sp + half);
-  bf16_t* o = dst + (int64_t)row * ld + col;
+  const T* sp = src + (int64_t)(row % src_rows) * ld + col;
+  T* o = dst + (int64_t)row * ld + col;
   if (col >= rot_cols) {
-    *reinterpret_cast<u32x4*>(o) = r1;
-    *reinterpret_cast<u32x4*>(o + half) = r2;
+    constexpr int NV = 8 * (int)sizeof(T) / 16;
+#pragma unroll
+    for (int q = 0; q < NV; q++) {
+      reinterpret_cast<u32x4*>(o)[q] = reinterpret_cast<const u32x4*>(sp)[q];
+      reinterpret_cast<u32x4*>(o + half)[q] = reinterpret_cast<const u32x4*>(sp + half)[q];
+    }
     return;
   }
   float x1[8], x2[8];
-#pragma unroll
-  for (int q = 0; q < 4; q++) {
-    x1[2 * q] = bf2f((bf16_t)(r1[q] & 0xffffu));
-    x1[2 * q + 1] = bf2f((bf16_t)(r1[q] >> 16));
-    x2[2 * q] = bf2f((bf16_t)(r2[q] & 0xffffu));
-    x2[2 * q + 1] = bf2f((bf16_t)(r2[q] >> 16));
-  }
-  auto rotate_store = [&](int p, bf16_t* d) {
+  Vec8<T>::load(sp, x1);
+  Vec8<T>::load(sp + half, x2);
+  auto rotate_store = [&](int p, T* d) {
     float c[8], s[8], y1[8], y2[8];
     Vec8<float>::load(cos_t + (int64_t)p * half + i, c);
     Vec8<float>::load(sin_t + (int64_t)p * half + i, s);
 #pragma unroll
     for (int e = 0; e < 8; e++) rope_pair(x1[e], x2[e], c[e], s[e], y1[e], y2[e]);
-    Vec8<bf16_t>::store(d, y1);
-    Vec8<bf16_t>::store(d + half, y2);
+    Vec8<T>::store(d, y1);
+    Vec8<T>::store(d + half, y2);
   };
   const int p = pos[row];
   if (q_alt && col < q_cols && shift[row] >= 0) rotate_store(p - shift[row], q_alt + (int64_t)row * ld + col);
   rotate_store(p, o);
 }
 
-hipError_t rope_broadcast(const void* src, int src_rows, void* dst, int64_t ld, int n_rows, int n_cols, int rot_cols,
+hipError_t rope_broadcast(int dt, const void* src, int src_rows, void* dst, int64_t ld, int n_rows, int n_cols, int rot_cols,
                           int q_cols, int D, const int32_t* pos, const float* cos_tab, const float* sin_tab, void* q_alt,
                           const int32_t* shift, hipStream_t st) {
   if (n_rows <= 0) return hipSuccess;
   if (src_rows < 1 || D % 16 || n_cols % D || ld % 8 || (q_alt && !shift)) return hipErrorInvalidValue;
   const int64_t total = (int64_t)n_rows * (n_cols / D) * (D / 16);
-  hipLaunchKernelGGL(rope_broadcast_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
-                     (const bf16_t*)src, src_rows, (bf16_t*)dst, ld, n_rows, n_cols, rot_cols, q_cols, D, pos, cos_tab,
-                     sin_tab, (bf16_t*)q_alt, shift);
+  const dim3 grid((unsigned)((total + 255) / 256));
+  if (dt == DT_F32)
+    hipLaunchKernelGGL(rope_broadcast_kernel<float>, grid, dim3(256), 0, st, (const float*)src, src_rows, (float*)dst, ld,
+                       n_rows, n_cols, rot_cols, q_cols, D, pos, cos_tab, sin_tab, (float*)q_alt, shift);
+  else
+    hipLaunchKernelGGL(rope_broadcast_kernel<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)src, src_rows, (bf16_t*)dst,
+                       ld, n_rows, n_cols, rot_cols, q_cols, D, pos, cos_tab, sin_tab, (bf16_t*)q_alt, shift);
   return hipGetLastError();
 }
 

@@ -157,12 +157,13 @@ hipError_t rmsnorm_rows(int dt, const float* x, int64_t ldx, const float* g, int
 // rot_cols rotated at pos[r] as the projection's rotary epilogue rotates them, the rest
 // copied; joins: query columns (below q_cols) also rotated at pos[r] - shift[r] into q_alt
 // where shift[r] >= 0
-hipError_t rope_broadcast(const void* src, int src_rows, void* dst, int64_t ld, int n_rows, int n_cols, int rot_cols,
+hipError_t rope_broadcast(int dt, const void* src, int src_rows, void* dst, int64_t ld, int n_rows, int n_cols, int rot_cols,
                           int q_cols, int D, const int32_t* pos, const float* cos_tab, const float* sin_tab, void* q_alt,
                           const int32_t* shift, hipStream_t st);
+// (row r's position is pos[r step], its shift alt_shift[r step])
 hipError_t rope_qk(int dt, void* qkv, int64_t ld, int n_rows, int H, int Hkv, int D, const int32_t* pos,
                    const float* cos_tab, const float* sin_tab, void* q_alt, const int32_t* alt_shift,
-                   hipStream_t st);
+                   hipStream_t st, int step = 1);
 // kv_build: rotate q (in place) and k of document rows and write k, v into the cache
 struct KvBlock {      // 16 consecutive rows of one document
   int64_t off;        // document region byte offset

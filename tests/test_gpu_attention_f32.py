@@ -1,7 +1,8 @@
 """FP32 attention: the keys of long items go to several workgroups where few items are long.  The
 split changes no bits: documents alone (split) and among many (whole), at the edges of tiles (16
 and 32 keys) and of chunks (512 keys), through lists and joins, at every head dimension, and
-suffixes of one and of several blocks of query rows."""
+suffixes of one and of several blocks of query rows.  (Among many, the first layer's projection is
+shared by all items; alone it is not.)"""
 import numpy as np
 import pytest
 
