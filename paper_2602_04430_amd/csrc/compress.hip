@@ -461,65 +461,221 @@ __device__ inline uint32_t order_key(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// exclusive prefix sum over the block (256 threads); returns the block total in *total
-__device__ inline int block_scan(int v, int* total, int* wsum) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int x = v;
+// inclusive prefix sum over a wavefront
+__device__ inline int wave_scan(int v) {
+  const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
+    const int y = __shfl_up(v, o, 64);
+    if (lane >= o) v += y;
   }
-  __syncthreads();
-  if (lane == 63) wsum[w] = x;
-  __syncthreads();
-  int before = 0;
-  for (int k = 0; k < w; k++) before += wsum[k];
-  *total = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-  return before + x - v;
+  return v;
+}
+__device__ inline int bits_below(uint64_t mask) {   // set bits of mask below this lane's
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
 }
 
+// sum over a wavefront, the same in every lane's view (register-to-register steps: a shuffle goes
+// through LDS)
+template <int CTRL, int ROWS> __device__ inline int dpp_add(int v) {
+  return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);
+}
+__device__ inline int wave_total(int v) {
+  v = dpp_add<0x111, 0xf>(v);   // row_shr 1, 2, 4, 8: lane 15 of each row of 16 holds the row's sum
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  v = dpp_add<0x118, 0xf>(v);
+  v = dpp_add<0x142, 0xa>(v);   // row_bcast 15 into rows 1 and 3, row_bcast 31 into rows 2 and 3
+  v = dpp_add<0x143, 0xc>(v);
+  return __builtin_amdgcn_readlane(v, 63);
+}
+
+// NW wavefronts per document: the threshold bit by bit from the first bit in which the document's
+// keys differ, ending as soon as exactly k keys lie at or above it, then one pass that writes
+// the rows in order.  The keys stay in registers, 16 a lane; only documents over 4096 rows are read
+// again in each pass.
+// Bound by the chain of passes and, over many documents, by instructions.  So a document that fits
+// one wavefront's registers gets one wavefront (no barriers, nothing computed four times over),
+// a longer one a workgroup.  4096 documents of 512 rows in the median (2.7 M scores): 134 us with 33
+// passes over memory and block reductions, 42 with a workgroup for every document, 41 with a
+// wavefront for every document, now 23.
+constexpr int kSelRegs = 16, kSelShort = kSelRegs * 64;
+template <int NW>
+__device__ __forceinline__ void select_rows(const float* __restrict__ scores, int L, int k, int32_t* __restrict__ out, int w) {
+  constexpr int REGS = kSelRegs, ROW = 64 * NW, kSelRows = REGS * ROW;
+  static_assert(REGS * NW <= 64, "a lane per register and wavefront in the prefix sums");
+  __shared__ uint32_t red[2][NW];
+  __shared__ int cnt[2][NW], tab[2][64];
+  const int lane = threadIdx.x & 63, tid = 64 * w + lane;
+  const bool many = L > kSelRows;
+  uint32_t key[REGS];
+  // f(register) for the registers that hold rows of the segment at c0, four (a branch) at a time
+  auto regs = [&](int c0, auto f) __attribute__((always_inline)) {
+#pragma unroll
+    for (int g = 0; g < REGS; g += 4)
+      if (c0 + g * ROW < L) {
+#pragma unroll
+        for (int j = g; j < g + 4; j++) f(j);
+      }
+  };
+  auto load = [&](int c0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < REGS; j++) key[j] = 0u;   // below every threshold tried
+    // all loads first: a key formed beside its load would wait for it before the next load starts
+    regs(c0, [&](int j) __attribute__((always_inline)) {
+      key[j] = __builtin_bit_cast(uint32_t, scores[min(c0 + j * ROW + tid, L - 1)]);
+    });
+    __builtin_amdgcn_sched_barrier(0);
+    regs(c0, [&](int j) __attribute__((always_inline)) {
+      key[j] = c0 + j * ROW + tid < L ? order_key(__builtin_bit_cast(float, key[j])) : 0u;
+    });
+  };
+  // f(row, register) over the document's rows, a whole wavefront at a time
+  auto each = [&](auto f) __attribute__((always_inline)) {
+    for (int c0 = 0; c0 < L; c0 += kSelRows) {
+      if (many) load(c0);
+      regs(c0, [&](int j) __attribute__((always_inline)) { f(c0 + j * ROW + tid, j); });
+    }
+  };
+  load(0);
+
+  // ---- the bits that all keys share
+  uint32_t all = ~0u, any = 0u;
+  each([&](int i, int j) __attribute__((always_inline)) {
+    if (i < L) {
+      all &= key[j];
+      any |= key[j];
+    }
+  });
+#pragma unroll
+  for (int o = 32; o; o >>= 1) {
+    all &= (uint32_t)__shfl_xor((int)all, o, 64);
+    any |= (uint32_t)__shfl_xor((int)any, o, 64);
+  }
+  if constexpr (NW > 1) {
+    if (lane == 0) {
+      red[0][w] = all;
+      red[1][w] = any;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NW; q++) {
+      all &= red[0][q];
+      any |= red[1][q];
+    }
+  }
+  all = __builtin_amdgcn_readfirstlane(all);
+  any = __builtin_amdgcn_readfirstlane(any);
+
+  // ---- largest t with #(key >= t) >= k
+  int par = 0;
+  auto total = [&](int c) __attribute__((always_inline)) {   // of the lanes' counts
+    c = wave_total(c);
+    if constexpr (NW > 1) {
+      if (lane == 0) cnt[par][w] = c;
+      __syncthreads();
+      c = 0;
+#pragma unroll
+      for (int q = 0; q < NW; q++) c += cnt[par][q];
+      par ^= 1;
+    }
+    return __builtin_amdgcn_readfirstlane(c);
+  };
+  const int top = all == any ? -1 : 31 - __builtin_clz(all ^ any);
+  uint32_t t = top < 0 ? all : all & ~((2u << top) - 1u);
+  bool exact = false;
+  for (int bit = top; bit >= 0 && !exact; bit--) {
+    const uint32_t cand = t | (1u << bit);
+    int c = 0;
+    each([&](int, int j) __attribute__((always_inline)) { c += key[j] >= cand ? 1 : 0; });
+    c = total(c);
+    if (c >= k) t = cand;
+    exact = c == k;
+  }
+  int need = 0;   // rows equal to t still to take, where not all of them are
+  if (!exact) {
+    int c = 0;
+    each([&](int i, int j) __attribute__((always_inline)) { c += i < L && key[j] > t ? 1 : 0; });
+    need = k - total(c);
+  }
+
+  // ---- rows in order: a register's rows of all wavefronts come before the next register's
+  // lane j NW + w: the sum over the registers and wavefronts before (j, w), from each one's count
+  int eq_before = 0, out_before = 0;
+  auto prefix = [&](int v, int* before, int which) __attribute__((always_inline)) {
+    if constexpr (NW > 1) {
+      __syncthreads();
+      v = tab[which][lane];
+    }
+    const int inc = wave_scan(v), base = *before + inc - v;
+    *before += __builtin_amdgcn_readlane(inc, 63);
+    return base;
+  };
+  auto put = [&](int& v, int j, int c, int which) __attribute__((always_inline)) {
+    if constexpr (NW > 1) {
+      if (lane == 0) tab[which][j * NW + w] = c;
+    } else {
+      v = lane == j ? c : v;
+    }
+  };
+  for (int c0 = 0; c0 < L; c0 += kSelRows) {
+    if (many) load(c0);
+    if (NW > 1) {
+      if (tid < 64) tab[0][tid] = tab[1][tid] = 0;   // registers past the document's end
+      __syncthreads();
+    }
+    int eq_base = 0;
+    if (!exact) {
+      int v = 0;
+      regs(c0, [&](int j) __attribute__((always_inline)) {
+        put(v, j, __popcll(__ballot(c0 + j * ROW + tid < L && key[j] == t)), 0);
+      });
+      eq_base = prefix(v, &eq_before, 0);
+    }
+    auto taken = [&](int j) __attribute__((always_inline)) {
+      const bool in = c0 + j * ROW + tid < L;
+      if (exact) return in && key[j] >= t;
+      const bool eq = in && key[j] == t;
+      const int rank = __builtin_amdgcn_readlane(eq_base, j * NW + w) + bits_below(__ballot(eq));
+      return in && (key[j] > t || (eq && rank < need));
+    };
+    int v = 0;
+    regs(c0, [&](int j) __attribute__((always_inline)) { put(v, j, __popcll(__ballot(taken(j))), 1); });
+    const int base = prefix(v, &out_before, 1);
+    regs(c0, [&](int j) __attribute__((always_inline)) {
+      const bool tk = taken(j);
+      const int pos = __builtin_amdgcn_readlane(base, j * NW + w) + bits_below(__ballot(tk));
+      if (tk) out[pos] = c0 + j * ROW + tid;
+    });
+    if (NW > 1 && many) __syncthreads();
+  }
+}
+
+// order: the n_long documents of more than kSelShort rows, a workgroup each, then the others, a
+// wavefront each
 __global__ __launch_bounds__(kEaThreads) void ea_select_kernel(const float* __restrict__ scores,
                                                                const int64_t* __restrict__ doc_off,
                                                                const int32_t* __restrict__ kcount,
                                                                const int64_t* __restrict__ out_off,
+                                                               const int32_t* __restrict__ order, int n_docs, int n_long,
                                                                int32_t* __restrict__ idx) {
-  __shared__ int wsum[4];
-  __shared__ float red[4];
-  const int d = blockIdx.x, tid = threadIdx.x;
+  constexpr int NW = kEaThreads / 64;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), b = blockIdx.x;
+  const bool is_long = b < n_long;
+  const int at = is_long ? b : n_long + (b - n_long) * NW + w;
+  if (at >= n_docs) return;
+  const int d = order[at];
   const int64_t s0 = doc_off[d];
   const int L = (int)(doc_off[d + 1] - s0), k = kcount[d];
   int32_t* out = idx + out_off[d];
   if (k >= L) {
-    for (int i = tid; i < L; i += kEaThreads) out[i] = i;
+    const int tid = is_long ? (int)threadIdx.x : (int)(threadIdx.x & 63), step = is_long ? kEaThreads : 64;
+    for (int i = tid; i < L; i += step) out[i] = i;
     return;
   }
-  // largest t with #(key >= t) >= k, bit by bit from the top
-  uint32_t t = 0;
-  for (int bit = 31; bit >= 0; bit--) {
-    const uint32_t cand = t | (1u << bit);
-    int c = 0;
-    for (int i = tid; i < L; i += kEaThreads) c += order_key(scores[s0 + i]) >= cand ? 1 : 0;
-    if ((int)block_sum((float)c, red) >= k) t = cand;  // counts stay below 2^24: exact in float
-  }
-  int gt = 0;
-  for (int i = tid; i < L; i += kEaThreads) gt += order_key(scores[s0 + i]) > t ? 1 : 0;
-  const int need = k - (int)block_sum((float)gt, red);  // rows equal to t still to take, >= 1
-  int eq_before = 0, out_before = 0;
-  for (int c0 = 0; c0 < L; c0 += kEaThreads) {
-    const int i = c0 + tid;
-    const uint32_t key = i < L ? order_key(scores[s0 + i]) : 0u;
-    const int eq = (i < L && key == t) ? 1 : 0;
-    int eq_tot;
-    const int eq_rank = eq_before + block_scan(eq, &eq_tot, wsum);
-    const int take = (i < L && (key > t || (eq && eq_rank < need))) ? 1 : 0;
-    int take_tot;
-    const int pos = out_before + block_scan(take, &take_tot, wsum);
-    if (take) out[pos] = i;
-    eq_before += eq_tot;
-    out_before += take_tot;
-    __syncthreads();
-  }
+  if (k <= 0) return;
+  if (is_long) select_rows<NW>(scores + s0, L, k, out, w);
+  else select_rows<1>(scores + s0, L, k, out, 0);
 }
 
 template <typename T, int D>
@@ -565,10 +721,14 @@ hipError_t ea_finish(const float* acc, int Hkv, int rows, float* out, hipStream_
 }
 
 hipError_t ea_select(const float* scores, const int64_t* doc_off, const int32_t* kcount, const int64_t* out_off,
-                     int n_docs, int32_t* idx, hipStream_t st) {
+                     const int32_t* order, int n_docs, int n_long, int32_t* idx, hipStream_t st) {
   if (n_docs <= 0) return hipSuccess;
-  hipLaunchKernelGGL(ea_select_kernel, dim3(n_docs), dim3(kEaThreads), 0, st, scores, doc_off, kcount, out_off, idx);
+  constexpr int NW = kEaThreads / 64;
+  hipLaunchKernelGGL(ea_select_kernel, dim3(n_long + (n_docs - n_long + NW - 1) / NW), dim3(kEaThreads), 0, st, scores,
+                     doc_off, kcount, out_off, order, n_docs, n_long, idx);
   return hipGetLastError();
 }
+
+int ea_select_short() { return kSelShort; }
 
 }  // namespace kvop

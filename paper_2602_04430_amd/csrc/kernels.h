@@ -136,9 +136,11 @@ hipError_t ea_zero(float* p, int64_t n, hipStream_t st);
 // out[row] = sum over kv heads of acc[row][g]
 hipError_t ea_finish(const float* acc, int Hkv, int rows, float* out, hipStream_t st);
 // per document d (scores rows doc_off[d] .. doc_off[d+1]): the kcount[d] highest scores, equal
-// scores lower row first, ascending document-relative rows written at idx + out_off[d]
+// scores lower row first, ascending document-relative rows written at idx + out_off[d].  order lists
+// the documents, first the n_long ones of more than ea_select_short() rows.
 hipError_t ea_select(const float* scores, const int64_t* doc_off, const int32_t* kcount, const int64_t* out_off,
-                     int n_docs, int32_t* idx, hipStream_t st);
+                     const int32_t* order, int n_docs, int n_long, int32_t* idx, hipStream_t st);
+int ea_select_short();
 
 // ---------------------------------------------------------------- elementwise / small kernels
 // x[row] = embed[tok[row]] (embed in `dt`), FP32 output; ids clamped to [0, V)

@@ -35,3 +35,36 @@ def test_scores_at_tile_edges(device, compute, D):
         ref = oc.ea_scores(m, docs.doc(i), 7)
         np.testing.assert_allclose(got[docs.offsets[i]:docs.offsets[i + 1]], ref, rtol=rtol, atol=1e-6,
                                    err_msg=f"document {i} L {L}")
+
+
+def test_select_at_register_and_segment_edges(device):
+    """Selection against the oracle's top-k of the same FP32 values: lengths at the edges of a wavefront,
+    a workgroup, the rows that one wavefront (1024) and one workgroup (4096) keep in registers, scores that differ in every bit or in one,
+    all equal, signed zeros, infinities and the type's extremes."""
+    import torch
+
+    from paper_2602_04430_amd import kvop as K
+    lengths = np.array([2, 63, 64, 65, 255, 256, 257, 511, 513, 1023, 1024, 1025, 4095, 4096, 4097, 8192, 8193], np.int64)
+    rng = np.random.default_rng(9)
+    eng = Engine(synth.ModelShape(n_layers=1, d_model=128, n_heads=4, n_kv_heads=2, head_dim=64, d_ffn=128, vocab=256),
+                 synth.make_weights(synth.ModelShape(n_layers=1, d_model=128, n_heads=4, n_kv_heads=2, head_dim=64,
+                                                     d_ffn=128, vocab=256), 1), "f32", "f32", pool_bytes=1 << 24)
+    n, offs = int(lengths.sum()), np.concatenate([[0], np.cumsum(lengths)])
+    big = np.finfo(np.float32).max
+    kinds = {"distinct": rng.standard_normal(n).astype(np.float32),
+             "one bit": np.where(rng.random(n) < 0.5, np.float32(1.0), np.nextafter(np.float32(1.0), np.float32(2.0))),
+             "equal": np.full(n, 0.25, np.float32),
+             "extremes": rng.choice(np.array([0.0, big, -big, np.inf, -np.inf, 1e-45], np.float32), n)}
+    for name, sc in kinds.items():
+        dsc = torch.from_numpy(sc.astype(np.float32)).cuda()
+        for r in (0.99, 0.5, 0.03):
+            ks = [synth.retained_count(r, int(L)) for L in lengths]
+            idx = torch.full((sum(ks) + 1,), -1, dtype=torch.int32, device="cuda")
+            io = K.kvop_ea_select(eng.pool, dsc, offs, r, idx)
+            torch.cuda.synchronize()
+            got = idx.cpu().numpy()
+            assert got[-1] == -1
+            for i, L in enumerate(lengths):
+                want = oc.ea_select(sc[offs[i]:offs[i + 1]].astype(np.float64), ks[i])
+                np.testing.assert_array_equal(got[io[i]:io[i + 1]], want, err_msg=f"{name} r {r} L {L}")
+    eng.close()
