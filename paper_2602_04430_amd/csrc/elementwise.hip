@@ -675,25 +675,31 @@ hipError_t head_map(int dt, const float* x, int64_t ldx, int n_items, int d, con
 }
 
 // ---------------------------------------------------------------- validation
+// A workgroup per list, four pairs of neighbours per thread in flight: a wavefront per list with one
+// pair at a time waited for memory 64 times for a list of 4096 rows (24 us), now 4.7.
 __global__ __launch_bounds__(256) void validate_kernel(const int32_t* __restrict__ idx,
-                                                       const ListCheck* __restrict__ lists, int n_lists,
-                                                       int* __restrict__ bad) {
-  int li = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (li >= n_lists) return;
-  ListCheck l = lists[li];
-  int ok = 1;
-  for (int i = lane; i < l.n; i += 64) {
-    int v = idx[l.off + i];
-    if (v < 0 || v >= l.L) ok = 0;
-    if (i > 0 && idx[l.off + i - 1] >= v) ok = 0;
+                                                       const ListCheck* __restrict__ lists, int* __restrict__ bad) {
+  const ListCheck l = lists[blockIdx.x];
+  int wrong = 0;
+  for (int i0 = threadIdx.x; i0 < l.n; i0 += 1024) {
+    int v[4], before[4];
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      const int i = min(i0 + 256 * u, l.n - 1);
+      v[u] = idx[l.off + i];
+      before[u] = i > 0 ? idx[l.off + i - 1] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; u++)
+      if (v[u] < 0 || v[u] >= l.L || before[u] >= v[u]) wrong = 1;
   }
-  ok = __all(ok);
-  if (lane == 0 && !ok) atomicAdd(bad, 1);
+  wrong = __syncthreads_or(wrong);
+  if (threadIdx.x == 0 && wrong) atomicAdd(bad, 1);
 }
 
 hipError_t validate_lists(const int32_t* idx, const ListCheck* lists, int n_lists, int* bad, hipStream_t st) {
   if (n_lists <= 0) return hipSuccess;
-  hipLaunchKernelGGL(validate_kernel, dim3((n_lists + 3) / 4), dim3(256), 0, st, idx, lists, n_lists, bad);
+  hipLaunchKernelGGL(validate_kernel, dim3(n_lists), dim3(256), 0, st, idx, lists, bad);
   return hipGetLastError();
 }
 
