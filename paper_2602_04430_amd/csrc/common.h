@@ -101,16 +101,46 @@ __device__ inline float as_f32(uint32_t v) { return __builtin_bit_cast(float, v)
 
 __device__ inline float silu(float x) { return x / (1.0f + __expf(-x)); }
 
-// wavefront reductions (64 lanes)
+// Wavefront reductions (64 lanes), by register-to-register lane moves: a shuffle goes through LDS, six
+// of them one after the other.  Lanes 32, 16, 8, 4, 2 and 1 apart are combined in this order (a
+// rotation of a row of 16 by 4 reaches the lane 4 across or the one 12 across, which is equal
+// by then), so the bits are those of the shuffles.  (x.own, x.across): a lane pair's two values
+// in either order.
+struct LanePair {
+  float own, across;
+};
+__device__ inline LanePair lanes_32(float v) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, v);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return {__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1])};
+}
+__device__ inline LanePair lanes_16(float v) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, v);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return {__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1])};
+}
+template <int CTRL> __device__ inline LanePair lanes_dpp(float v) {
+  return {v, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true))};
+}
+template <typename F> __device__ __forceinline__ float wave_reduce(float v, F f) {
+  LanePair p = lanes_32(v);
+  v = f(p.own, p.across);
+  p = lanes_16(v);
+  v = f(p.own, p.across);
+  p = lanes_dpp<0x128>(v);   // row_ror 8
+  v = f(p.own, p.across);
+  p = lanes_dpp<0x124>(v);   // row_ror 4
+  v = f(p.own, p.across);
+  p = lanes_dpp<0x4e>(v);    // quad_perm 2 3 0 1
+  v = f(p.own, p.across);
+  p = lanes_dpp<0xb1>(v);    // quad_perm 1 0 3 2
+  return f(p.own, p.across);
+}
 __device__ inline float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  return wave_reduce(v, [](float a, float b) __attribute__((always_inline)) { return a + b; });
 }
 __device__ inline float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
+  return wave_reduce(v, [](float a, float b) __attribute__((always_inline)) { return fmaxf(a, b); });
 }
 
 // MFMA wrappers.  16x16 output blocks; lane l holds C[4*(l/16) + r][l % 16], r = 0..3.
