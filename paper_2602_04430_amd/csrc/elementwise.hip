@@ -526,7 +526,7 @@ hipError_t head_filter(int dt, const float* x, int64_t ldx, int n_items, int d, 
 // (item, label) product is summed as before, eight values per lane and 512-value step and then
 // across the wavefront, but a head row is read from L2 once for IT items instead of once per
 // item, and the labels spread over eight workgroups: one workgroup per item walked all 256 rows
-// (1 MiB from L2 an item; 109 us for 192 items, now 29 + 4).
+// (1 MiB from L2 an item; 109 us for 192 items, now 16 + 4).
 template <typename T, int IT>
 __global__ __launch_bounds__(256) void head_map_kernel(const float* __restrict__ x, int64_t ldx, int n_items, int d,
                                                        const float* __restrict__ g, float eps, const T* __restrict__ W,
@@ -651,8 +651,9 @@ template <typename T>
 static hipError_t head_map_t(const float* x, int64_t ldx, int n_items, int d, const float* g, float eps, const T* head,
                              int lo, int n, const int32_t* in_rows, const int32_t* out_rows, float* logits, int64_t ldl,
                              hipStream_t st) {
-  // as many items as their rows fit 64 KiB of LDS (two workgroups per CU), down to one
-  if (d <= 2048) return launch_head_map<T, 8>(x, ldx, n_items, d, g, eps, head, lo, n, in_rows, out_rows, logits, ldl, st);
+  // two items while their rows fit 64 KiB of LDS, else one.  More items a workgroup read the head
+  // less often from L2 but leave CUs idle and make each one's chain longer: 192 items of 2048
+  // columns 16 us with two, 20 with four, 27 with eight; two is also the fastest at 1 and at 2048.
   if (d <= 8192) return launch_head_map<T, 2>(x, ldx, n_items, d, g, eps, head, lo, n, in_rows, out_rows, logits, ldl, st);
   return launch_head_map<T, 1>(x, ldx, n_items, d, g, eps, head, lo, n, in_rows, out_rows, logits, ldl, st);
 }

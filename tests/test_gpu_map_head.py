@@ -1,4 +1,5 @@
-"""The map head at the edges of its splits (items of 8 or 2 per workgroup, labels of 32): logits
+"""The map head at the edges of its splits (items of 2 or, beyond 8192 columns, 1 per workgroup,
+labels of 32): logits
 against the FP64 oracle within the FP32 bound, the same bits alone and among many, ids the first
 maximum of the item's logits."""
 import numpy as np
@@ -11,7 +12,7 @@ from tests.gpu_common import E_F32, Engine, say
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("d,labels,items", [(128, 1, 1), (128, 31, 9), (128, 33, 17), (128, 100, 8), (2112, 40, 5)])
+@pytest.mark.parametrize("d,labels,items", [(128, 1, 1), (128, 31, 9), (128, 33, 17), (128, 100, 8), (2112, 40, 5), (8256, 33, 3)])
 def test_map_head_splits(device, d, labels, items):
     shape = synth.ModelShape(n_layers=1, d_model=d, n_heads=2, n_kv_heads=1, head_dim=32, d_ffn=64, vocab=160)
     w = synth.make_weights(shape, 3, gain_jitter=0.1)
