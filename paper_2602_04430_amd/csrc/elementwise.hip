@@ -8,36 +8,78 @@
 
 namespace kvop {
 
+// eight values in 16- or 32-byte accesses
+template <typename T> struct Vec8;
+template <> struct Vec8<bf16_t> {
+  __device__ static void load(const bf16_t* p, float* x) {
+    const u32x4 v = *reinterpret_cast<const u32x4*>(p);
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      x[2 * q] = bf2f((bf16_t)(v[q] & 0xffffu));
+      x[2 * q + 1] = bf2f((bf16_t)(v[q] >> 16));
+    }
+  }
+  __device__ static void store(bf16_t* p, const float* x) {
+    u32x4 v;
+#pragma unroll
+    for (int q = 0; q < 4; q++) v[q] = pack_bf16x2(x[2 * q], x[2 * q + 1]);
+    *reinterpret_cast<u32x4*>(p) = v;
+  }
+};
+template <> struct Vec8<float> {
+  __device__ static void load(const float* p, float* x) {
+    const f32x4 a = *reinterpret_cast<const f32x4*>(p), b = *reinterpret_cast<const f32x4*>(p + 4);
+#pragma unroll
+    for (int q = 0; q < 4; q++) { x[q] = a[q]; x[4 + q] = b[q]; }
+  }
+  __device__ static void store(float* p, const float* x) {
+    *reinterpret_cast<f32x4*>(p) = f32x4{x[0], x[1], x[2], x[3]};
+    *reinterpret_cast<f32x4*>(p + 4) = f32x4{x[4], x[5], x[6], x[7]};
+  }
+};
+
 // ---------------------------------------------------------------- embedding
+// A wavefront per row, eight values per lane and access, a row's pieces in flight together.  Bound by
+// the bytes written: 62 870 rows of 2048 took 219 us with a workgroup per row and a value per thread
+// and access, now 148.
 template <typename T>
-__global__ void embed_kernel(const T* __restrict__ E, const int32_t* __restrict__ tok, int S, int n_rows, int d,
-                             int vocab, float* __restrict__ x) {
-  int row = blockIdx.x;
+__global__ __launch_bounds__(256) void embed_kernel(const T* __restrict__ E, const int32_t* __restrict__ tok, int S,
+                                                    int n_rows, int d, int vocab, float* __restrict__ x) {
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (row >= n_rows) return;
   int t = S > 0 ? tok[row % S] : tok[row];
   t = min(max(t, 0), vocab - 1);  // ids are validated by the callers; the clamp only guards the gather
   const T* e = E + (int64_t)t * d;
   float* o = x + (int64_t)row * d;
-  for (int c = threadIdx.x; c < d; c += blockDim.x) o[c] = to_f32(e[c]);
+  for (int c0 = 8 * lane; c0 < d; c0 += 2048) {
+    float v[4][8];
+#pragma unroll
+    for (int u = 0; u < 4; u++) Vec8<T>::load(e + min(c0 + 512 * u, d - 8), v[u]);
+#pragma unroll
+    for (int u = 0; u < 4; u++)
+      if (c0 + 512 * u < d) Vec8<float>::store(o + c0 + 512 * u, v[u]);
+  }
 }
 
 hipError_t embed_rows(int dt, const void* E, const int32_t* tok, int n_rows, int d, int vocab, float* x,
                       hipStream_t st) {
   if (n_rows <= 0) return hipSuccess;
+  if (d % 8) return hipErrorInvalidValue;   // eight-value row pieces
   if (dt == DT_F32)
-    hipLaunchKernelGGL(embed_kernel<float>, dim3(n_rows), dim3(256), 0, st, (const float*)E, tok, 0, n_rows, d, vocab, x);
+    hipLaunchKernelGGL(embed_kernel<float>, dim3((n_rows + 3) / 4), dim3(256), 0, st, (const float*)E, tok, 0, n_rows, d, vocab, x);
   else
-    hipLaunchKernelGGL(embed_kernel<bf16_t>, dim3(n_rows), dim3(256), 0, st, (const bf16_t*)E, tok, 0, n_rows, d, vocab, x);
+    hipLaunchKernelGGL(embed_kernel<bf16_t>, dim3((n_rows + 3) / 4), dim3(256), 0, st, (const bf16_t*)E, tok, 0, n_rows, d, vocab, x);
   return hipGetLastError();
 }
 
 hipError_t embed_suffix(int dt, const void* E, const int32_t* suffix, int S, int n_rows, int d, int vocab, float* x,
                         hipStream_t st) {
   if (n_rows <= 0) return hipSuccess;
+  if (d % 8) return hipErrorInvalidValue;   // eight-value row pieces
   if (dt == DT_F32)
-    hipLaunchKernelGGL(embed_kernel<float>, dim3(n_rows), dim3(256), 0, st, (const float*)E, suffix, S, n_rows, d, vocab, x);
+    hipLaunchKernelGGL(embed_kernel<float>, dim3((n_rows + 3) / 4), dim3(256), 0, st, (const float*)E, suffix, S, n_rows, d, vocab, x);
   else
-    hipLaunchKernelGGL(embed_kernel<bf16_t>, dim3(n_rows), dim3(256), 0, st, (const bf16_t*)E, suffix, S, n_rows, d, vocab, x);
+    hipLaunchKernelGGL(embed_kernel<bf16_t>, dim3((n_rows + 3) / 4), dim3(256), 0, st, (const bf16_t*)E, suffix, S, n_rows, d, vocab, x);
   return hipGetLastError();
 }
 
@@ -113,35 +155,6 @@ hipError_t rmsnorm_rows(int dt, const float* x, int64_t ldx, const float* g, int
 // ---------------------------------------------------------------- rotary embedding
 // thread per (row, head, 8 consecutive pairs i..i+7): (x_i, x_{i+D/2}) ->
 // (x_i c - x_{i+D/2} s, x_{i+D/2} c + x_i s), 16- or 32-byte accesses (D/2 a multiple of 8)
-template <typename T> struct Vec8;
-template <> struct Vec8<bf16_t> {
-  __device__ static void load(const bf16_t* p, float* x) {
-    const u32x4 v = *reinterpret_cast<const u32x4*>(p);
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-      x[2 * q] = bf2f((bf16_t)(v[q] & 0xffffu));
-      x[2 * q + 1] = bf2f((bf16_t)(v[q] >> 16));
-    }
-  }
-  __device__ static void store(bf16_t* p, const float* x) {
-    u32x4 v;
-#pragma unroll
-    for (int q = 0; q < 4; q++) v[q] = pack_bf16x2(x[2 * q], x[2 * q + 1]);
-    *reinterpret_cast<u32x4*>(p) = v;
-  }
-};
-template <> struct Vec8<float> {
-  __device__ static void load(const float* p, float* x) {
-    const f32x4 a = *reinterpret_cast<const f32x4*>(p), b = *reinterpret_cast<const f32x4*>(p + 4);
-#pragma unroll
-    for (int q = 0; q < 4; q++) { x[q] = a[q]; x[4 + q] = b[q]; }
-  }
-  __device__ static void store(float* p, const float* x) {
-    *reinterpret_cast<f32x4*>(p) = f32x4{x[0], x[1], x[2], x[3]};
-    *reinterpret_cast<f32x4*>(p + 4) = f32x4{x[4], x[5], x[6], x[7]};
-  }
-};
-
 template <typename T>
 __global__ __launch_bounds__(256) void rope_kernel(T* __restrict__ qkv, int64_t ld, int n_rows, int n_heads, int H,
                                                    int D, const int32_t* __restrict__ pos,
