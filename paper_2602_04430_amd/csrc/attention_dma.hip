@@ -62,6 +62,7 @@ struct DmaCfg {
   static constexpr int LDS_TOTAL = LDS;
   static constexpr int OPS = NJ + (FP8 ? 1 : 0);     // vector-memory operations of one tile (chunks, FP8 scales)
   static_assert((NS - 2) * (OPS + 1) <= 63 && NS >= 2, "vmcnt immediates");
+  static_assert(kOwnRows % KTO == 0, "whole own tiles between moves of the base");
 };
 
 // log2(16 / CH): consecutive rows that share one 256-byte bank line
@@ -211,6 +212,7 @@ __device__ void attn_dma_unit(const AttnArgs& a, int unit, uint8_t* smem) {
     ic.ksc = ic.vsc = nullptr;
     ic.k = ic.v = a.pool;
     if (s == 2) {
+      ic.np = kOwnRows;
       ic.clampL = max(ic.n, 1);
       ic.pitch = (int)a.own_stride * 2;
       const uint8_t* ob = reinterpret_cast<const uint8_t*>(a.own) + (int64_t)w_own_row0 * a.own_stride * 2;
@@ -276,7 +278,17 @@ __device__ void attn_dma_unit(const AttnArgs& a, int unit, uint8_t* smem) {
     ic.slot = ic.slot + 1 == C::NRING ? 0 : ic.slot + 1;
     ic.stage = ic.stage + 1 == NS ? 0 : ic.stage + 1;
     ic.t += step_of(ic.s);
-    if (ic.t >= ic.np && ic.s < 2) enter_tiles(next_source(ic.s));
+    if (ic.t >= ic.np) {
+      if (ic.s < 2) {
+        enter_tiles(next_source(ic.s));
+      } else {
+        ic.t = 0;
+        ic.n -= kOwnRows;
+        ic.clampL = max(ic.n, 1);
+        ic.k += (int64_t)kOwnRows * ic.pitch;
+        ic.v += (int64_t)kOwnRows * ic.pitch;
+      }
+    }
   };
 
   // the tile being computed

@@ -36,6 +36,7 @@ struct F32Cfg {
   static constexpr int REGION = KT * RB;             // bytes of the K (or V) part of a tile
   static constexpr int NR = REGION / 16 / 256;       // chunk loads per thread and part
   static_assert(NR >= 1 && REGION % 4096 == 0, "whole chunk loads per thread");
+  static_assert(kOwnRows % KT == 0, "whole own tiles between moves of the base");
   static constexpr int STAGE = 2 * REGION;
   static constexpr int LEAD = NS - 1;                // row numbers are loaded LEAD tiles before their chunks
   static constexpr int NRING = NS + LEAD;
@@ -156,17 +157,20 @@ __device__ void attn_f32_unit(const AttnArgs& a, int unit, int chunk, uint8_t* s
       if (rc.t >= rc.n && rc.s < 2) enter_rows(next_source(rc.s), 0);
     }
   };
-  struct { int s, t, n, clampL, pitch, slot, stage; bool list; const uint8_t *k, *v; } ic;
+  struct { int s, t, n, np, clampL, pitch, slot, stage; bool list; const uint8_t *k, *v; } ic;
   auto enter_tiles = [&](int s, int t) __attribute__((always_inline)) {
     ic.s = s;
     ic.t = t;
-    ic.n = keys_of(s);
+    ic.n = ic.np = keys_of(s);
     ic.list = list_of(s) != nullptr;
     ic.k = ic.v = a.pool;
     if (s == 2) {
+      ic.t = 0;
+      ic.n -= t;
+      ic.np = kOwnRows;
       ic.clampL = max(ic.n, 1);
       ic.pitch = (int)a.own_stride * 4;
-      const uint8_t* ob = reinterpret_cast<const uint8_t*>(a.own) + (int64_t)val(wp->own_row0) * a.own_stride * 4;
+      const uint8_t* ob = reinterpret_cast<const uint8_t*>(a.own) + (int64_t)(val(wp->own_row0) + t) * a.own_stride * 4;
       ic.k = ob + (int64_t)(a.own_kcol + h * D) * 4;
       ic.v = ob + (int64_t)(a.own_vcol + h * D) * 4;
     } else if (ic.n > 0) {
@@ -196,7 +200,17 @@ __device__ void attn_f32_unit(const AttnArgs& a, int unit, int chunk, uint8_t* s
     ic.slot = ic.slot + 1 == C::NRING ? 0 : ic.slot + 1;
     ic.stage = ic.stage + 1 == NS ? 0 : ic.stage + 1;
     ic.t += KT;
-    if (ic.t >= ic.n && ic.s < 2) enter_tiles(next_source(ic.s), 0);
+    if (ic.t >= ic.np) {
+      if (ic.s < 2) {
+        enter_tiles(next_source(ic.s), 0);
+      } else {
+        ic.t = 0;
+        ic.n -= kOwnRows;
+        ic.clampL = max(ic.n, 1);
+        ic.k += (int64_t)kOwnRows * ic.pitch;
+        ic.v += (int64_t)kOwnRows * ic.pitch;
+      }
+    }
   };
   struct { int s, t, n, pos_add, top, slot, stage; bool list; } cc;
   auto enter_compute = [&](int s, int t) __attribute__((always_inline)) {

@@ -14,6 +14,11 @@ template <int BYTES, typename T> __device__ inline void load_to_lds(const T* g, 
 #endif
 }
 
+// Offsets within a key source are 32 bits.  A cached document has fewer than 65 536 rows of at most
+// 512 bytes; an own row is as long as the projection's, and a suffix of such rows may pass 4 GiB, so
+// its base moves on every kOwnRows rows.
+constexpr int kOwnRows = 1024;
+
 template <int N> __device__ inline void vm_wait() {
   static_assert(N >= 0 && N <= 63, "vmcnt range");
   // gfx9 s_waitcnt: vmcnt in bits 3:0 and 15:14, expcnt 6:4 (7: no wait), lgkmcnt 11:8 (15: no wait)
