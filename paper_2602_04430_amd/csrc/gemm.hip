@@ -139,7 +139,8 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B,
 
   // Accumulators start at zero, or for the residual add at the residual itself: its reads
   // (in the accumulator layout, lane -> C[.. + 4*(lane/16) + r][.. + lane%16]) then overlap
-  // the first slabs instead of a read-modify-write pass after the last one.
+  // the first slabs instead of a read-modify-write pass after the last one.  (Wavefronts that only
+  // load own no outputs: past the tile they would read what other workgroups are writing.)
   f32x4 acc[MI][NI];
   if constexpr (EPI == EPI_ADD) {
     const float* Cf = reinterpret_cast<const float*>(Cv);
@@ -151,7 +152,7 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B,
 #pragma unroll
         for (int r = 0; r < 4; r++) {
           const int row = rb0 + 16 * i + r, col = cb0 + 16 * j;
-          acc[i][j][r] = (row < M && col < N) ? Cf[(int64_t)row * ldc + col] : 0.f;
+          acc[i][j][r] = (NWC == NW || wave < NWC) && row < M && col < N ? Cf[(int64_t)row * ldc + col] : 0.f;
         }
   } else {
 #pragma unroll
