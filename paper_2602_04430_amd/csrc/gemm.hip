@@ -816,6 +816,17 @@ int gemm_pick_tile(int dt, int epi, const GemmShape& s, bool aligned) {
   const Cand* cands = dt == DT_F32 ? f32_cands : bf16_cands;
   const int n_cands = (int)((dt == DT_F32 ? sizeof(f32_cands) : sizeof(bf16_cands)) / sizeof(Cand));
   const int swiglu_narrow = dt == DT_F32 ? 4 : 27;   // 32 columns wide where columns go in pairs: no gain over the next
+  // Where the 256x256 tile has more than one round, a smaller tile has to be estimated 5% faster: the
+  // constants are of one round, and over several the bytes that a smaller tile reads more per
+  // product count (M = 20 000, N = 2048, K = 5632 with the residual: 375 and 372 us estimated for
+  // 256x256 and 256x128, 432 and 494 measured).  Over 25 row counts from 2048 to 65 536 and eight
+  // projections the choice is then nowhere slower than 256x256 from 8192 rows on (within the 2% that
+  // two sweeps differ), without the margin by up to 14% at nine of them.
+  constexpr int kLarge = 26;
+  constexpr double kMargin = 1.05;
+  const TileCfg& large = kBf16Tiles[kLarge];
+  const bool rounds_of_large = dt == DT_BF16 && gemm_tile_ok(dt, kLarge, s, epi) &&
+                               (int64_t)((s.M + large.BM - 1) / large.BM) * ((s.N + large.BN - 1) / large.BN) > 256;
   int best = -1;
   double best_t = 0.0;
   for (int i = 0; i < n_cands; i++) {
@@ -826,7 +837,8 @@ int gemm_pick_tile(int dt, int epi, const GemmShape& s, bool aligned) {
     const TileCfg& t = tile_cfg(dt, c.tile);
     const int64_t tiles = (int64_t)((s.M + t.BM - 1) / t.BM) * ((s.N + t.BN - 1) / t.BN);
     const double k = s.K / 1024.0, rounds = (double)((tiles + 256 * c.per_cu - 1) / (256 * c.per_cu));
-    const double us = rounds * (c.a + c.b * k) + c.fixed + c.tail * k;
+    const double margin = rounds_of_large && c.tile != kLarge ? kMargin : 1.0;
+    const double us = margin * (rounds * (c.a + c.b * k) + c.fixed + c.tail * k);
     if (best < 0 || us < best_t) { best = c.tile; best_t = us; }
   }
   if (best >= 0) return best;
