@@ -105,12 +105,6 @@ __device__ inline void ds_read_tr8_x4(const uint32_t (&ad)[4], u32x2 (&y)[4]) {
       : "memory");
 }
 
-// m c - mc with the product rounded first
-__device__ inline float scaled_minus(float m, float c, float mc) {
-#pragma clang fp contract(off)
-  return m * c - mc;
-}
-
 template <typename TKV, int D, int KT, int NS, int KC, bool LISTS>
 __device__ void attn_dma_unit(const AttnArgs& a, int unit, uint8_t* smem) {
   using C = DmaCfg<TKV, D, KT, NS>;

@@ -51,15 +51,17 @@ struct F32Cfg {
 // The keys of an item are taken in chunks.  Each chunk has an online softmax of its own, and the
 // chunks' maxima, sums and outputs are put together in order by this one step, whether one
 // workgroup takes them all or one workgroup each: the split changes no bit.  (m, l, o) is the
-// state so far, (mc, lc, oc) the next chunk's.
+// state so far, (mc, lc, oc) the next chunk's.  A state's probabilities are relative to its maximum's
+// scaled and rounded value, so the factors are of the differences of those: taken of the exact
+// products, the roundings of large maxima (half an ulp: 1e-3 at a maximum of 2^14) stayed in.
 struct MergeFactors {
   float run, next;
 };
 __device__ inline MergeFactors merge_stats(float& m, float& l, float mc, float lc, float scale_log2) {
-  const float mn = fmaxf(m, mc);
+  const float mn = fmaxf(m, mc), mns = mn * scale_log2;
   MergeFactors f;
-  f.run = m == mn ? 1.f : __builtin_amdgcn_exp2f((m - mn) * scale_log2);
-  f.next = mc == mn ? 1.f : __builtin_amdgcn_exp2f((mc - mn) * scale_log2);
+  f.run = m == mn ? 1.f : __builtin_amdgcn_exp2f(scaled_minus(m, scale_log2, mns));
+  f.next = mc == mn ? 1.f : __builtin_amdgcn_exp2f(scaled_minus(mc, scale_log2, mns));
   l = __builtin_fmaf(lc, f.next, l * f.run);
   m = mn;
   return f;
@@ -324,7 +326,7 @@ __device__ void attn_f32_unit(const AttnArgs& a, int unit, int chunk, uint8_t* s
       const float mc = m_new == -INFINITY ? 0.f : m_new * c;
       // exactly 1 when the maximum did not move, 0 when m_run = -inf
       const bool moved = m_new > m_run;
-      const float alpha = moved ? __builtin_amdgcn_exp2f(__builtin_fmaf(m_run, c, -mc)) : 1.f;
+      const float alpha = moved ? __builtin_amdgcn_exp2f(scaled_minus(m_run, c, mc)) : 1.f;
       float psum = 0.f;
 #pragma unroll
       for (int b = 0; b < NB; b++)

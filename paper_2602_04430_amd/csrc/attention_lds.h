@@ -47,6 +47,12 @@ __device__ inline float max_over_groups(float x) {
   return fmaxf(__builtin_bit_cast(float, (uint32_t)b[0]), __builtin_bit_cast(float, (uint32_t)b[1]));
 }
 
+// m c - mc with the product rounded first
+__device__ inline float scaled_minus(float m, float c, float mc) {
+#pragma clang fp contract(off)
+  return m * c - mc;
+}
+
 // plain global load (global_load, not flat: a flat load also counts in lgkmcnt)
 template <typename T> __device__ inline T gload(const T* p) {
   return *reinterpret_cast<const __attribute__((address_space(1))) T*>(reinterpret_cast<uintptr_t>(p));
