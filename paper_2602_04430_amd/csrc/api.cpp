@@ -1278,7 +1278,11 @@ static kvop_status op_eval_impl(kvop_pool* p, const kvop_op* op, float r, const 
     // FP32 chunks that do not fit the feed-forward buffer: a region of their own, if there is one to
     // be had (not while the stream is captured: the workspace cannot grow there)
     LayerPlan lp{};
-    count_keys(work, &lp.attn);
+    AttnArgs counts{}, counts_last{};   // of the suffix layers' work items, and of the last layer's
+    count_keys(work, &counts);
+    count_keys(work_last, &counts_last);
+    lp.attn.longest_keys = counts.longest_keys;
+    lp.attn.total_keys = counts.total_keys;
     lp.attn.Hkv = Hkv;
     lp.attn.G = G;
     lp.attn.Pmax = Pmax_s;
@@ -1325,6 +1329,8 @@ static kvop_status op_eval_impl(kvop_pool* p, const kvop_op* op, float r, const 
       lp.attn.work = (const AttnWork*)(md + (lp.q_last ? o_wlast : o_work));
       lp.attn.n_work = (int)(lp.q_last ? work_last.size() : work.size());
       lp.attn.Pmax = lp.q_last ? 1 : Pmax_s;
+      lp.attn.longest_keys = (lp.q_last ? counts_last : counts).longest_keys;
+      lp.attn.total_keys = (lp.q_last ? counts_last : counts).total_keys;
       lp.attn.n_part = lp.q_last ? chunks_last : chunks;
       lp.attn.part = part ? (float*)((char*)m->ws.p + base_ws) : nullptr;
       kvop_status s = run_layer(m, l, bufs, lp, p->base, p->kvdt, nullptr, 0, st);
