@@ -416,6 +416,15 @@ int32_t kvop_gemm_pick_tile(int32_t dtype, int32_t epilogue, int32_t M, int32_t 
  * a BF16 cache. */
 kvop_status kvop_set_attention_kernel(int32_t variant);
 int32_t kvop_get_attention_kernel(void);
+/* The form of the attention that a suffix layer of kvop_op_eval takes over a work list (one item per
+ * document or pair and block of query rows): query_rows query rows an item and kv head (1 .. 64),
+ * longest_keys keys of the longest item, total_keys of all together (retained and own rows).
+ * BF16 compute: the stages of the direct-load kernel (0: the register-staged kernel serves it);
+ * FP32: 2 = the keys of long items go to several workgroups (where there is room for their
+ * states), 3 = one workgroup per item and kv head.  All forms give the same bits.  Host state only,
+ * no device needed.  -1 for arguments out of range. */
+int32_t kvop_attention_form(int32_t dtype, int32_t kv_dtype, int32_t head_dim, int32_t n_kv_heads, int32_t query_rows,
+                            int32_t longest_keys, int64_t total_keys);
 /* Widen n FP8 (E4M3 fn) codes (device bytes) to BF16 bit patterns (device uint16) with the
  * conversion the direct-load attention kernels apply to FP8 cache rows.  n > 0, a multiple
  * of 8 (EINVAL otherwise).  Asynchronous on stream. */

@@ -2214,6 +2214,22 @@ int32_t kvop_gemm_pick_tile(int32_t dtype, int32_t epi, int32_t M, int32_t N, in
   return gemm_pick_tile(dtype == KVOP_F32 ? DT_F32 : DT_BF16, epi, s);
 }
 
+int32_t kvop_attention_form(int32_t dtype, int32_t kv_dtype, int32_t D, int32_t Hkv, int32_t query_rows,
+                            int32_t longest_keys, int64_t total_keys) {
+  if ((dtype != KVOP_F32 && dtype != KVOP_BF16) || kv_dtype < KVOP_KV_F32 || kv_dtype > KVOP_KV_FP8 ||
+      (dtype == KVOP_F32) != (kv_dtype == KVOP_KV_F32) || (D != 32 && D != 64 && D != 128) || Hkv < 1 || query_rows < 1 ||
+      query_rows > 64 || longest_keys < 0 || total_keys < longest_keys)
+    return -1;
+  AttnArgs a{};
+  a.Hkv = Hkv;
+  a.G = 1;
+  a.Pmax = query_rows;
+  a.longest_keys = longest_keys;
+  a.total_keys = total_keys;
+  const int kvdt = kv_dtype == KVOP_KV_F32 ? DT_F32 : (kv_dtype == KVOP_KV_BF16 ? DT_BF16 : DT_FP8);
+  return attention_form(dtype == KVOP_F32 ? DT_F32 : DT_BF16, kvdt, D, a);
+}
+
 kvop_status kvop_debug_read_cache(kvop_pool* p, kvop_handle h, int32_t layer, int32_t kv_head, int32_t kv,
                                   float* out, void* stream) {
   if (!p || !out) return fail(KVOP_EINVAL, "null argument");

@@ -443,6 +443,11 @@ bool attention_is_dma(int cdt, int kvdt, int D) {
   return g_attn_impl >= 0 && cdt == DT_BF16 && (kvdt == DT_BF16 || kvdt == DT_FP8) && (D == 64 || D == 128);
 }
 
+int attention_form(int cdt, int kvdt, int D, const AttnArgs& a) {
+  if (attention_is_dma(cdt, kvdt, D)) return attention_dma_stages(kvdt, D, g_attn_impl, a);
+  return cdt == DT_F32 ? (attention_f32_splits(D, a) ? 2 : 3) : 0;
+}
+
 hipError_t attention(int cdt, int kvdt, int D, const AttnArgs& a, hipStream_t st) {
   if (a.n_work <= 0) return hipSuccess;
   if (attention_is_dma(cdt, kvdt, D)) {

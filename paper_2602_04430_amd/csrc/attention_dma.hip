@@ -625,15 +625,22 @@ static bool longest_unit_bound(const AttnArgs& a, int D) {
   return 2.0 * chain_us > bytes_us;
 }
 
+int attention_dma_stages(int kvdt, int D, int variant, const AttnArgs& a) {
+  if (variant == 0) return 2;
+  if (variant == 1 || D == 64 || kvdt == DT_FP8 || a.counter) return 3;
+  return longest_unit_bound(a, D) ? 4 : 2;
+}
+
 template <typename TKV, int D>
-static hipError_t launch_dma_variant(int variant, const AttnArgs& a, hipStream_t st) {
+static hipError_t launch_dma_variant(int kvdt, int variant, const AttnArgs& a, hipStream_t st) {
+  const int stages = attention_dma_stages(kvdt, D, variant, a);
   if (variant == 0) return launch_dma<TKV, D, 64, 2>(a, st);
   if constexpr (D == 64) return launch_dma<TKV, D, 64, 3>(a, st);
   else {
     if (variant == 1) return launch_dma<TKV, D, 64, 3>(a, st);
     if constexpr (sizeof(TKV) == 1) return launch_dma<TKV, D, 64, 3, 32>(a, st);
-    else if (a.counter) return launch_dma<TKV, D, 32, 3>(a, st);
-    else if (longest_unit_bound(a, D)) return launch_dma<TKV, D, 32, 4>(a, st);
+    else if (stages == 3) return launch_dma<TKV, D, 32, 3>(a, st);
+    else if (stages == 4) return launch_dma<TKV, D, 32, 4>(a, st);
     else return launch_dma<TKV, D, 32, 2>(a, st);
   }
 }
@@ -659,11 +666,11 @@ hipError_t attention_dma(int kvdt, int D, int variant, const AttnArgs& a, hipStr
   if (a.counter && a.persistent_wgs < 1) return hipErrorInvalidValue;
   if (a.G * a.Pmax > 64 || a.G < 1 || a.Pmax < 1) return hipErrorInvalidValue;
   if (kvdt == DT_BF16) {
-    if (D == 128) return launch_dma_variant<bf16_t, 128>(variant, a, st);
-    if (D == 64) return launch_dma_variant<bf16_t, 64>(variant, a, st);
+    if (D == 128) return launch_dma_variant<bf16_t, 128>(kvdt, variant, a, st);
+    if (D == 64) return launch_dma_variant<bf16_t, 64>(kvdt, variant, a, st);
   } else if (kvdt == DT_FP8) {
-    if (D == 128) return launch_dma_variant<fp8_t, 128>(variant, a, st);
-    if (D == 64) return launch_dma_variant<fp8_t, 64>(variant, a, st);
+    if (D == 128) return launch_dma_variant<fp8_t, 128>(kvdt, variant, a, st);
+    if (D == 64) return launch_dma_variant<fp8_t, 64>(kvdt, variant, a, st);
   }
   return hipErrorInvalidValue;
 }

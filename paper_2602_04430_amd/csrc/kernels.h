@@ -108,15 +108,22 @@ hipError_t attention(int cdt, int kvdt, int D, const AttnArgs& a, hipStream_t st
 // into registers, G query heads of one kv head per workgroup (G in {1, 2, 4}, D in {64, 128})
 bool attention_decode_ok(int kvdt, int D, int G);
 hipError_t attention_decode(int kvdt, int D, const AttnArgs& a, hipStream_t st);
-// BF16 compute with a BF16 or FP8 cache, D in {64, 128}: tiles fetched by direct global->LDS
-// loads.  variant: 0 = 64-key tiles / 2 stages, 1 = 64 / 3, 2 = 32 / 3.
+// FP32 compute and cache, D in {32, 64, 128}; whether the work list is one whose long items are split
+// over several workgroups (given a.part)
 hipError_t attention_f32(int D, const AttnArgs& a, hipStream_t st);
 bool attention_f32_splits(int D, const AttnArgs& a);
+// BF16 compute with a BF16 or FP8 cache, D in {64, 128}: tiles fetched by direct global->LDS
+// loads.  variant: 0 = 64-key tiles / 2 stages, 1 = 64 / 3, 2 = 32-key tiles of a BF16 cache at
+// D = 128 in 2, 3 (persistent) or 4 stages by the work list, otherwise as 1.
 hipError_t attention_dma(int kvdt, int D, int variant, const AttnArgs& a, hipStream_t st);
+int attention_dma_stages(int kvdt, int D, int variant, const AttnArgs& a);
 // FP8 (E4M3) codes -> BF16 bits with the conversion the direct-load kernels use (n % 8 == 0)
 hipError_t fp8_widen(const uint8_t* codes, uint16_t* out, int n, hipStream_t st);
 // whether attention() runs the direct-load kernels for this combination (they alone honour pad_a)
 bool attention_is_dma(int cdt, int kvdt, int D);
+// the form attention() launches for such a work list: the stages of the direct-load kernel; FP32 2 =
+// long items split over workgroups (where there is room for their states), 3 = whole; else 0
+int attention_form(int cdt, int kvdt, int D, const AttnArgs& a);
 // attention kernel used by attention(): -1 = register-staged, else the attention_dma variant
 void attention_set_impl(int impl);
 int attention_get_impl();

@@ -79,6 +79,7 @@ _SIGS = {
                                   C.c_int32, C.c_int64, C.c_int64, C.c_int64, _P]),
     "kvop_gemm_set_tile": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32]),
     "kvop_gemm_pick_tile": (C.c_int32, [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32]),
+    "kvop_attention_form": (C.c_int32, [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int64]),
     "kvop_debug_read_cache": (C.c_int, [_P, C.c_uint64, C.c_int32, C.c_int32, C.c_int32, _P, _P]),
     "kvop_cascade_eval": (C.c_int, [_P, C.POINTER(kvop_op), C.POINTER(kvop_stage), C.c_int32, _P, C.c_int32, _P, _P,
                                     _P, _P, _P]),
@@ -290,6 +291,11 @@ def kvop_gemm_set_tile(dtype: int, epilogue: int, N: int, K: int, M: int, tile: 
 
 def kvop_gemm_pick_tile(dtype: int, epilogue: int, M: int, N: int, K: int) -> int:
     return int(lib().kvop_gemm_pick_tile(dtype, epilogue, M, N, K))
+
+
+def kvop_attention_form(dtype: int, kv_dtype: int, head_dim: int, n_kv_heads: int, query_rows: int,
+                        longest_keys: int, total_keys: int) -> int:
+    return int(lib().kvop_attention_form(dtype, kv_dtype, head_dim, n_kv_heads, query_rows, longest_keys, total_keys))
 
 
 def kvop_debug_read_cache(pool, handle, layer: int, kv_head: int, kv: int, out_dev, stream=None) -> None:
