@@ -304,14 +304,23 @@ struct LayerPlan {
 };
 
 // what the attention launcher goes by: the longest work item's keys and the sum over all
-void count_keys(const std::vector<AttnWork>& work, AttnArgs* a) {
-  a->longest_keys = 0;
-  a->total_keys = 0;
-  for (const AttnWork& w : work) {
+struct KeyCount {
+  int longest = 0;
+  int64_t total = 0;
+  void add(const AttnWork& w) {
     const int k = std::max(w.n_a, w.pad_a) + w.n_b + w.n_own;
-    a->longest_keys = std::max(a->longest_keys, k);
-    a->total_keys += k;
+    longest = std::max(longest, k);
+    total += k;
   }
+  void give(AttnArgs* a) const {
+    a->longest_keys = longest;
+    a->total_keys = total;
+  }
+};
+KeyCount count_keys(const std::vector<AttnWork>& work) {
+  KeyCount c;
+  for (const AttnWork& w : work) c.add(w);
+  return c;
 }
 
 // numbers the FP32 chunks of the items that have several; returns how many there are
@@ -914,7 +923,7 @@ static kvop_status kv_build_impl(kvop_pool* p, const int32_t* tokens, const int6
     lp.alt_shift = nullptr;
     lp.attn.work = (const AttnWork*)(md + o_work);
     lp.attn.n_work = (int)work.size();
-    count_keys(work, &lp.attn);
+    count_keys(work).give(&lp.attn);
     lp.attn.idx = nullptr;
     lp.attn.Pmax = Pmax;
     lp.own_from_qkv = false;
@@ -1143,6 +1152,7 @@ static kvop_status op_eval_impl(kvop_pool* p, const kvop_op* op, float r, const 
     work.reserve((size_t)B * wq);
     work_last.reserve((size_t)B);
     std::vector<int32_t> pos_dec(kind == KVOP_MAP ? B : 0);
+    KeyCount counts, counts_last;   // of the suffix layers' work items, and of the last layer's
     for (int b = 0; b < B; b++) {
       int it = w0 + b;
       const DocSlot* A = docs[it * per];
@@ -1176,6 +1186,7 @@ static kvop_status op_eval_impl(kvop_pool* p, const kvop_op* op, float r, const 
         w.n_own = std::min(S, q0 + Pmax_s);
         w.own_pos0 = pos0;
         work.push_back(w);
+        counts.add(w);
         if (q0 + Pmax_s >= S) {
           // the last layer: the item's last row only, against all its own rows
           w.q_row0 = b * S + S - 1;
@@ -1183,6 +1194,7 @@ static kvop_status op_eval_impl(kvop_pool* p, const kvop_op* op, float r, const 
           w.n_q = 1;
           w.n_own = S;
           work_last.push_back(w);
+          counts_last.add(w);
         }
       }
       if (kind == KVOP_MAP) pos_dec[b] = pos0 + S;
@@ -1196,8 +1208,11 @@ static kvop_status op_eval_impl(kvop_pool* p, const kvop_op* op, float r, const 
       const int kmax = work.empty() ? 0 : work.front().n_a + work.front().n_b;
       for (AttnWork& w : work) w.pad_a = kmax - w.n_b;
       for (AttnWork& w : work_last) w.pad_a = kmax - w.n_b;
+      counts = count_keys(work);
+      counts_last = count_keys(work_last);
     }
-    const int chunks = number_chunks(work, D), chunks_last = number_chunks(work_last, D);
+    const bool f32 = m->dt == DT_F32;
+    const int chunks = f32 ? number_chunks(work, D) : 0, chunks_last = f32 ? number_chunks(work_last, D) : 0;
     // map decode: work items with one query position against (retained rows + own rows)
     std::vector<AttnWork> dwork;
     std::vector<int32_t> own_src, own_dst;
@@ -1278,16 +1293,12 @@ static kvop_status op_eval_impl(kvop_pool* p, const kvop_op* op, float r, const 
     // FP32 chunks that do not fit the feed-forward buffer: a region of their own, if there is one to
     // be had (not while the stream is captured: the workspace cannot grow there)
     LayerPlan lp{};
-    AttnArgs counts{}, counts_last{};   // of the suffix layers' work items, and of the last layer's
-    count_keys(work, &counts);
-    count_keys(work_last, &counts_last);
-    lp.attn.longest_keys = counts.longest_keys;
-    lp.attn.total_keys = counts.total_keys;
+    counts.give(&lp.attn);
     lp.attn.Hkv = Hkv;
     lp.attn.G = G;
     lp.attn.Pmax = Pmax_s;
     size_t part = 0;
-    if (m->dt == DT_F32 && chunks > 0 && part_bytes(m, chunks, Pmax_s) > rows * F * 4 &&
+    if (chunks > 0 && part_bytes(m, chunks, Pmax_s) > rows * F * 4 &&
         attention_f32_splits(D, lp.attn)) {
       hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
       if (hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone)
@@ -1329,8 +1340,7 @@ static kvop_status op_eval_impl(kvop_pool* p, const kvop_op* op, float r, const 
       lp.attn.work = (const AttnWork*)(md + (lp.q_last ? o_wlast : o_work));
       lp.attn.n_work = (int)(lp.q_last ? work_last.size() : work.size());
       lp.attn.Pmax = lp.q_last ? 1 : Pmax_s;
-      lp.attn.longest_keys = (lp.q_last ? counts_last : counts).longest_keys;
-      lp.attn.total_keys = (lp.q_last ? counts_last : counts).total_keys;
+      (lp.q_last ? counts_last : counts).give(&lp.attn);
       lp.attn.n_part = lp.q_last ? chunks_last : chunks;
       lp.attn.part = part ? (float*)((char*)m->ws.p + base_ws) : nullptr;
       kvop_status s = run_layer(m, l, bufs, lp, p->base, p->kvdt, nullptr, 0, st);
@@ -1782,7 +1792,7 @@ kvop_status kvop_mixed_eval(kvop_pool* p, const kvop_mixed_op* ops, int32_t n_op
       lp.alt_shift = any_join ? (const int32_t*)(md + o_shift) : nullptr;
       lp.attn.work = (const AttnWork*)(md + o_work);
       lp.attn.n_work = (int)work.size();
-      count_keys(work, &lp.attn);
+      count_keys(work).give(&lp.attn);
       lp.attn.idx = idx;
       lp.attn.Pmax = Pmax;
       lp.attn.counter = persistent ? counter : nullptr;
