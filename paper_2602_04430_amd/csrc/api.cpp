@@ -1101,6 +1101,7 @@ static kvop_status op_eval_impl(kvop_pool* p, const kvop_op* op, float r, const 
     for (int j = 0; j < per; j++) lidx[i * per + j] = (int64_t)ids[i] * per + j;
   std::vector<const DocSlot*> docs(n_lists);
   std::vector<ListCheck> checks(n_lists);
+  int32_t longest_list = 0;
   for (int i = 0; i < n_lists; i++) {
     const int64_t li = lidx[i];
     docs[i] = lookup(p, hs[li]);
@@ -1111,6 +1112,7 @@ static kvop_status op_eval_impl(kvop_pool* p, const kvop_op* op, float r, const 
       return fail(KVOP_EINVAL, "list " + std::to_string(li) + " holds " + std::to_string(k) + " rows, k(r, L) = " +
                                    std::to_string(retained_count(r, docs[i]->L)));
     checks[i] = ListCheck{idx_off[li], (int32_t)k, docs[i]->L};
+    longest_list = std::max(longest_list, (int32_t)k);
   }
   for (int i = 0; i < n_eval; i++) {
     int64_t top = join ? (int64_t)docs[2 * i]->L + docs[2 * i + 1]->L : docs[i]->L;
@@ -1126,7 +1128,7 @@ static kvop_status op_eval_impl(kvop_pool* p, const kvop_op* op, float r, const 
     memcpy(m->stage.p + o_chk, checks.data(), checks.size() * sizeof(ListCheck));
     HIPTRY(hipMemcpyAsync(m->meta.p, m->stage.p, mir.size, hipMemcpyHostToDevice, st));
     HIPTRY(hipMemsetAsync(m->dflag, 0, 4, st));
-    HIPTRY(validate_lists(idx, (const ListCheck*)m->meta.p, n_lists, m->dflag, st));
+    HIPTRY(validate_lists(idx, (const ListCheck*)m->meta.p, n_lists, longest_list, m->dflag, st));
     HIPTRY(hipMemcpyAsync(m->hflag, m->dflag, 4, hipMemcpyDeviceToHost, st));
     HIPTRY(hipStreamSynchronize(st));
     if (m->hflag[0] != 0)
@@ -1582,6 +1584,7 @@ kvop_status kvop_mixed_eval(kvop_pool* p, const kvop_mixed_op* ops, int32_t n_op
   std::vector<int32_t> rank(n_items);
   std::vector<const DocSlot*> docA(n_items), docB(n_items, nullptr);
   std::vector<ListCheck> checks;
+  int32_t longest_list = 0;
   for (int i = 0; i < n_items; i++) {
     int k = item_op[i];
     if (k < 0 || k >= n_ops) return fail(KVOP_EINVAL, "item operator out of range");
@@ -1599,6 +1602,7 @@ kvop_status kvop_mixed_eval(kvop_pool* p, const kvop_mixed_op* ops, int32_t n_op
       if (!(o.flags & KVOP_FLAG_ANY_COUNT) && kk != retained_count(r, d->L))
         return fail(KVOP_EINVAL, "list " + std::to_string(li) + " does not hold k(r, L) rows");
       checks.push_back(ListCheck{idx_off[li], (int32_t)kk, d->L});
+      longest_list = std::max(longest_list, (int32_t)kk);
       (j == 0 ? docA[i] : docB[i]) = d;
     }
     int64_t top = docA[i]->L + (docB[i] ? docB[i]->L : 0);
@@ -1614,7 +1618,7 @@ kvop_status kvop_mixed_eval(kvop_pool* p, const kvop_mixed_op* ops, int32_t n_op
     memcpy(m->stage.p + o_chk, checks.data(), checks.size() * sizeof(ListCheck));
     HIPTRY(hipMemcpyAsync(m->meta.p, m->stage.p, mir.size, hipMemcpyHostToDevice, st));
     HIPTRY(fill_i32(m->dflag, 0, 1, st));
-    HIPTRY(validate_lists(idx, (const ListCheck*)m->meta.p, (int)checks.size(), m->dflag, st));
+    HIPTRY(validate_lists(idx, (const ListCheck*)m->meta.p, (int)checks.size(), longest_list, m->dflag, st));
     HIPTRY(hipMemcpyAsync(m->hflag, m->dflag, 4, hipMemcpyDeviceToHost, st));
     HIPTRY(hipStreamSynchronize(st));
     if (m->hflag[0] != 0)

@@ -689,17 +689,27 @@ hipError_t head_map(int dt, const float* x, int64_t ldx, int n_items, int d, con
 }
 
 // ---------------------------------------------------------------- validation
-// A workgroup per list, four pairs of neighbours per thread in flight: a wavefront per list with one
-// pair at a time waited for memory 64 times for a list of 4096 rows (24 us), now 4.7.
+// A workgroup or (WAVES = 1) a wavefront per list, four pairs of neighbours per lane in flight: with
+// one pair at a time a wavefront waited for memory 64 times for a list of 4096 rows (25 us for 1024
+// lists of up to that).  A workgroup per list ends a long one sooner, a wavefront per list starts
+// many short ones sooner (1.2 M workgroups/ms): us with workgroups and wavefronts 4.8 and 8.9 for
+// 1024 lists of up to 4096 rows, 7.8 and 11.1 for 4096, 13 and 14 for 8000, 23 and 20 for 16 000;
+// 5.0 and 4.9 for 2000 of 1024; 3.1 and 2.6 for 1000 of 256, 12.8 and 4.9 for 12 000; 25.6 and 8.5
+// for 30 000 of 4.
+template <int WAVES>
 __global__ __launch_bounds__(256) void validate_kernel(const int32_t* __restrict__ idx,
-                                                       const ListCheck* __restrict__ lists, int* __restrict__ bad) {
-  const ListCheck l = lists[blockIdx.x];
+                                                       const ListCheck* __restrict__ lists, int n_lists,
+                                                       int* __restrict__ bad) {
+  constexpr int T = 64 * WAVES;
+  const int li = blockIdx.x * (4 / WAVES) + (int)threadIdx.x / T, t = threadIdx.x % T;
+  if (li >= n_lists) return;   // whole wavefronts, and for WAVES = 4 no workgroup
+  const ListCheck l = lists[li];
   int wrong = 0;
-  for (int i0 = threadIdx.x; i0 < l.n; i0 += 1024) {
+  for (int i0 = t; i0 < l.n; i0 += 4 * T) {
     int v[4], before[4];
 #pragma unroll
     for (int u = 0; u < 4; u++) {
-      const int i = min(i0 + 256 * u, l.n - 1);
+      const int i = min(i0 + T * u, l.n - 1);
       v[u] = idx[l.off + i];
       before[u] = i > 0 ? idx[l.off + i - 1] : -1;
     }
@@ -707,13 +717,18 @@ __global__ __launch_bounds__(256) void validate_kernel(const int32_t* __restrict
     for (int u = 0; u < 4; u++)
       if (v[u] < 0 || v[u] >= l.L || before[u] >= v[u]) wrong = 1;
   }
-  wrong = __syncthreads_or(wrong);
-  if (threadIdx.x == 0 && wrong) atomicAdd(bad, 1);
+  if constexpr (WAVES == 4) wrong = __syncthreads_or(wrong);
+  else wrong = __any(wrong);
+  if (t == 0 && wrong) atomicAdd(bad, 1);
 }
 
-hipError_t validate_lists(const int32_t* idx, const ListCheck* lists, int n_lists, int* bad, hipStream_t st) {
+hipError_t validate_lists(const int32_t* idx, const ListCheck* lists, int n_lists, int longest, int* bad,
+                          hipStream_t st) {
   if (n_lists <= 0) return hipSuccess;
-  hipLaunchKernelGGL(validate_kernel, dim3(n_lists), dim3(256), 0, st, idx, lists, bad);
+  if (n_lists > 2 * longest)
+    hipLaunchKernelGGL(validate_kernel<1>, dim3((n_lists + 3) / 4), dim3(256), 0, st, idx, lists, n_lists, bad);
+  else
+    hipLaunchKernelGGL(validate_kernel<4>, dim3(n_lists), dim3(256), 0, st, idx, lists, n_lists, bad);
   return hipGetLastError();
 }
 

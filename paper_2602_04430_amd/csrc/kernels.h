@@ -208,12 +208,14 @@ hipError_t head_map(int dt, const float* x, int64_t ldx, int n_items, int d, con
                     const void* head, int lo, int n, const int32_t* in_rows, const int32_t* out_rows, float* logits,
                     int64_t ld_logits, int32_t* tok_out, int64_t ld_tok, int32_t* next_tok, bool next_by_out,
                     hipStream_t st);
-// index-list validation: counts lists that are unsorted or out of range into *bad
+// index-list validation: counts lists that are unsorted or out of range into *bad; longest: rows of
+// the longest list
 struct ListCheck {
   int64_t off;
   int32_t n, L;
 };
-hipError_t validate_lists(const int32_t* idx, const ListCheck* lists, int n_lists, int* bad, hipStream_t st);
+hipError_t validate_lists(const int32_t* idx, const ListCheck* lists, int n_lists, int longest, int* bad,
+                          hipStream_t st);
 // counts, into *bad, the wavefronts that saw a token id outside [0, vocab)
 hipError_t validate_tokens(const int32_t* tok, int64_t n, int vocab, int* bad, hipStream_t st);
 // weight conversion: dst (dt) = src (f32); for interleave16 != 0 the rows of two [F, d]
