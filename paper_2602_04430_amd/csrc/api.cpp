@@ -1293,7 +1293,7 @@ static kvop_status op_eval_impl(kvop_pool* p, const kvop_op* op, float r, const 
     size_t act = act_bytes(m, rows, join);
     size_t own_bytes = kind == KVOP_MAP ? (size_t)c.n_layers * B * rows_per_item * 2 * Hkv * D * e : 0;
     // FP32 chunks that do not fit the feed-forward buffer: a region of their own, if there is one to
-    // be had (not while the stream is captured: the workspace cannot grow there)
+    // be had
     LayerPlan lp{};
     counts.give(&lp.attn);
     lp.attn.Hkv = Hkv;
@@ -1302,9 +1302,7 @@ static kvop_status op_eval_impl(kvop_pool* p, const kvop_op* op, float r, const 
     size_t part = 0;
     if (chunks > 0 && part_bytes(m, chunks, Pmax_s) > rows * F * 4 &&
         attention_f32_splits(D, lp.attn)) {
-      hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-      if (hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone)
-        part = (size_t)part_bytes(m, chunks, Pmax_s);
+      part = (size_t)part_bytes(m, chunks, Pmax_s);
       if (part > kMaxPart) part = 0;
     }
     const size_t base_ws = align_up(act + align_up(own_bytes, kAlign), kAlign);

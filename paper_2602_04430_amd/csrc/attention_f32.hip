@@ -12,7 +12,8 @@
 // of 32 keys and 4-byte reads of V), so where few items are long its keys go to several workgroups,
 // kAttnChunkKeys to each, and a second launch puts their results together.  64 documents of 16 to
 // 4096 rows, D = 128, 8 kv heads: 64 query rows 695 -> 206 us, 2 query rows 670 -> 144 us; 1024
-// documents: 2800 -> 2040 and 2350 -> 1230 us.
+// documents: 2800 -> 2040 and 2350 -> 1230 us.  That is for a call whose items share one suffix; mixed
+// batches and a map's decoding steps bring no room for the states and run each unit whole.
 //
 // LDS layout of a tile part (K or V): FP32 rows, 16-byte chunk c of row r at slot c ^ swz(r), so
 // that the 16 rows read at one chunk (K) and the 16 chunks read of one row (V) lie on distinct

@@ -41,7 +41,8 @@ const char* gemm_tile_name(int dt, int tile);
 bool gemm_tile_ok(int dt, int tile, const GemmShape& s, int epi);
 hipError_t gemm(int dt, int out_dt, int epi, int tile, const void* A, const void* B, void* C, const GemmShape& s,
                 hipStream_t st, const RopeEpi* rope = nullptr);
-// head dims the rotary epilogue serves (whole heads in every BF16 tile, 8-pair groups)
+// head dims the rotary epilogue serves (a BF16 tile holds whole heads, or, narrower than one, matching
+// parts of its two halves; 8-pair groups)
 bool gemm_rope_supported(int D);
 // tile for a shape: the tuned table's, else the one of least estimated time; aligned: A and B
 // start on 16-byte boundaries (otherwise only register-staged tiles are taken)

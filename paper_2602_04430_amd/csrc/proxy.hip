@@ -212,12 +212,10 @@ __device__ inline float gelu_grad_f(float x) {
 // results equal the separate passes (gather, projection, head) bit for bit.
 //
 // Bound by reading the features once (164 MB for 20 000 x 2048).  The rows per workgroup are the
-// fewest that make one round of the 256 CUs (16 to 96): every workgroup streams all of W1 from
+// fewest that make one round of the 256 CUs (32 to 96): every workgroup streams all of W1 from
 // L2, and a second round would cost as much again.  20 000 rows: 133 us as three passes (72
 // gather, 48 projection, 13 head) when this was written, 56 us now.
 constexpr int kInferLoaders = 2, kInferStages = 4, kInferAhead = 3;
-
-__device__ inline float gelu_f(float x);
 
 template <int MB, int H>
 __global__ __launch_bounds__(64 * (MB + kInferLoaders)) void proxy_infer_kernel(
@@ -354,9 +352,12 @@ static hipError_t launch_infer(const float* F, int n, int d, const float* mean, 
   return hipGetLastError();
 }
 
-// Fewer rows than this run the separate passes: a workgroup's stream of W1 takes 28 us whatever its
-// rows (2048 -> 256: 4096 rows 29 us in three passes, 38 in one; 8192 rows 42 and 43; 20 000
-// rows 82 and 56).  The standardiser has 32 KiB of LDS beside the slabs.
+// Fewer rows than this run the separate passes: a workgroup's stream of W1 takes its time whatever its
+// rows (2048 -> 256: 28 us; 4096 rows 29 us in three passes, 38 in one; 8192 rows 42 and 41; 20 000
+// rows 80 and 53).  From 8192 rows on one pass is the faster at every size it takes, 64 to 4096
+// columns and 64 to 256 hidden units (8192 rows of 4096 -> 256 69 us and 66, of 64 -> 64 15 and 10);
+// below, it depends on the size (4096 rows: 45 and 64, 15 and 9).  The standardiser has 32 KiB
+// of LDS beside the slabs.
 constexpr int kInferFusedRows = 8192;
 static bool infer_sizes_ok(int d, int H) { return d % 64 == 0 && d <= 4096 && (H == 64 || H == 128 || H == 256); }
 bool proxy_infer_fused(int n, int d, int H) { return n >= kInferFusedRows && infer_sizes_ok(d, H); }
@@ -366,13 +367,12 @@ hipError_t proxy_infer(const float* F, int n, int d, int H, const float* mean, c
                        int8_t* answered, hipStream_t st) {
   if (n <= 0) return hipSuccess;
   if (!infer_sizes_ok(d, H)) return hipErrorInvalidValue;
-  const int mb = std::min(6, std::max(1, (n + 256 * 16 - 1) / (256 * 16)));
+  const int mb = std::min(6, std::max(2, (n + 256 * 16 - 1) / (256 * 16)));
 #define KVOP_INFER(MB)                                                                                                 \
   (H == 256   ? launch_infer<MB, 256>(F, n, d, mean, istd, w1, b1, W2, b2, tau, cls, conf, answered, st)               \
    : H == 128 ? launch_infer<MB, 128>(F, n, d, mean, istd, w1, b1, W2, b2, tau, cls, conf, answered, st)               \
               : launch_infer<MB, 64>(F, n, d, mean, istd, w1, b1, W2, b2, tau, cls, conf, answered, st))
   switch (mb) {
-    case 1: return KVOP_INFER(1);
     case 2: return KVOP_INFER(2);
     case 3: return KVOP_INFER(3);
     case 4: return KVOP_INFER(4);
