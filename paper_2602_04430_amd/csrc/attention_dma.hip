@@ -30,7 +30,7 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "attention_lds.h"
+#include "direct_loads.h"
 #include "common.h"
 #include "kernels.h"
 
@@ -78,23 +78,6 @@ template <int CH> __device__ inline int swz_v8(int r) {
   else return ((r >> 2) & 1) | (((r >> 4) & 1) << 1);
 }
 
-// Transposed LDS reads as inline assembly, each block with its own wait.  (The builtin form makes
-// the compiler wait for every direct-to-LDS load in flight (vmcnt(0)) before it, since it
-// cannot tell which LDS bytes the read touches.)  The caller reads V only from stages whose
-// loads have completed (checked by the tile wait).
-__device__ inline uint32_t lds_addr(const uint8_t* p) { return (uint32_t)reinterpret_cast<uintptr_t>(p); }
-// y[2 i] from address ad[i], y[2 i + 1] from ad[i] + STEP
-template <int STEP> __device__ inline void ds_read_tr16_x8(const uint32_t (&ad)[4], u32x2 (&y)[8]) {
-  asm volatile(
-      "ds_read_b64_tr_b16 %0, %8\n\tds_read_b64_tr_b16 %1, %8 offset:%c12\n\t"
-      "ds_read_b64_tr_b16 %2, %9\n\tds_read_b64_tr_b16 %3, %9 offset:%c12\n\t"
-      "ds_read_b64_tr_b16 %4, %10\n\tds_read_b64_tr_b16 %5, %10 offset:%c12\n\t"
-      "ds_read_b64_tr_b16 %6, %11\n\tds_read_b64_tr_b16 %7, %11 offset:%c12\n\t"
-      "s_waitcnt lgkmcnt(0)"
-      : "=&v"(y[0]), "=&v"(y[1]), "=&v"(y[2]), "=&v"(y[3]), "=&v"(y[4]), "=&v"(y[5]), "=&v"(y[6]), "=&v"(y[7])
-      : "v"(ad[0]), "v"(ad[1]), "v"(ad[2]), "v"(ad[3]), "i"(STEP)
-      : "memory");
-}
 __device__ inline void ds_read_tr8_x4(const uint32_t (&ad)[4], u32x2 (&y)[4]) {
   asm volatile(
       "ds_read_b64_tr_b8 %0, %4\n\tds_read_b64_tr_b8 %1, %5\n\t"
@@ -186,7 +169,7 @@ __device__ void attn_dma_unit(const AttnArgs& a, int unit, uint8_t* smem) {
       // last tile the load goes on with row numbers that nobody reads.
       const int tl = rc.t < rc.n ? rc.t : rc.t % max(rc.n, 1);
       const int32_t* g = rc.idx ? rc.idx + min(tl + lane, rc.n - 1) : dummy;
-      __builtin_amdgcn_global_load_lds(g, (lds_void_t*)(ring + rc.slot * 64), 4, 0, 0);
+      load_to_lds<4>(g, ring + rc.slot * 64);
       rc.slot = rc.slot + 1 == C::NRING ? 0 : rc.slot + 1;
       rc.t += step_of(rc.s);
       if (rc.t >= rc.np && rc.s < 2) enter_rows(next_source(rc.s));
@@ -250,7 +233,7 @@ __device__ void attn_dma_unit(const AttnArgs& a, int unit, uint8_t* smem) {
         const int sw = v ? (FP8 && !OWN ? swz_v8<CH>(rr) : swz_v<CH>(rr)) : swz_k<CH>(rr);
         const uint8_t* g = (v ? ic.v : ic.k) + (off[j] + (uint32_t)((slot ^ sw) * 16));
         uint8_t* l = sb + (v ? C::REGION : 0) + (256 * j + 64 * wave) * 16;
-        __builtin_amdgcn_global_load_lds(g, (lds_void_t*)l, 16, 0, 0);
+        load_to_lds<16>(g, l);
       }
     if constexpr (FP8) {
       float* meta = reinterpret_cast<float*>(sb + 2 * C::REGION);
@@ -259,7 +242,7 @@ __device__ void attn_dma_unit(const AttnArgs& a, int unit, uint8_t* smem) {
         const int row = min(max(ic.list ? rws[lane] : min(tl + lane, ic.n - 1), 0), ic.clampL - 1);
         g = (wave == 0 ? ic.ksc : ic.vsc) + (row >> 4);
       }
-      __builtin_amdgcn_global_load_lds(g, (lds_void_t*)(meta + min(wave, 2) * 64), 4, 0, 0);
+      load_to_lds<4>(static_cast<const uint8_t*>(g), meta + min(wave, 2) * 64);
     }
   };
   auto issue_tile = [&]() __attribute__((always_inline)) {

@@ -22,7 +22,7 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "attention_lds.h"
+#include "direct_loads.h"
 #include "common.h"
 #include "kernels.h"
 

@@ -23,6 +23,7 @@
 #include <algorithm>
 
 #include "common.h"
+#include "direct_loads.h"
 #include "kernels.h"
 
 namespace kvop {
@@ -71,10 +72,7 @@ __device__ inline float block_max(float v, float* red) {
 }
 
 // ---------------------------------------------------------------- expected log-weights
-typedef __attribute__((address_space(3))) void lds_void_t;
-
-// two fragments of transposed LDS reads (rows at ad[i] and STEP bytes after), with their wait (see
-// the attention kernel: as builtins they would wait for the direct loads in flight)
+// two transposed reads of 16 rows, with their wait
 template <int STEP> __device__ inline void ds_read_tr16_x2(uint32_t a0, uint32_t a1, u32x4& f0, u32x4& f1) {
   u32x2 y0, y1, y2, y3;
   asm volatile(
@@ -88,19 +86,9 @@ template <int STEP> __device__ inline void ds_read_tr16_x2(uint32_t a0, uint32_t
 }
 template <int STEP> __device__ inline void ds_read_tr16_x4(const uint32_t (&ad)[4], u32x4* f) {
   u32x2 y[8];
-  asm volatile(
-      "ds_read_b64_tr_b16 %0, %8\n\tds_read_b64_tr_b16 %1, %8 offset:%c12\n\t"
-      "ds_read_b64_tr_b16 %2, %9\n\tds_read_b64_tr_b16 %3, %9 offset:%c12\n\t"
-      "ds_read_b64_tr_b16 %4, %10\n\tds_read_b64_tr_b16 %5, %10 offset:%c12\n\t"
-      "ds_read_b64_tr_b16 %6, %11\n\tds_read_b64_tr_b16 %7, %11 offset:%c12\n\ts_waitcnt lgkmcnt(0)"
-      : "=&v"(y[0]), "=&v"(y[1]), "=&v"(y[2]), "=&v"(y[3]), "=&v"(y[4]), "=&v"(y[5]), "=&v"(y[6]), "=&v"(y[7])
-      : "v"(ad[0]), "v"(ad[1]), "v"(ad[2]), "v"(ad[3]), "i"(STEP)
-      : "memory");
+  ds_read_tr16_x8<STEP>(ad, y);
 #pragma unroll
   for (int i = 0; i < 4; i++) f[i] = u32x4{y[2 * i][0], y[2 * i][1], y[2 * i + 1][0], y[2 * i + 1][1]};
-}
-template <int N> __device__ inline void loads_wait() {
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
 // four consecutive elements as floats
@@ -166,9 +154,8 @@ __global__ __launch_bounds__(kEaThreads) __attribute__((amdgpu_waves_per_eu(2)))
 #pragma unroll
       for (int i = 0; i < OPS; i++) {
         const int f = i * kEaThreads + tid, r = f / CH, c = (f % CH) ^ swz(r);
-        __builtin_amdgcn_global_load_lds(
-            reinterpret_cast<const uint8_t*>(Q + (int64_t)min(t * kEaChunk + r, L - 1) * ld + 8 * c),
-            (lds_void_t*)(tiles + (t % NS) * TILE + (i * kEaThreads + 64 * w) * 8), 16, 0, 0);
+        load_to_lds<16>(Q + (int64_t)min(t * kEaChunk + r, L - 1) * ld + 8 * c,
+                        tiles + (t % NS) * TILE + (i * kEaThreads + 64 * w) * 8);
       }
     };
     f32x4 acc[NR][NB], ones[NR];
@@ -186,9 +173,9 @@ __global__ __launch_bounds__(kEaThreads) __attribute__((amdgpu_waves_per_eu(2)))
     for (int t = 0; t < NS - 1 && t < nt; t++) issue(t);
     for (int t = 0; t < nt; t++) {
       const int behind = nt - 1 - t;
-      if (behind >= NS - 2) loads_wait<(NS - 2) * OPS>();
-      else if (behind == 1) loads_wait<OPS>();
-      else loads_wait<0>();
+      if (behind >= NS - 2) vm_wait<(NS - 2) * OPS>();
+      else if (behind == 1) vm_wait<OPS>();
+      else vm_wait<0>();
       __builtin_amdgcn_s_barrier();                    // tile t visible, tile t - 1 consumed
       if (t + NS - 1 < nt) issue(t + NS - 1);
       const uint8_t* tb = reinterpret_cast<const uint8_t*>(tiles + (t % NS) * TILE);

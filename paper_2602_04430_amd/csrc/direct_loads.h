@@ -1,5 +1,6 @@
-// What the attention kernels with direct global -> LDS loads share: explicit waits on the tiles in
-// flight, loads that keep to the vector-memory counter, and a lane-group maximum.
+// What the kernels with direct global -> LDS loads share: explicit waits on the loads in flight, loads
+// that keep to the vector-memory counter, transposed LDS reads, and for attention the rounding of a
+// scaled maximum, a lane-group maximum and the own rows' step.
 #pragma once
 #include "common.h"
 
@@ -45,6 +46,24 @@ __device__ inline float max_over_groups(float x) {
   const uint32_t v = __builtin_bit_cast(uint32_t, m);
   const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
   return fmaxf(__builtin_bit_cast(float, (uint32_t)b[0]), __builtin_bit_cast(float, (uint32_t)b[1]));
+}
+
+// Transposed LDS reads as inline assembly, each block with its own wait.  (The builtin form makes
+// the compiler wait for every direct-to-LDS load in flight (vmcnt(0)) before it, since it
+// cannot tell which LDS bytes the read touches.)  The caller reads only stages whose
+// loads have completed (by its own wait).
+__device__ inline uint32_t lds_addr(const uint8_t* p) { return (uint32_t)reinterpret_cast<uintptr_t>(p); }
+// y[2 i] from address ad[i], y[2 i + 1] from ad[i] + STEP
+template <int STEP> __device__ inline void ds_read_tr16_x8(const uint32_t (&ad)[4], u32x2 (&y)[8]) {
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %8\n\tds_read_b64_tr_b16 %1, %8 offset:%c12\n\t"
+      "ds_read_b64_tr_b16 %2, %9\n\tds_read_b64_tr_b16 %3, %9 offset:%c12\n\t"
+      "ds_read_b64_tr_b16 %4, %10\n\tds_read_b64_tr_b16 %5, %10 offset:%c12\n\t"
+      "ds_read_b64_tr_b16 %6, %11\n\tds_read_b64_tr_b16 %7, %11 offset:%c12\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(y[0]), "=&v"(y[1]), "=&v"(y[2]), "=&v"(y[3]), "=&v"(y[4]), "=&v"(y[5]), "=&v"(y[6]), "=&v"(y[7])
+      : "v"(ad[0]), "v"(ad[1]), "v"(ad[2]), "v"(ad[3]), "i"(STEP)
+      : "memory");
 }
 
 // m c - mc with the product rounded first

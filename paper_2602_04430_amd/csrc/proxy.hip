@@ -12,6 +12,7 @@
 #include <algorithm>
 
 #include "common.h"
+#include "direct_loads.h"
 #include "kernels.h"
 
 namespace kvop {
@@ -25,16 +26,6 @@ namespace kvop {
 // direct loads, 112 KiB in flight.  20 000 x 2048: 9335 us with one thread per column reading
 // its own rows (8 workgroups, one load latency every few rows), now 226 us (5.6 ns a row and pass).
 constexpr int kStatCols = 16, kStatRows = 256, kStatStages = 8, kStatLoaders = 4;
-template <int N> __device__ inline void loads_wait() {
-  static_assert(N >= 0 && N <= 63, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
-// waits until at most `behind` (0 .. MAXB, uniform) groups of OPS loads are outstanding
-template <int MAXB, int OPS> __device__ inline void loads_wait_behind(int behind) {
-  if constexpr (MAXB <= 0) loads_wait<0>();
-  else if (behind >= MAXB) loads_wait<MAXB * OPS>();
-  else loads_wait_behind<MAXB - 1, OPS>(behind);
-}
 
 __global__ __launch_bounds__(64 * (1 + kStatLoaders)) void proxy_stats_kernel(const float* __restrict__ F, int64_t n,
                                                                              int d, float* __restrict__ mean,
@@ -55,15 +46,13 @@ __global__ __launch_bounds__(64 * (1 + kStatLoaders)) void proxy_stats_kernel(co
     for (int i = 0; i < OPS; i++) {
       const int f = i * 64 * kStatLoaders + 64 * (wave - 1) + lane;    // 16-byte chunk: row f / 4, columns 4 (f % 4)
       const int64_t row = r0 + f / 4 < n ? r0 + f / 4 : n - 1;
-      __builtin_amdgcn_global_load_lds(
-          reinterpret_cast<const uint8_t*>(F + row * d + c0 + 4 * (f % 4)),
-          (__attribute__((address_space(3))) void*)(dst + (i * 64 * kStatLoaders + 64 * (wave - 1)) * 4), 16, 0, 0);
+      load_to_lds<16>(F + row * d + c0 + 4 * (f % 4), dst + (i * 64 * kStatLoaders + 64 * (wave - 1)) * 4);
     }
   };
   if (wave > 0) {
     for (int t = 0; t < kStatStages - 1 && t < 2 * nt; t++) issue(t);
     for (int t = 0; t < 2 * nt; t++) {
-      loads_wait_behind<kStatStages - 2, OPS>(2 * nt - 1 - t);
+      vm_wait_behind<kStatStages - 2, OPS, 0>(2 * nt - 1 - t);
       __builtin_amdgcn_s_barrier();                                    // stage t visible, stage t - 1 consumed
       if (t + kStatStages - 1 < 2 * nt) issue(t + kStatStages - 1);
     }
@@ -245,14 +234,12 @@ __global__ __launch_bounds__(64 * (MB + kInferLoaders)) void proxy_infer_kernel(
 #pragma unroll
       for (int i = 0; i < OPS; i++) {
         const int f = i * 64 * kInferLoaders + lt, j = f / 8, c = (f % 8) ^ ((j >> 1) & 7);
-        __builtin_amdgcn_global_load_lds(
-            reinterpret_cast<const uint8_t*>(W1 + (int64_t)j * d + 64 * t + 8 * c),
-            (__attribute__((address_space(3))) void*)(dst + (i * 64 * kInferLoaders + 64 * (wave - MB)) * 16), 16, 0, 0);
+        load_to_lds<16>(W1 + (int64_t)j * d + 64 * t + 8 * c, dst + (i * 64 * kInferLoaders + 64 * (wave - MB)) * 16);
       }
     };
     for (int t = 0; t < kInferStages - 1 && t < nt; t++) issue(t);
     for (int t = 0; t < nt; t++) {
-      loads_wait_behind<kInferStages - 2, OPS>(nt - 1 - t);
+      vm_wait_behind<kInferStages - 2, OPS, 0>(nt - 1 - t);
       __builtin_amdgcn_s_barrier();                    // slab t visible, slab t - 1 consumed
       if (t + kInferStages - 1 < nt) issue(t + kInferStages - 1);
     }
