@@ -741,11 +741,13 @@ kvop_status kvop_pool_stats(const kvop_pool* p, uint64_t* used, uint64_t* cap, i
 kvop_status kvop_kv_release(kvop_pool* p, const kvop_handle* hs, int32_t n) {
   if (!p || (n > 0 && !hs) || n < 0) return fail(KVOP_EINVAL, "bad arguments");
   std::vector<uint32_t> slots;
+  std::vector<bool> seen(p->slots.size());
+  slots.reserve(n);
   for (int i = 0; i < n; i++) {
     if (!lookup(p, hs[i])) return fail(KVOP_EBADHANDLE, "handle " + std::to_string(i) + " is not live in this pool");
     uint32_t s = (uint32_t)(hs[i] & 0xffffffffu);
-    if (std::find(slots.begin(), slots.end(), s) != slots.end())
-      return fail(KVOP_EBADHANDLE, "handle released twice in one call");
+    if (seen[s]) return fail(KVOP_EBADHANDLE, "handle released twice in one call");
+    seen[s] = true;
     slots.push_back(s);
   }
   for (uint32_t s : slots) {
