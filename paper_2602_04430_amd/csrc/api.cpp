@@ -1016,37 +1016,41 @@ kvop_status kvop_ea_select(kvop_pool* p, const float* scores, const int64_t* off
   if (n == 0) return KVOP_OK;
   hipStream_t st = (hipStream_t)stream;
   std::vector<int64_t> doc_off(n + 1), out_off(n + 1);
-  std::vector<int32_t> kc(n), order_of(n);
+  std::vector<int32_t> kc(n);
+  const int64_t short_rows = ea_select_short();
   int n_long = 0;
   out_off[0] = 0;
   for (int i = 0; i < n; i++) {
     const int64_t L = offsets[i + 1] - offsets[i];
     if (L < 1 || L >= kRopeMaxPos) return fail(KVOP_EINVAL, "document " + std::to_string(i) + ": bad length");
-    n_long += L > ea_select_short();
+    n_long += L > short_rows;
     doc_off[i] = offsets[i] - offsets[0];
     kc[i] = kvop_retained_count(r, L);
     out_off[i + 1] = out_off[i] + kc[i];
   }
   doc_off[n] = offsets[n] - offsets[0];
-  for (int i = 0, at_long = 0, at_short = n_long; i < n; i++)
-    order_of[doc_off[i + 1] - doc_off[i] > ea_select_short() ? at_long++ : at_short++] = i;
   kvop_model* m = p->m;
   CallOrder order(m, st);
   Mirror mir;
-  size_t o_doc = mir.add((n + 1) * 8), o_out = mir.add((n + 1) * 8), o_k = mir.add(n * 4), o_ord = mir.add(n * 4);
+  size_t o_doc = mir.add((n + 1) * 8), o_out = mir.add((n + 1) * 8), o_k = mir.add(n * 4),
+         o_ord = mir.add(n_long ? n * 4 : 0);
   if (m->stage.reserve(mir.size) != hipSuccess || m->meta.reserve(mir.size, st) != hipSuccess)
     return fail(KVOP_ENOMEM, "metadata staging");
   memcpy(m->stage.p + o_doc, doc_off.data(), (n + 1) * 8);
   memcpy(m->stage.p + o_out, out_off.data(), (n + 1) * 8);
   memcpy(m->stage.p + o_k, kc.data(), n * 4);
-  memcpy(m->stage.p + o_ord, order_of.data(), n * 4);
+  if (n_long) {   // (short documents only: in their order)
+    int32_t* order_of = (int32_t*)(m->stage.p + o_ord);
+    for (int i = 0, at_long = 0, at_short = n_long; i < n; i++)
+      order_of[doc_off[i + 1] - doc_off[i] > short_rows ? at_long++ : at_short++] = i;
+  }
   char* md = (char*)m->meta.p;
   if (hipMemcpyAsync(md, m->stage.p, mir.size, hipMemcpyHostToDevice, st) != hipSuccess ||
       hipEventRecord(m->stage.ev, st) != hipSuccess)
     return fail(KVOP_EDEVICE, "metadata upload");
   m->stage.pending = true;
   if (ea_select(scores + offsets[0], (const int64_t*)(md + o_doc), (const int32_t*)(md + o_k),
-                (const int64_t*)(md + o_out), (const int32_t*)(md + o_ord), n, n_long, idx, st) != hipSuccess)
+                (const int64_t*)(md + o_out), n_long ? (const int32_t*)(md + o_ord) : nullptr, n, n_long, idx, st) != hipSuccess)
     return fail(KVOP_EDEVICE, "selection launch");
   memcpy(idx_offsets, out_off.data(), (n + 1) * 8);
   return KVOP_OK;

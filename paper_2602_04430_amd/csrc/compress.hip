@@ -639,7 +639,7 @@ __device__ __forceinline__ void select_rows(const float* __restrict__ scores, in
 }
 
 // order: the n_long documents of more than kSelShort rows, a workgroup each, then the others, a
-// wavefront each
+// wavefront each (null: none is long)
 __global__ __launch_bounds__(kEaThreads) void ea_select_kernel(const float* __restrict__ scores,
                                                                const int64_t* __restrict__ doc_off,
                                                                const int32_t* __restrict__ kcount,
@@ -651,7 +651,7 @@ __global__ __launch_bounds__(kEaThreads) void ea_select_kernel(const float* __re
   const bool is_long = b < n_long;
   const int at = is_long ? b : n_long + (b - n_long) * NW + w;
   if (at >= n_docs) return;
-  const int d = order[at];
+  const int d = order ? order[at] : at;
   const int64_t s0 = doc_off[d];
   const int L = (int)(doc_off[d + 1] - s0), k = kcount[d];
   int32_t* out = idx + out_off[d];

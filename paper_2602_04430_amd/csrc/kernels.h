@@ -145,7 +145,7 @@ hipError_t ea_zero(float* p, int64_t n, hipStream_t st);
 hipError_t ea_finish(const float* acc, int Hkv, int rows, float* out, hipStream_t st);
 // per document d (scores rows doc_off[d] .. doc_off[d+1]): the kcount[d] highest scores, equal
 // scores lower row first, ascending document-relative rows written at idx + out_off[d].  order lists
-// the documents, first the n_long ones of more than ea_select_short() rows.
+// the documents, first the n_long ones of more than ea_select_short() rows (null: n_long is 0).
 hipError_t ea_select(const float* scores, const int64_t* doc_off, const int32_t* kcount, const int64_t* out_off,
                      const int32_t* order, int n_docs, int n_long, int32_t* idx, hipStream_t st);
 int ea_select_short();
